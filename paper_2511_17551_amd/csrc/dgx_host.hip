@@ -295,6 +295,51 @@ void clear_graph(dgx_ctx *ctx) {
 
 bool is_mix(const dgx_ctx *ctx) { return ctx->cfg.equation >= DGX_EQ_EULER_MIX; }
 
+// Fills K.G from the reaction table, or leaves K.G.ng = 0 where a reaction
+// does not have the grouped form (KinGroups).
+void group_reactions(KinC &K) {
+    KinGroups &G = K.G;
+    G = KinGroups{};
+    int ng = 0;
+    for (int r = 0; r < K.nr; ++r) {
+        int dn[kNS], partner = kNS, np = 0, left = 0, right = 0;
+        for (int s = 0; s < kNS; ++s) {
+            const int a = K.nu[r][s], b = K.nup[r][s];
+            if (a < 0 || b < 0) return;
+            dn[s] = b - a;
+            const int m = std::min(a, b);
+            if (m > 0) partner = s;
+            np += m;
+            left += std::max(-dn[s], 0);
+            right += std::max(dn[s], 0);
+        }
+        if (np > 1 || left > 2 || right > 2) return;
+        int g = 0;
+        for (; g < ng; ++g) {
+            bool same = !(G.mask[g] >> partner & 1);
+            for (int s = 0; s < kNS; ++s) same = same && G.dn[g][s] == dn[s];
+            if (same) break;
+        }
+        if (g == ng) {
+            ++ng;
+            int e[2] = {0, 2};  // next factor of either side
+            for (int s = 0; s < kNS; ++s) {
+                G.dn[g][s] = dn[s];
+                G.dn_sum[g] += dn[s];
+                G.wdn[g][s] = K.W[s] * dn[s];
+                for (int q = 0; q < std::abs(dn[s]); ++q) G.sel[g][e[dn[s] > 0]++][s] = 1.0;
+            }
+            for (int i = e[0]; i < 2; ++i) G.one[g][i] = 1.0;
+            for (int i = e[1]; i < 4; ++i) G.one[g][i] = 1.0;
+        }
+        G.mask[g] |= 1 << partner;
+        G.lnA[g][partner] = K.lnA[r];
+        G.b[g][partner] = K.b[r];
+        G.tha[g][partner] = K.tha[r];
+    }
+    G.ng = ng;
+}
+
 // Host T(e) for a single mixture state (Dirichlet boundary states).
 double host_T(const dgx_ctx *ctx, const double *u) {
     const MixC &M = ctx->mix;
@@ -600,6 +645,8 @@ static int create_body(const dgx_config *cfg, dgx_ctx **out) {
             ctx->mix.e0[s] = ctx->sp.e0[s];
             ctx->mix.mol[s] = ctx->sp.molecule[s] ? 1 : 0;
         }
+        const int *mol = ctx->mix.mol;
+        ctx->mix.std_mol = mol[0] && mol[1] && mol[2] && !mol[3] && !mol[4];
     }
     if (mix && cfg->reactions) {
         // reaction table: sources in the right-hand side (DGX_EQ_REACT_MIX)
@@ -632,6 +679,11 @@ static int create_body(const dgx_config *cfg, dgx_ctx **out) {
             K.gconst[s] = g;
         }
         K.lnpref_Ru = std::log(sp.p_ref / sp.Ru);
+        for (int s = 0; s < 5; ++s) {
+            K.iW[s] = 1.0 / sp.W[s];
+            K.th0[s] = sp.e0[s] / ctx->mix.Rs[s];
+        }
+        group_reactions(K);
     }
     for (const auto &e : kRhs) {
         if (e.dim == cfg->dim && e.N == cfg->N && e.eq == cfg->equation && e.vf == cfg->volume_flux &&
@@ -1140,12 +1192,15 @@ int dgx_chem_step(dgx_ctx *ctx, double *u, double dt, double tol, int maxit, dgx
     const double ttol = 1e-14;
     const int tmaxit = 100;
     int *subs = stats ? ctx->subs.p : nullptr;
-    if (ctx->cfg.dim == 2)
-        hipLaunchKernelGGL(k_chem<2>, dim3(blocks), dim3(tb), 0, s, u, count, dt, ctx->kin_d.p, ctx->mix, ctx->T.p, tol,
+    // the grouped rates where the mechanism has that form (KinGroups) and the
+    // molecules are the first three species; else reaction by reaction
+    const bool grp = ctx->kin.G.ng > 0 && ctx->mix.std_mol;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(tb), 0, s, u, count, dt, ctx->kin_d.p, ctx->mix, ctx->T.p, tol,
                            maxit, ttol, tmaxit, iters, subs, ctx->flags.p);
-    else
-        hipLaunchKernelGGL(k_chem<3>, dim3(blocks), dim3(tb), 0, s, u, count, dt, ctx->kin_d.p, ctx->mix, ctx->T.p, tol,
-                           maxit, ttol, tmaxit, iters, subs, ctx->flags.p);
+    };
+    if (ctx->cfg.dim == 2) grp ? launch(k_chem<2, true>) : launch(k_chem<2, false>);
+    else grp ? launch(k_chem<3, true>) : launch(k_chem<3, false>);
     if (hipGetLastError() != hipSuccess) return set_err(ctx, DGX_E_DEVICE, "chemistry launch failed");
     if (!stats) return DGX_OK;
     return collect_stats(ctx, count, maxit, stats, s, true);

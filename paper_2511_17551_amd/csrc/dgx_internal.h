@@ -24,6 +24,24 @@ struct MixC {
     double thv[kNS];   // vibrational temperature (0 for atoms)
     double e0[kNS];    // formation energy J/kg
     int mol[kNS];      // linear diatomic?
+    int std_mol;       // 1: mol is (1, 1, 1, 0, 0), the order N2, O2, NO, N, O
+};
+
+// Reactions grouped by net stoichiometry dn = nu' - nu, for the mechanisms in
+// which every reaction is a group's minimal reaction (at most two reactant
+// and two product factors) times at most one unchanged partner: dissociation
+// X2 + M <-> X + Y + M for any partner M, and exchange.  A group then shares
+// ln K_c and its two factor products, and its reactions differ by the
+// partner (slots 0..4: that species, 5: none).
+constexpr int kMaxG = kMaxR;
+struct KinGroups {
+    int ng;                       // 0: the mechanism does not have this form
+    int mask[kMaxG];              // slots in use (bit set)
+    double lnA[kMaxG][kNS + 1], b[kMaxG][kNS + 1], tha[kMaxG][kNS + 1];
+    double dn[kMaxG][kNS], dn_sum[kMaxG], wdn[kMaxG][kNS];  // dn, its sum, W_s dn_s
+    // the factors (two reactants, two products): one-hot over the species; an
+    // absent factor has no species and the value one = 1
+    double sel[kMaxG][4][kNS], one[kMaxG][4];
 };
 
 // Reaction data (device memory, read with uniform addresses).
@@ -35,6 +53,9 @@ struct KinC {
     double W[kNS];
     double gconst[kNS];             // T-independent part of -g_s/(R_s T)
     double lnpref_Ru;               // ln(p_ref / R_u)
+    double iW[kNS];                 // 1 / W_s
+    double th0[kNS];                // e0_s / R_s
+    KinGroups G;
 };
 
 // Face codes of the element-neighbour table: >= 0 conforming neighbour,

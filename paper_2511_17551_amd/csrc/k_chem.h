@@ -34,8 +34,142 @@
 
 namespace dgx {
 
-// Species sources w_s and their Jacobian dw[s][j] = d w_s / d rho_j along the
-// fixed-energy manifold, at the temperature T of the composition rs.
+// Species sources w_s (kg m^-3 s^-1) and, with JAC, their Jacobian dw[s][j] =
+// d w_s / d rho_j along the fixed-energy manifold, at the temperature T of
+// the composition rs: the mechanisms of grouped form (KinGroups) with the
+// molecules first.
+//
+// What bounds it: the dependency chains and issue of one node's arithmetic (a
+// thread per node, two waves per SIMD).  Reaction by reaction, as in
+// chem_sources below, most of the time went into uniform branches over the
+// stoichiometric coefficients (about 80 per reaction) and two library
+// exponentials per reaction.  Here a group evaluates ln K_c and its factor
+// products once; k_b = k_f / K_c comes from the two reduced exponentials and
+// the sum of their binary exponents, which neither under- nor overflows
+// before the final scaling (near 0 K, where the exponents leave the range of
+// an int, from the exponential of ln k_f - ln K_c); the factors are gathered and their derivatives
+// scattered with one-hot coefficients (exact); and the temperature part of
+// the Jacobian is one outer product at the end.  k_chem on the 64 x 128
+// cylinder (131,072 nodes, hot state): 184 us reaction by reaction, 78 us
+// grouped, so the grouped form is taken wherever it exists.
+template <bool JAC>
+__device__ __forceinline__ void chem_sources_grouped(const KinC &K, const MixC &M, const double *rs, double T,
+                                                     double *w, double (*dw)[kNS]) {
+    const KinGroups &G = K.G;
+    const double lnT = log(T);
+    const double iT = rcp(T);
+    double gRT[kNS], dgRT[kNS], conc[kNS], dTdr[kNS], wT[kNS];
+    double rhocv = 0.0;
+#pragma unroll
+    for (int s = 0; s < kNS; ++s) {
+        const bool mol = s < 3;
+        const double h = K.th0[s] * iT;            // e0_s / (R_s T)
+        double ert = (mol ? 2.5 : 1.5) + h;        // e_s / (R_s T)
+        double cvr = mol ? 2.5 : 1.5;              // cv_s / R_s
+        double g = K.gconst[s] - (mol ? 3.5 : 2.5) * lnT + h;
+        if (mol) {
+            const double x = M.thv[s] * iT;
+            double em, om;  // e^-x, 1 - e^-x
+            exp_pair(x, em, om);
+            const double io = rcp(om);
+            const double xq = x * em * io;
+            ert += xq;
+            cvr = fma(xq, x * io, cvr);
+            g += log(om);
+        }
+        gRT[s] = g;                      // g_s / (R_s T)
+        dgRT[s] = -(ert + 1.0) * iT;     // its T-derivative -h_s / (R_s T^2)
+        dTdr[s] = -M.Rs[s] * T * ert;    // -e_s, scaled below
+        rhocv = fma(rs[s] * M.Rs[s], cvr, rhocv);
+        conc[s] = rs[s] * K.iW[s];
+        w[s] = 0.0;
+        wT[s] = 0.0;
+        if (JAC) {
+#pragma unroll
+            for (int j = 0; j < kNS; ++j) dw[s][j] = 0.0;
+        }
+    }
+    const double lnpr = K.lnpref_Ru - lnT;
+#pragma unroll 1
+    for (int g = 0; g < G.ng; ++g) {
+        double mlnK = -G.dn_sum[g] * lnpr;  // -ln K_c
+        double dlnK = -G.dn_sum[g] * iT;    // d ln K_c / dT
+#pragma unroll
+        for (int s = 0; s < kNS; ++s) {
+            mlnK = fma(G.dn[g][s], gRT[s], mlnK);
+            dlnK = fma(-G.dn[g][s], dgRT[s], dlnK);
+        }
+        int nK;
+        const double mK = 1.0 + expm1_reduced(mlnK, nK);
+        const bool in_range = fabs(mlnK) < 4e8;
+        double f[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            f[i] = G.one[g][i];
+#pragma unroll
+            for (int s = 0; s < kNS; ++s) f[i] = fma(G.sel[g][i][s], conc[s], f[i]);
+        }
+        const double F = f[0] * f[1], B = f[2] * f[3];
+        // sums over the partners: k_f c_M, k_b c_M and their T-derivatives
+        double Sf = 0.0, Sb = 0.0, Tf = 0.0, Tb = 0.0, val[kNS];
+#pragma unroll
+        for (int j = 0; j < kNS; ++j) val[j] = 0.0;
+        const int mask = G.mask[g];
+        auto partner = [&](int m, double c) {
+            const double lnkf = fma(G.b[g][m], lnT, G.lnA[g][m]) - G.tha[g][m] * iT;
+            const double dl = fma(G.tha[g][m], iT, G.b[g][m]) * iT;
+            int n;
+            const double mf = 1.0 + expm1_reduced(lnkf, n);
+            const double kf = ldexp(mf, n);
+            double kb = ldexp(mf * mK, n + nK);
+            if (!in_range) {
+                const double mb = 1.0 + expm1_reduced(lnkf + mlnK, n);
+                kb = ldexp(mb, n);
+            }
+            const double cf = kf * c, cb = kb * c;
+            Sf += cf;
+            Sb += cb;
+            if (JAC) {
+                Tf = fma(cf, dl, Tf);
+                Tb = fma(cb, dl - dlnK, Tb);
+                if (m < kNS) val[m] = kf * F - kb * B;
+            }
+        };
+#pragma unroll
+        for (int m = 0; m < kNS; ++m)
+            if (mask >> m & 1) partner(m, conc[m]);
+        if (mask >> kNS & 1) partner(kNS, 1.0);
+        const double R = Sf * F - Sb * B;
+#pragma unroll
+        for (int s = 0; s < kNS; ++s) w[s] = fma(G.wdn[g][s], R, w[s]);
+        if (JAC) {
+            const double dRdT = Tf * F - Tb * B;
+            const double d0 = Sf * f[1], d1 = Sf * f[0], d2 = -Sb * f[3], d3 = -Sb * f[2];
+#pragma unroll
+            for (int j = 0; j < kNS; ++j) {
+                double v = fma(G.sel[g][0][j], d0, val[j]);
+                v = fma(G.sel[g][1][j], d1, v);
+                v = fma(G.sel[g][2][j], d2, v);
+                v = fma(G.sel[g][3][j], d3, v) * K.iW[j];  // dR / d rho_j at fixed T
+#pragma unroll
+                for (int s = 0; s < kNS; ++s) dw[s][j] = fma(G.wdn[g][s], v, dw[s][j]);
+            }
+#pragma unroll
+            for (int s = 0; s < kNS; ++s) wT[s] = fma(G.wdn[g][s], dRdT, wT[s]);
+        }
+    }
+    if (JAC) {
+        const double irc = rcp(rhocv);
+#pragma unroll
+        for (int j = 0; j < kNS; ++j) {
+            const double dT = dTdr[j] * irc;
+#pragma unroll
+            for (int s = 0; s < kNS; ++s) dw[s][j] = fma(wT[s], dT, dw[s][j]);
+        }
+    }
+}
+
+// The same for any mechanism, reaction by reaction.
 __device__ __forceinline__ void chem_sources(const KinC &K, const MixC &M, const double *rs, double T, double *w,
                                              double (*dw)[kNS]) {
     const double lnT = log(T);
@@ -132,6 +266,7 @@ __device__ __forceinline__ void chem_sources(const KinC &K, const MixC &M, const
 // x = A^{-1} b for the 5x5 system (Gaussian elimination, partial pivoting;
 // row exchanges by selects so that the arrays stay in registers).
 __device__ __forceinline__ void solve5(double (*A)[kNS], double *b, double *x) {
+    double ip[kNS];  // 1 / pivot
 #pragma unroll
     for (int c = 0; c < kNS; ++c) {
         // pivot: the largest |A[k][c]|, k >= c, swapped into row c
@@ -156,10 +291,10 @@ __device__ __forceinline__ void solve5(double (*A)[kNS], double *b, double *x) {
             b[c] = sw ? b[k] : b[c];
             b[k] = sw ? t : b[k];
         }
-        const double ip = rcp(A[c][c]);
+        ip[c] = rcp(A[c][c]);
 #pragma unroll
         for (int k = c + 1; k < kNS; ++k) {
-            const double f = A[k][c] * ip;
+            const double f = A[k][c] * ip[c];
 #pragma unroll
             for (int j = c + 1; j < kNS; ++j) A[k][j] = fma(-f, A[c][j], A[k][j]);
             b[k] = fma(-f, b[c], b[k]);
@@ -170,7 +305,7 @@ __device__ __forceinline__ void solve5(double (*A)[kNS], double *b, double *x) {
         double s = b[c];
 #pragma unroll
         for (int j = c + 1; j < kNS; ++j) s = fma(-A[c][j], x[j], s);
-        x[c] = s / A[c][c];
+        x[c] = s * ip[c];
     }
 }
 
@@ -180,17 +315,23 @@ constexpr double kChemStall = 1e-3;  // a step cut below this fraction twice in 
 // Damped Newton for one backward-Euler step over h from ra into rs.  Tn: the
 // temperature of ra on entry, of rs on a converged exit.  Adds the
 // iterations to it; returns false if the iteration failed.
+template <bool GRP>
 __device__ __forceinline__ bool chem_newton(const KinC &K, const MixC &M, const double *ra, double *rs, double rho,
                                             double rhoe, double h, double &Tn, double tol, int maxit, double ttol,
                                             int tmaxit, int &it) {
 #pragma unroll
     for (int s = 0; s < kNS; ++s) rs[s] = ra[s];
+    // (grouped form: std_mol holds)
+    auto solve_T = [&]() {
+        return GRP ? mix_newton_t<true>(M, rs, rhoe, Tn, ttol, tmaxit) : mix_newton(M, rs, rhoe, Tn, ttol, tmaxit);
+    };
     int low = 0;
     for (int k = 0; k < maxit; ++k) {
         ++it;
-        if (mix_newton(M, rs, rhoe, Tn, ttol, tmaxit) < 0 || !(Tn > 0.0)) return false;
+        if (solve_T() < 0 || !(Tn > 0.0)) return false;
         double w[kNS], A[kNS][kNS], G[kNS], d[kNS];
-        chem_sources(K, M, rs, Tn, w, A);
+        if constexpr (GRP) chem_sources_grouped<true>(K, M, rs, Tn, w, A);
+        else chem_sources(K, M, rs, Tn, w, A);
 #pragma unroll
         for (int s = 0; s < kNS; ++s) {
             G[s] = -(rs[s] - ra[s] - h * w[s]);
@@ -211,7 +352,7 @@ __device__ __forceinline__ bool chem_newton(const KinC &K, const MixC &M, const 
 #pragma unroll
         for (int s = 0; s < kNS; ++s) rs[s] = fma(theta, d[s], rs[s]);
         if (!(dmax == dmax)) return false;
-        if (dmax <= tol * rho) return mix_newton(M, rs, rhoe, Tn, ttol, tmaxit) >= 0;
+        if (dmax <= tol * rho) return solve_T() >= 0;
         low = theta < kChemStall ? low + 1 : 0;
         if (low >= 2) return false;
     }
@@ -219,15 +360,16 @@ __device__ __forceinline__ bool chem_newton(const KinC &K, const MixC &M, const 
 }
 
 // Chemistry over dt per node, in place on the species rows of u
-// ([nvar][count], species first).  Two waves per SIMD: the Newton state,
-// the 5x5 Jacobian and the per-reaction terms need about 280 registers, and
-// one wave per SIMD leaves the long dependency chains (T solve, rates,
-// elimination) unhidden; the compiler spills 33 VGPRs at this bound, a
-// better trade (1.45x on the 131,072-node cylinder) than one wave.  T holds the incoming state's temperature
+// ([nvar][count], species first).  GRP: the grouped rates.  Two waves per
+// SIMD: the Newton state, the 5x5 Jacobian and the rate terms need about 280
+// registers, and one wave per SIMD leaves the long dependency chains (T
+// solve, rates, elimination) unhidden; the compiler spills about 27 VGPRs at
+// this bound, a better trade (1.45x on the 131,072-node cylinder) than one
+// wave.  T holds the incoming state's temperature
 // on entry (warm start) and the new one on exit; iters (optional) the Newton
 // iterations summed over the substeps, -1 if the node did not converge;
 // subs (optional) the number of substeps.
-template <int DIM>
+template <int DIM, bool GRP>
 __global__ void __launch_bounds__(256, 2) k_chem(double *__restrict__ u, int64_t count, double dt, const KinC *kin,
                                               MixC M, double *__restrict__ T, double tol, int maxit, double ttol,
                                               int tmaxit, int *__restrict__ iters, int *__restrict__ subs,
@@ -260,7 +402,7 @@ __global__ void __launch_bounds__(256, 2) k_chem(double *__restrict__ u, int64_t
         }
         double rs[kNS];
         double Tn = Ta;
-        if (chem_newton(K, M, ra, rs, rho, rhoe, ldexp(dt, -lev), Tn, tol, maxit, ttol, tmaxit, it)) {
+        if (chem_newton<GRP>(K, M, ra, rs, rho, rhoe, ldexp(dt, -lev), Tn, tol, maxit, ttol, tmaxit, it)) {
 #pragma unroll
             for (int s = 0; s < kNS; ++s) ra[s] = rs[s];
             Ta = Tn;

@@ -133,41 +133,85 @@ __device__ __forceinline__ double inv_ln_mean(double x, double y) {
 }
 
 // ---------------------------------------------------------------- mixture
-// e^-x and 1 - e^-x from one transcendental: whichever of the two is at
-// least 1 - e^-1/2 (about 0.39) comes from the other by a subtraction that
-// keeps it within about 2 ulp (x below 1/2: expm1, so that 1 - e^-x keeps
-// its digits as x -> 0; above: exp).
-__device__ __forceinline__ void exp_pair(double x, double &em, double &om) {
-    if (x < 0.5) {
-        om = -expm1(-x);
-        em = 1.0 - om;
-    } else {
-        em = exp(-x);
-        om = 1.0 - em;
-    }
+// Argument reduction of the exponential: y = n ln 2 + r with |r| <= ln(2)/2;
+// returns e^r - 1 to its last digits (Taylor to r^13: remainder below 4e-18
+// on this range), so that e^y = 2^n (1 + p).  y is cut at +-7e8, where n still
+// fits an int (so do sums of two such n) and 2^n has long under- or
+// overflowed (a NaN is cut too: callers use T beside it, which carries it on).
+__device__ __forceinline__ double expm1_reduced(double y, int &n) {
+    y = fmin(fmax(y, -7e8), 7e8);
+    // round y / ln 2 to an integer in the low bits of t
+    const double t = fma(y, 1.4426950408889634, 6755399441055744.0);
+    const double k = t - 6755399441055744.0;
+    n = (int)(unsigned)__double_as_longlong(t);
+    // ln 2 as its double and the remainder
+    const double r = fma(-k, 2.3190468138462996e-17, fma(-k, 0.69314718055994529, y));
+    double q = 1.0 / 6227020800.0;
+    q = fma(q, r, 1.0 / 479001600.0);
+    q = fma(q, r, 1.0 / 39916800.0);
+    q = fma(q, r, 1.0 / 3628800.0);
+    q = fma(q, r, 1.0 / 362880.0);
+    q = fma(q, r, 1.0 / 40320.0);
+    q = fma(q, r, 1.0 / 5040.0);
+    q = fma(q, r, 1.0 / 720.0);
+    q = fma(q, r, 1.0 / 120.0);
+    q = fma(q, r, 1.0 / 24.0);
+    q = fma(q, r, 1.0 / 6.0);
+    q = fma(q, r, 0.5);
+    return fma(r * r, q, r);
 }
 
-__device__ __forceinline__ void mix_energy_cv(const MixC &M, const double *rs, double T,
-                                              double &rhoe, double &rhocv) {
-    double e = 0.0, cv = 0.0;
+// e^-x and 1 - e^-x from one reduction, without a branch: with e^-x =
+// 2^n (1 + p), 1 - e^-x = (1 - 2^n) - 2^n p, which is -p itself for small x
+// (n = 0, no cancellation) and is at least 0.29 otherwise.
+__device__ __forceinline__ void exp_pair(double x, double &em, double &om) {
+    int n;
+    const double p = expm1_reduced(-x, n);
+    const double s = ldexp(1.0, n);
+    em = fma(s, p, s);
+    om = fma(-s, p, 1.0 - s);
+}
+
+// Which species are molecules: with STD the documented order (N2, O2, NO, N,
+// O), known at compile time, so that the three vibrational terms are
+// evaluated side by side; else the flags of the species table, tested one
+// species after another.  MixC::std_mol says which of the two holds.
+template <bool STD>
+__device__ __forceinline__ bool mix_is_mol(const MixC &M, int s) {
+    return STD ? s < 3 : M.mol[s] != 0;
+}
+
+// Vibrational energy sum_s rho_s R_s theta_s/(e^x - 1) and its T-derivative,
+// x = theta_s/T.
+template <bool STD>
+__device__ __forceinline__ void mix_vib(const MixC &M, const double *rs, double T, double &ev, double &cv) {
+    const double iT = rcp(T);
+    ev = 0.0;
+    cv = 0.0;
 #pragma unroll
     for (int s = 0; s < kNS; ++s) {
-        double es = 1.5 * M.Rs[s] * T + M.e0[s];
-        double cs = 1.5 * M.Rs[s];
-        if (M.mol[s]) {
-            const double x = M.thv[s] * rcp(T);
+        if (mix_is_mol<STD>(M, s)) {
+            const double x = M.thv[s] * iT;
             double em, om;  // e^-x, 1 - e^-x
             exp_pair(x, em, om);
             // R theta/(e^x - 1) = R theta e^-x / (1 - e^-x); its T-derivative R x^2 e^-x / (1 - e^-x)^2
-            const double q = em * rcp(om);
-            es += M.Rs[s] * T + M.Rs[s] * M.thv[s] * q;
-            cs += M.Rs[s] + M.Rs[s] * x * x * q * rcp(om);
+            const double io = rcp(om);
+            const double q = em * io;
+            const double c = rs[s] * M.Rs[s];
+            ev = fma(c * M.thv[s], q, ev);
+            cv = fma(c * x * x, q * io, cv);
         }
-        e = fma(rs[s], es, e);
-        cv = fma(rs[s], cs, cv);
     }
-    rhoe = e;
-    rhocv = cv;
+}
+
+// Heat capacity density without vibration: 3/2 R_s per atom, 5/2 R_s per
+// linear molecule.
+template <bool STD>
+__device__ __forceinline__ double mix_cv_rigid(const MixC &M, const double *rs) {
+    double a = 0.0;
+#pragma unroll
+    for (int s = 0; s < kNS; ++s) a = fma(rs[s], mix_is_mol<STD>(M, s) ? 2.5 * M.Rs[s] : 1.5 * M.Rs[s], a);
+    return a;
 }
 
 // Newton iteration on sum rho_s e_s(T) = rho e, from T0; returns iterations,
@@ -176,21 +220,42 @@ __device__ __forceinline__ void mix_energy_cv(const MixC &M, const double *rs, d
 // |rho e| + sum_s |rho_s e0_s|): where the thermal energy is itself that small
 // (near-vacuum gas left by the positivity limiter, T of order 1e-10 K) no
 // iterate meets a relative test, and T is as accurate as the data allow.
-__device__ __forceinline__ int mix_newton(const MixC &M, const double *rs, double rhoe_target,
-                                          double &T, double tol, int maxit) {
-    double floor = fabs(rhoe_target);
+// What bounds it: the FP64 issue of the exponentials.  Each iteration is one
+// reciprocal of T, three exponentials and reciprocals (mix_vib) and one
+// Newton quotient; the parts linear in T (rho cv without vibration, the
+// formation energies) are summed once before the loop.  With the library's
+// exp and expm1 (two branches) and the per-species sums inside the loop, the
+// indicator with this solve took 55 us on the curved 24^3 N = 4 mesh; now 45.
+template <bool STD>
+__device__ __forceinline__ int mix_newton_t(const MixC &M, const double *rs, double rhoe_target, double &T,
+                                            double tol, int maxit) {
+    double floor = fabs(rhoe_target), b = -rhoe_target;
 #pragma unroll
-    for (int s = 0; s < kNS; ++s) floor = fma(fabs(rs[s]), fabs(M.e0[s]), floor);
+    for (int s = 0; s < kNS; ++s) {
+        floor = fma(fabs(rs[s]), fabs(M.e0[s]), floor);
+        b = fma(rs[s], M.e0[s], b);
+    }
     floor *= 8.0 * 2.220446049250313e-16;
+    const double a = mix_cv_rigid<STD>(M, rs);
+#pragma unroll 1
     for (int it = 1; it <= maxit; ++it) {
-        double f, fp;
-        mix_energy_cv(M, rs, T, f, fp);
-        const double r = f - rhoe_target;
-        const double dT = r / fp;
+        double ev, cv;
+        mix_vib<STD>(M, rs, T, ev, cv);
+        const double r = fma(a, T, b) + ev;
+        // r / fp with a residual correction (the quotient to its last digit)
+        const double fp = a + cv, ifp = rcp(fp);
+        double dT = r * ifp;
+        dT = fma(fma(-fp, dT, r), ifp, dT);
         T -= dT;
         if (fabs(dT) <= tol * fabs(T) || fabs(r) <= floor) return it;
     }
     return -1;
+}
+
+__device__ __forceinline__ int mix_newton(const MixC &M, const double *rs, double rhoe_target, double &T, double tol,
+                                          int maxit) {
+    return M.std_mol ? mix_newton_t<true>(M, rs, rhoe_target, T, tol, maxit)
+                     : mix_newton_t<false>(M, rs, rhoe_target, T, tol, maxit);
 }
 
 __device__ __forceinline__ double mix_rR(const MixC &M, const double *rs) {
@@ -202,21 +267,17 @@ __device__ __forceinline__ double mix_rR(const MixC &M, const double *rs) {
 
 // Frozen sound speed sqrt(gamma_f p / rho), gamma_f = 1 + sum rho_s R_s / sum rho_s cv_s.
 __device__ __forceinline__ double mix_sound(const MixC &M, const double *rs, double rho, double T) {
-    double cv = 0.0;
-#pragma unroll
-    for (int s = 0; s < kNS; ++s) {
-        double cs = 1.5 * M.Rs[s];
-        if (M.mol[s]) {
-            const double x = M.thv[s] * rcp(T);
-            double em, om;
-            exp_pair(x, em, om);
-            cs += M.Rs[s] + M.Rs[s] * x * x * em * rcp(om * om);
-        }
-        cv = fma(rs[s], cs, cv);
+    double ev, cv;
+    if (M.std_mol) {
+        mix_vib<true>(M, rs, T, ev, cv);
+        cv += mix_cv_rigid<true>(M, rs);
+    } else {
+        mix_vib<false>(M, rs, T, ev, cv);
+        cv += mix_cv_rigid<false>(M, rs);
     }
     const double rR = mix_rR(M, rs);
-    const double g = 1.0 + rR / cv;
-    return wave_sqrt(g * rR * T / rho);
+    const double g = fma(rR, rcp(cv), 1.0);
+    return wave_sqrt(g * rR * T * rcp(rho));
 }
 
 // State of a node from its conserved vector (and T for a mixture).

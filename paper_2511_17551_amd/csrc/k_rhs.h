@@ -157,7 +157,11 @@ struct RhsShape {
     static constexpr int B1 = PDC * NVP;
     static constexpr int B2 = NFV * NV;
     static constexpr int B3 = NSFC * NV;
-    static constexpr int M12 = B1 > B2 ? B1 : B2;
+    // entropy-conservative mixture flux: two of the node exponentials lie
+    // behind the pair fluxes (the others take the place of rho E and c)
+    static constexpr bool ECM = MIX && VF == 0;
+    static constexpr int B1E = ECM ? B1 + 2 * NN : B1;
+    static constexpr int M12 = B1E > B2 ? B1E : B2;
     static constexpr int BUF = M12 > B3 ? M12 : B3;
     // curved: one metric row per node (the current direction); J and the
     // face normals are read from memory
@@ -342,6 +346,7 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     };
 
     double ku[S::KEEPU ? NV : 1];  // the own state, kept for the stage update
+    double T_own = 1.0;
     // ---- stage the element: primitives (+ species, metric terms)
     {
         double uo[NV];
@@ -359,6 +364,7 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
                 if (node < GA) sJa[node] = P.geo[(size_t)e * GA + node];
             }
             if constexpr (MIX) Tn = P.T[gi];
+            T_own = Tn;
         } else {
 #pragma unroll
             for (int v = 0; v < NV; ++v) uo[v] = 1.0;
@@ -603,12 +609,29 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
 #pragma unroll
     for (int v = 0; v < NV; ++v) dg[v] = 0.0;
     const double gm1_inv = 1.0 / (gamma - 1.0);
+    // entropy-conservative mixture flux: beta = 1/T and the node's
+    // exponentials, evaluated once per node, replace rho E and c (read no more)
+    // and follow the pair fluxes
+    static_assert(!S::ECM || kEcMol == 3, "LDS places of the node exponentials");
+    [[maybe_unused]] const int off_e1 = PDC * NVP;  // E[1], E[2] in the buffer
+    EcNode<DIM> own_ec;
+    if constexpr (S::ECM) {
+        if (valid) {
+            double v[DIM];
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) v[c] = sq[(1 + c) * NN + node];
+            ec_node<DIM>(ku, v, T_own, P.M, own_ec);
+            sq[(2 + DIM) * NN + node] = own_ec.beta;
+            sq[(3 + DIM) * NN + node] = own_ec.E[0];
+            buf[off_e1 + node] = own_ec.E[1];
+            buf[off_e1 + NN + node] = own_ec.E[2];
+        }
+        __syncthreads();
+    }
     // the configured two-point volume flux F#(A, B; nbar) from node states
     // (for the perfect-gas entropy-conservative flux see ec_pair)
     auto volume_flux = [&](const St<DIM, MIX> &A, const St<DIM, MIX> &B, const double *nbar, double *F) {
-        if constexpr (VF == 0) {
-            if constexpr (MIX) ec_mixture_state<DIM>(A, B, nbar, P.M, F);
-        } else if constexpr (VF == 1) {
+        if constexpr (VF == 1) {
             ducros_state<DIM, MIX>(A, B, nbar, F);
         } else if constexpr (VF == 4) {
             central_state<DIM, MIX>(A, B, nbar, F);
@@ -629,20 +652,98 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
                            esq[(1 + DIM) * NN + nb], esq[QB * NN + nb], nbar, gm1_inv, F);
     };
     // circulant pairs (below): the own node's state and current metric row
-    // stay in registers for the whole volume term (not with the entropy-
-    // conservative mixture flux, whose registers would then cost a wave)
-    constexpr bool CIRC_K = PDC == NN && (N1 % 2 == 1) && 2 * NCH == N1 - 1 && !S::EC && !(MIX && VF == 0);
+    // stay in registers for the whole volume term
+    constexpr bool CIRC_K = PDC == NN && (N1 % 2 == 1) && 2 * NCH == N1 - 1 && !S::EC;
+    static_assert(!S::ECM || CIRC_K, "the entropy-conservative mixture flux is built for the circulant pairs");
     St<DIM, MIX> own_st;
     double own_row[DIM];
     if constexpr (CIRC_K) {
-        if (valid) lds_state<DIM, MIX>(su, sq, NN, node, gamma, own_st);
+        if (!S::ECM && valid) lds_state<DIM, MIX>(su, sq, NN, node, gamma, own_st);
         if constexpr (CURV) {
 #pragma unroll
             for (int c = 0; c < DIM; ++c) own_row[c] = valid ? sJa[c * NN + node] : 0.0;
         }
     }
+    // the epilogue's loads, issued as late as their latency can still overlap
+    // something
+    auto load_epilogue = [&]() {
+        const bool st = valid && mode != 0;
+        const bool s0 = st && P.sa != 0.0;
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) {
+        for (int v = 0; v < NV; ++v) {
+            if constexpr (S::KEEPU) eu[v] = ku[v];
+            else eu[v] = st ? P.u[v * stride + gi] : 0.0;
+            eu0[v] = s0 ? P.u0[v * stride + gi] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < NW; ++k) evp[k] = (EQ == 1 && valid) ? P.vpart[(size_t)k * stride + gi] : 0.0;
+        if constexpr (CURV) Jc = valid ? P.Jn[gi] : 1.0;
+    };
+    if constexpr (S::ECM) {
+        // the circulant pairs described below, with the loops over directions
+        // and offsets kept: the flux is about 1,200 instructions, and six
+        // copies of it do not fit the instruction cache
+        // (the sums go to acc, with 1 - alpha in the coefficients: nine
+        // registers fewer)
+        int rem = node, step = 1;
+        const double hi = 1.0 - alpha;
+#pragma unroll 1
+        for (int d = 0; d < DIM; ++d) {
+            double jnext[DIM];
+#pragma unroll
+            for (int c = 0; c < DIM; ++c)
+                jnext[c] = (valid && d + 1 < DIM) ? P.geo[((d + 1) * DIM + c) * stride + gi] : 0.0;
+            const int a = rem % N1;
+            rem /= N1;
+#pragma unroll 1
+            for (int j = 1; j <= NCH; ++j) {
+                if (valid) {
+                    const int cb = a + j >= N1 ? a + j - N1 : a + j;
+                    const int nb = node + (cb - a) * step;
+                    double nbar[DIM], F[NV];
+#pragma unroll
+                    for (int c = 0; c < DIM; ++c) nbar[c] = 0.5 * (own_row[c] + sJa[c * NN + nb]);
+                    EcNode<DIM> B;
+#pragma unroll
+                    for (int k = 0; k < kNS; ++k) B.rs[k] = su[k * NN + nb];
+#pragma unroll
+                    for (int c = 0; c < DIM; ++c) B.v[c] = sq[(1 + c) * NN + nb];
+                    B.beta = sq[(2 + DIM) * NN + nb];
+                    B.rR = sq[(1 + DIM) * NN + nb] * B.beta;  // p / T
+                    B.E[0] = sq[(3 + DIM) * NN + nb];
+                    B.E[1] = buf[off_e1 + nb];
+                    B.E[2] = buf[off_e1 + NN + nb];
+                    ec_mixture_pair<DIM>(own_ec, B, nbar, P.M, F);
+                    const double coef = hi * sDc[a * N1 + cb];
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) {
+                        buf[node * NVP + v] = F[v];
+                        acc[v] = fma(coef, F[v], acc[v]);
+                    }
+                }
+                __syncthreads();
+                if (j == NCH && d + 1 < DIM && valid) {
+#pragma unroll
+                    for (int c = 0; c < DIM; ++c) {
+                        sJa[c * NN + node] = jnext[c];
+                        own_row[c] = jnext[c];
+                    }
+                }
+                if (valid) {
+                    const int a2 = a - j < 0 ? a - j + N1 : a - j;
+                    const int src = node + (a2 - a) * step;
+                    const double coef = hi * sDc[a * N1 + a2];
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) acc[v] = fma(coef, buf[src * NVP + v], acc[v]);
+                }
+                __syncthreads();
+            }
+            step *= N1;
+        }
+        load_epilogue();
+    }
+#pragma unroll
+    for (int d = 0; d < (S::ECM ? 0 : DIM); ++d) {
         // curved elements: the next direction's metric row, loaded now and
         // stored once this direction's pair fluxes are done
         double jnext[DIM];
@@ -761,19 +862,7 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
                     }
                 }
             }
-            if (d == DIM - 1 && ch == NCH - 1) {
-                const bool st = valid && mode != 0;
-                const bool s0 = st && P.sa != 0.0;
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    if constexpr (S::KEEPU) eu[v] = ku[v];
-                    else eu[v] = st ? P.u[v * stride + gi] : 0.0;
-                    eu0[v] = s0 ? P.u0[v * stride + gi] : 0.0;
-                }
-#pragma unroll
-                for (int k = 0; k < NW; ++k) evp[k] = (EQ == 1 && valid) ? P.vpart[(size_t)k * stride + gi] : 0.0;
-                if constexpr (CURV) Jc = valid ? P.Jn[gi] : 1.0;
-            }
+            if (d == DIM - 1 && ch == NCH - 1) load_epilogue();
             __syncthreads();
             if constexpr (CURV) {
                 // every pair of this direction has read the row: replace it
@@ -825,7 +914,7 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     const double iJ = 1.0 / (CURV ? Jc : sJa[DIM * DIM]);
     double du[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) du[v] = -fma(1.0 - alpha, dg[v], acc[v]) * iJ;
+    for (int v = 0; v < NV; ++v) du[v] = -(S::ECM ? acc[v] : fma(1.0 - alpha, dg[v], acc[v])) * iJ;
 
     // ---- BR1 viscous divergence (perfect-gas Navier-Stokes, affine elements).
     // The gradient kernel wrote the element-local part (volume divergence and
@@ -983,8 +1072,11 @@ __device__ __forceinline__ void mortar_item(const RhsParams &P, int m, int t) {
 
 
 
+// (the entropy-conservative mixture flux is held to three waves per SIMD, what
+// its LDS allows: 22 registers spill, outside the pair loop; 143 -> 137 us per
+// right-hand side against two waves at 215 registers)
 template <int DIM, int N, int EQ, int VF, int SF, bool CURV, bool MORT = false, int CHF = 0>
-__global__ void __launch_bounds__(512) k_rhs(RhsParams P, int mode) {
+__global__ void __launch_bounds__(512, (EQ >= 2 && VF == 0) ? 3 : 2) k_rhs(RhsParams P, int mode) {
     const int e0 = (P.xcd ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x) * P.epb;
     rhs_chunk<DIM, N, EQ, VF, SF, CURV, MORT, CHF>(P, mode, e0);
 }

@@ -58,42 +58,65 @@ __device__ __forceinline__ double wave_sqrt(double x) {
     return fma(d, h, g);
 }
 
+// One step a b + c of a polynomial with a constant c, and its first step
+// a c1 + c0.  The constant stays in scalar registers (opaque to the compiler's
+// constant handling) and enters with a negation, which only the three-address
+// form of the instruction takes.  Left to itself the compiler chooses the
+// two-address form, whose addend is a vector register, and writes every
+// constant there first: two more vector instructions per step (2,200 of the
+// 11,000 of the entropy-conservative mixture kernel).
+// fma_kv keeps the constant where it is used (inside a loop it is written
+// again in each turn, by the scalar unit, instead of being held in scalar
+// registers that run out).
+__device__ __forceinline__ double fma_k(double a, double b, double c) {
+    double k = -c;
+    asm("" : "+s"(k));
+    return fma(a, b, -k);
+}
+__device__ __forceinline__ double fma_kv(double a, double b, double c) {
+    double k = -c;
+    asm volatile("" : "+s"(k));
+    return fma(a, b, -k);
+}
+__device__ __forceinline__ double poly_start(double a, double c1, double c0) { return fma(a, c1, c0); }
+
 // Logarithmic mean (y - x)/ln(y/x) and its reciprocal.  With f = (y-x)/(y+x)
 // and z = f^2, ln(y/x) = 2 atanh f, so the mean is (x+y)/(2 A(z)) with
 // A(z) = atanh(sqrt z)/sqrt z = sum_n z^n/(2n+1).  Three branches by z:
 //   * z < 1e-4: A to four terms, and for the mean 1/A expanded,
 //     1 - z/3 - 4z^2/45 - 44z^3/945 (remainder < 1e-17 relative), which
 //     saves a reciprocal;
-//   * z < 0.02 (ratios y/x up to 1.33): A, and 1/A, to ten terms; the
-//     coefficients of 1/A come from the exact inversion of the series of A
-//     (truncation below 1e-18 relative on this range);
+//   * z < 1/9 (ratios y/x up to 2): 1/A and 2A as polynomials of degree 10,
+//     interpolated at the Chebyshev nodes of [0, 1/9] with the value at 0 held
+//     exact (relative error below 3e-18 and 7e-18 with the coefficients in
+//     double; the Taylor series of the same degree reaches z = 0.02);
 //   * beyond: the logarithm.
-__device__ __forceinline__ double inv_atanh_ratio10(double z) {
-    // 1/A(z), degree 9
-    double r = -74185965772.0 / 7795859096025.0;
-    r = fma(r, z, -5472607916.0 / 488462349375.0);
-    r = fma(r, z, -25865068.0 / 1915538625.0);
-    r = fma(r, z, -10719068.0 / 638512875.0);
-    r = fma(r, z, -10196.0 / 467775.0);
-    r = fma(r, z, -428.0 / 14175.0);
-    r = fma(r, z, -44.0 / 945.0);
-    r = fma(r, z, -4.0 / 45.0);
-    r = fma(r, z, -1.0 / 3.0);
-    return fma(r, z, 1.0);
+__device__ __forceinline__ double inv_atanh_ratio(double z) {
+    // 1/A(z), 0 <= z <= 1/9
+    double r = poly_start(z, -0.013685267223330775, -0.008103049428699534);
+    r = fma_kv(r, z, -0.011397025330915855);
+    r = fma_kv(r, z, -0.013487086275031281);
+    r = fma_kv(r, z, -0.01678833152650204);
+    r = fma_kv(r, z, -0.02179678054953089);
+    r = fma_kv(r, z, -0.030194003931586527);
+    r = fma_kv(r, z, -0.046560846557320394);
+    r = fma_kv(r, z, -0.0888888888889008);
+    r = fma_kv(r, z, -1.0 / 3.0);
+    return fma_kv(r, z, 1.0);
 }
 
-__device__ __forceinline__ double atanh_ratio10_x2(double z) {
-    // 2 A(z), degree 9
-    double r = 2.0 / 19.0;
-    r = fma(r, z, 2.0 / 17.0);
-    r = fma(r, z, 2.0 / 15.0);
-    r = fma(r, z, 2.0 / 13.0);
-    r = fma(r, z, 2.0 / 11.0);
-    r = fma(r, z, 2.0 / 9.0);
-    r = fma(r, z, 2.0 / 7.0);
-    r = fma(r, z, 2.0 / 5.0);
-    r = fma(r, z, 2.0 / 3.0);
-    return fma(r, z, 2.0);
+__device__ __forceinline__ double atanh_ratio_x2(double z) {
+    // 2 A(z), 0 <= z <= 1/9
+    double r = poly_start(z, 0.16164938169471338, 0.08800317650868773);
+    r = fma_kv(r, z, 0.12001155182857778);
+    r = fma_kv(r, z, 0.13314135550881162);
+    r = fma_kv(r, z, 0.15385570592912243);
+    r = fma_kv(r, z, 0.18181789417326447);
+    r = fma_kv(r, z, 0.22222222717801782);
+    r = fma_kv(r, z, 0.2857142856710506);
+    r = fma_kv(r, z, 0.40000000000014596);
+    r = fma_kv(r, z, 2.0 / 3.0);
+    return fma_kv(r, z, 2.0);
 }
 
 __device__ __forceinline__ double ln_mean(double x, double y) {
@@ -104,11 +127,11 @@ __device__ __forceinline__ double ln_mean(double x, double y) {
         const double q = d * rcp(s);
         const double z = q * q;
         const double h = 0.5 * s;
-        return fma(-h * z, 1.0 / 3.0 + z * (4.0 / 45.0 + z * (44.0 / 945.0)), h);
+        return fma(-h * z, fma_kv(z, poly_start(z, 44.0 / 945.0, 4.0 / 45.0), 1.0 / 3.0), h);
     }
-    if (d2 < 0.02 * s2) {
+    if (d2 < (1.0 / 9.0) * s2) {
         const double q = d * rcp(s);
-        return 0.5 * s * inv_atanh_ratio10(q * q);
+        return 0.5 * s * inv_atanh_ratio(q * q);
     }
     return d * rcp(log(y * rcp(x)));
 }
@@ -121,15 +144,44 @@ __device__ __forceinline__ double inv_ln_mean(double x, double y) {
         const double rs = rcp(s);
         const double q = d * rs;
         const double z = q * q;
-        const double P = 2.0 + z * (2.0 / 3.0 + z * (2.0 / 5.0 + z * (2.0 / 7.0)));
-        return P * rs;
+        return fma_kv(z, fma_kv(z, poly_start(z, 2.0 / 7.0, 2.0 / 5.0), 2.0 / 3.0), 2.0) * rs;
     }
-    if (d2 < 0.02 * s2) {
+    if (d2 < (1.0 / 9.0) * s2) {
         const double rs = rcp(s);
         const double q = d * rs;
-        return atanh_ratio10_x2(q * q) * rs;
+        return atanh_ratio_x2(q * q) * rs;
     }
     return log(y * rcp(x)) * rcp(d);
+}
+
+// The same where nine of them meet in one flux (the mixture's entropy-
+// conservative one): a single polynomial range, so that the usual pair takes
+// no branch, and for ratios above 2 the logarithm from the quotient of the
+// mantissas, ln(y/x) = k ln 2 + 2 f A(f^2) with f = (my - mx)/(my + mx),
+// |f| <= 1/3: the same polynomial, without a library logarithm.
+__device__ __forceinline__ double ln_ratio_far(double x, double y) {
+    const double mx = __builtin_amdgcn_frexp_mant(x), my = __builtin_amdgcn_frexp_mant(y);
+    const int k = __builtin_amdgcn_frexp_exp(y) - __builtin_amdgcn_frexp_exp(x);
+    const double q = (my - mx) * rcp(my + mx);
+    return fma((double)k, 0.69314718055994529, q * atanh_ratio_x2(q * q));
+}
+
+// ln mean of densities (>= 0; 0 where one of them is 0, the limit)
+__device__ __forceinline__ double ln_mean_wide(double x, double y) {
+    const double s = x + y, d = y - x;
+    const double q = d * rcp(fmax(s, 1e-300));
+    double m = 0.5 * s * inv_atanh_ratio(q * q);
+    if (3.0 * fabs(d) > s) m = (x == 0.0 || y == 0.0) ? 0.0 : d * rcp(ln_ratio_far(x, y));
+    return m;
+}
+
+// reciprocal of the ln mean of positive numbers
+__device__ __forceinline__ double inv_ln_mean_wide(double x, double y) {
+    const double s = x + y, d = y - x, rs = rcp(s);
+    const double q = d * rs;
+    double m = atanh_ratio_x2(q * q) * rs;
+    if (3.0 * fabs(d) > s) m = ln_ratio_far(x, y) * rcp(d);
+    return m;
 }
 
 // ---------------------------------------------------------------- mixture
@@ -146,18 +198,17 @@ __device__ __forceinline__ double expm1_reduced(double y, int &n) {
     n = (int)(unsigned)__double_as_longlong(t);
     // ln 2 as its double and the remainder
     const double r = fma(-k, 2.3190468138462996e-17, fma(-k, 0.69314718055994529, y));
-    double q = 1.0 / 6227020800.0;
-    q = fma(q, r, 1.0 / 479001600.0);
-    q = fma(q, r, 1.0 / 39916800.0);
-    q = fma(q, r, 1.0 / 3628800.0);
-    q = fma(q, r, 1.0 / 362880.0);
-    q = fma(q, r, 1.0 / 40320.0);
-    q = fma(q, r, 1.0 / 5040.0);
-    q = fma(q, r, 1.0 / 720.0);
-    q = fma(q, r, 1.0 / 120.0);
-    q = fma(q, r, 1.0 / 24.0);
-    q = fma(q, r, 1.0 / 6.0);
-    q = fma(q, r, 0.5);
+    double q = poly_start(r, 1.0 / 6227020800.0, 1.0 / 479001600.0);
+    q = fma_k(q, r, 1.0 / 39916800.0);
+    q = fma_k(q, r, 1.0 / 3628800.0);
+    q = fma_k(q, r, 1.0 / 362880.0);
+    q = fma_k(q, r, 1.0 / 40320.0);
+    q = fma_k(q, r, 1.0 / 5040.0);
+    q = fma_k(q, r, 1.0 / 720.0);
+    q = fma_k(q, r, 1.0 / 120.0);
+    q = fma_k(q, r, 1.0 / 24.0);
+    q = fma_k(q, r, 1.0 / 6.0);
+    q = fma_k(q, r, 0.5);
     return fma(r * r, q, r);
 }
 
@@ -522,11 +573,50 @@ __device__ __forceinline__ void split_form_state(const St<DIM, MIX> &L, const St
     }
 }
 
-// sinh(z)/z, with its series near 0
-__device__ __forceinline__ double sinhc(double z) {
-    const double z2 = z * z;
-    if (fabs(z) < 1e-3) return fma(z2 * (1.0 / 6.0), fma(z2, 1.0 / 20.0, 1.0), 1.0);
-    return sinh(z) / z;
+// What the entropy-conservative mixture flux takes of a node: beta = 1/T, the
+// gas constant density sum_s rho_s R_s and, per molecule among the first
+// three species, E = exp(-theta beta / 2) (a molecule elsewhere in the species
+// table takes its exponentials in the flux).
+constexpr int kEcMol = 3;
+template <int DIM>
+struct EcNode {
+    double rs[kNS], v[DIM], rR, beta, E[kEcMol];
+};
+
+__device__ __forceinline__ double exp_neg_half(double th, double beta) {
+    int n;
+    const double p = expm1_reduced(-0.5 * th * beta, n);
+    return ldexp(1.0 + p, n);
+}
+
+template <int DIM>
+__device__ __forceinline__ void ec_node(const double *rs, const double *v, double T, const MixC &M, EcNode<DIM> &e) {
+#pragma unroll
+    for (int k = 0; k < kNS; ++k) e.rs[k] = rs[k];
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) e.v[c] = v[c];
+    e.rR = mix_rR(M, rs);
+    e.beta = rcp(T);
+#pragma unroll
+    for (int k = 0; k < kEcMol; ++k) e.E[k] = exp_neg_half(M.thv[k], e.beta);
+}
+
+// exp(-theta bbar) sinh(z)/z, z = theta (bR - bL)/2, from the two E: the
+// series of sinh(z)/z to z^18 (remainder < 3e-20) for |z| < 1, else the
+// difference of the squares (a ratio above e^2, no cancellation).
+__device__ __forceinline__ double exp_sinhc(double th, double db, double EL, double ER) {
+    const double z = 0.5 * th * db, y = z * z;
+    double r = poly_start(y, 1.0 / 121645100408832000.0, 1.0 / 355687428096000.0);
+    r = fma_kv(r, y, 1.0 / 1307674368000.0);
+    r = fma_kv(r, y, 1.0 / 6227020800.0);
+    r = fma_kv(r, y, 1.0 / 39916800.0);
+    r = fma_kv(r, y, 1.0 / 362880.0);
+    r = fma_kv(r, y, 1.0 / 5040.0);
+    r = fma_kv(r, y, 1.0 / 120.0);
+    r = fma_kv(r, y, 1.0 / 6.0);
+    double s = EL * ER * fma(y, r, 1.0);
+    if (fabs(z) >= 1.0) s = fma(EL, EL, -ER * ER) * rcp(th * db);
+    return s;
 }
 
 // Entropy-conservative flux of the RRHO mixture (Tadmor's condition with
@@ -537,38 +627,58 @@ __device__ __forceinline__ double sinhc(double z) {
 // energy means e^_s = e0_s + c_s / beta^ln (c_s = 3/2 R_s, 5/2 R_s for
 // molecules) + R_s theta_s exp(-theta_s {{beta}}) sinhc(theta_s [[beta]]/2)
 // / ln-mean(1 - exp(-theta_s beta)) for molecules.
+//
+// What bounds it: FP64 issue.  A pair needs nine logarithmic means and three
+// exp-sinhc terms; with every exponential (three per molecule) evaluated per
+// pair by the library and the means in three branches, k_rhs on the curved
+// 16^3 N = 4 mesh took 184 us.  A node meets 12 partners, so its exponentials
+// are evaluated once (EcNode) and the pair multiplies them: about 500 vector
+// instructions per pair instead of 1,500 (the far branch of a trace species'
+// mean runs in two thirds of the waves there), k_rhs 118 us.
 template <int DIM>
-__device__ __forceinline__ void ec_mixture_state(const St<DIM, true> &L, const St<DIM, true> &R, const double *n,
-                                                 const MixC &M, double *F) {
-    const double rRL = mix_rR(M, L.rs), rRR = mix_rR(M, R.rs);
-    const double bL = rRL / L.p, bR = rRR / R.p;
-    const double bbar = 0.5 * (bL + bR), dB = bR - bL;
-    const double iblog = inv_ln_mean(bL, bR);
+__device__ __forceinline__ void ec_mixture_pair(const EcNode<DIM> &L, const EcNode<DIM> &R, const double *n,
+                                                const MixC &M, double *F) {
+    const double db = R.beta - L.beta;
+    const double iblog = inv_ln_mean_wide(L.beta, R.beta);
     double vb[DIM];
 #pragma unroll
     for (int c = 0; c < DIM; ++c) vb[c] = 0.5 * (L.v[c] + R.v[c]);
     const double vn = dotn<DIM>(vb, n);
-    const double pt = 0.5 * (rRL + rRR) / bbar;
-    double frho = 0.0, en = 0.0;
+    const double pt = (L.rR + R.rR) * rcp(L.beta + R.beta);
+    double sm = 0.0, en = 0.0;
 #pragma unroll
     for (int k = 0; k < kNS; ++k) {
-        const double a = L.rs[k], b = R.rs[k];
-        const double m = (a == b) ? a : (a == 0.0 || b == 0.0) ? 0.0 : ln_mean(a, b);
-        const double fk = m * vn;
-        F[k] = fk;
-        frho += fk;
-        double eh = fma(M.mol[k] ? 2.5 * M.Rs[k] : 1.5 * M.Rs[k], iblog, M.e0[k]);
+        const double m = ln_mean_wide(L.rs[k], R.rs[k]);
+        F[k] = m * vn;
+        sm += m;
+        double eh = M.e0[k];
         if (M.mol[k]) {
             const double th = M.thv[k];
-            const double yL = -expm1(-th * bL), yR = -expm1(-th * bR);
-            eh += M.Rs[k] * th * exp(-th * bbar) * sinhc(0.5 * th * dB) / ln_mean(yL, yR);
+            const double EL = k < kEcMol ? L.E[k < kEcMol ? k : 0] : exp_neg_half(th, L.beta);
+            const double ER = k < kEcMol ? R.E[k < kEcMol ? k : 0] : exp_neg_half(th, R.beta);
+            const double t = exp_sinhc(th, db, EL, ER) * inv_ln_mean_wide(fma(-EL, EL, 1.0), fma(-ER, ER, 1.0));
+            eh = fma(M.Rs[k], fma(th, t, 2.5 * iblog), eh);
+        } else {
+            eh = fma(M.Rs[k], 1.5 * iblog, eh);
         }
-        en = fma(eh, fk, en);
+        en = fma(eh, m, en);
+        __builtin_amdgcn_sched_barrier(0);
     }
+    const double frho = sm * vn;
 #pragma unroll
     for (int c = 0; c < DIM; ++c) F[kNS + c] = fma(frho, vb[c], pt * n[c]);
     const double k2 = dotn<DIM>(vb, vb) - 0.25 * (dotn<DIM>(L.v, L.v) + dotn<DIM>(R.v, R.v));
-    F[kNS + DIM] = en + frho * k2 + pt * vn;
+    F[kNS + DIM] = vn * (fma(sm, k2, en) + pt);
+}
+
+// the same from two node states (faces)
+template <int DIM>
+__device__ __forceinline__ void ec_mixture_state(const St<DIM, true> &L, const St<DIM, true> &R, const double *n,
+                                                 const MixC &M, double *F) {
+    EcNode<DIM> A, B;
+    ec_node<DIM>(L.rs, L.v, L.p * rcp(mix_rR(M, L.rs)), M, A);
+    ec_node<DIM>(R.rs, R.v, R.p * rcp(mix_rR(M, R.rs)), M, B);
+    ec_mixture_pair<DIM>(A, B, n, M, F);
 }
 
 // Ducros split-form flux: {{rho_s}} {{v}}.n, {{m}} {{v}}.n + {{p}} n, ({{rhoE}} + {{p}}) {{v}}.n

@@ -93,23 +93,45 @@ __device__ __forceinline__ void features(const double *st, int64_t count, int64_
     x[5] = (float)((e - (double)nrm[5]) / (double)nrm[11]);
 }
 
-// A fragment of a weight matrix W[rows][ld] (FP32 master) for output block
-// mt and input block kc, rounded to BF16; columns >= ncol read as 0.
-__device__ __forceinline__ bf16x4 wfrag(const float *W, int ld, int ncol, int mt, int kc, int r, int g) {
-    float v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int col = 16 * kc + 4 * g + j;
-        v[j] = col < ncol ? W[(16 * mt + r) * ld + col] : 0.0f;
-    }
-    return pack4(v[0], v[1], v[2], v[3]);
+// Weight fragments (A operands), kept beside the FP32 parameters as BF16 in
+// the order in which lanes take them, so that a kernel reads two fragments
+// with one 16-byte load per lane instead of gathering and rounding eight
+// floats: pairs of fragments, then lanes, then the two fragments' 4 values.
+// Forward fragment (mt, kc) of W: lane (r, g) holds W[16 mt + r][16 kc + 4 g +
+// j], transposed one W[16 kc + 4 g + j][16 mt + r].  Order: W1 (4, columns 6
+// and up zero), W2, W3, W2^T, W3^T (16 each, mt major).
+constexpr int kF1 = 0, kF2 = 4, kF3 = 20, kT2 = 36, kT3 = 52;
+static_assert(kT3 + 16 == kSurFrags, "fragment order");
+
+__host__ __device__ __forceinline__ int packed_at(int frag, int r, int g, int j) {
+    return ((frag >> 1) * 64 + 16 * g + r) * 8 + (frag & 1) * 4 + j;
 }
-// A fragment of W^T (input block mt as rows, output block kc as K).
-__device__ __forceinline__ bf16x4 wtfrag(const float *W, int ld, int mt, int kc, int r, int g) {
-    float v[4];
+
+// The places of parameter i in the packed copy: none, one (W1) or two.
+__host__ __device__ __forceinline__ int packed_places(int i, int at[2]) {
+    if (i < ob1) {
+        const int row = i / kSurIn, col = i - row * kSurIn;
+        at[0] = packed_at(kF1 + row / 16, row % 16, col / 4, col % 4);
+        return 1;
+    }
+    const bool w2 = i >= oW2 && i < ob2, w3 = i >= oW3 && i < ob3;
+    if (!w2 && !w3) return 0;
+    const int k = i - (w2 ? oW2 : oW3), row = k / H, col = k % H;
+    at[0] = packed_at((w2 ? kF2 : kF3) + 4 * (row / 16) + col / 16, row % 16, (col % 16) / 4, col % 4);
+    at[1] = packed_at((w2 ? kT2 : kT3) + 4 * (col / 16) + row / 16, col % 16, (row % 16) / 4, row % 4);
+    return 2;
+}
+
+// Fragments f0 .. f0 + n - 1 (f0 and n even) of the packed copy.
+template <int n>
+__device__ __forceinline__ void load_frags(const unsigned short *pk, int f0, int lane, bf16x4 *out) {
+    typedef short bf16x8 __attribute__((ext_vector_type(8)));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = W[(16 * kc + 4 * g + j) * ld + 16 * mt + r];
-    return pack4(v[0], v[1], v[2], v[3]);
+    for (int i = 0; i < n; i += 2) {
+        const bf16x8 v = *reinterpret_cast<const bf16x8 *>(pk + ((size_t)((f0 + i) >> 1) * 64 + lane) * 8);
+        out[i] = bf16x4{v[0], v[1], v[2], v[3]};
+        out[i + 1] = bf16x4{v[4], v[5], v[6], v[7]};
+    }
 }
 
 struct Fwd {
@@ -119,7 +141,8 @@ struct Fwd {
     float y;                             // output before b4 (summed over groups)
 };
 
-__device__ __forceinline__ void forward(const float *P, const float *x, int r, int g, Fwd &F) {
+// W: the forward fragments W1 (4), W2 (16), W3 (16)
+__device__ __forceinline__ void forward(const float *P, const bf16x4 *W, const float *x, int g, Fwd &F) {
     {
         float v[4];
 #pragma unroll
@@ -132,7 +155,7 @@ __device__ __forceinline__ void forward(const float *P, const float *x, int r, i
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        acc = mfma(wfrag(P + oW1, kSurIn, kSurIn, mt, 0, r, g), F.xb, acc);
+        acc = mfma(W[kF1 + mt], F.xb, acc);
 #pragma unroll
         for (int j = 0; j < 4; ++j) F.h1[mt][j] = tanh_fast(acc[j] + P[ob1 + 16 * mt + 4 * g + j]);
         F.hb1[mt] = pack4(F.h1[mt][0], F.h1[mt][1], F.h1[mt][2], F.h1[mt][3]);
@@ -141,7 +164,7 @@ __device__ __forceinline__ void forward(const float *P, const float *x, int r, i
     for (int mt = 0; mt < 4; ++mt) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kc = 0; kc < 4; ++kc) acc = mfma(wfrag(P + oW2, H, H, mt, kc, r, g), F.hb1[kc], acc);
+        for (int kc = 0; kc < 4; ++kc) acc = mfma(W[kF2 + 4 * mt + kc], F.hb1[kc], acc);
 #pragma unroll
         for (int j = 0; j < 4; ++j) F.h2[mt][j] = tanh_fast(acc[j] + P[ob2 + 16 * mt + 4 * g + j]);
         F.hb2[mt] = pack4(F.h2[mt][0], F.h2[mt][1], F.h2[mt][2], F.h2[mt][3]);
@@ -151,7 +174,7 @@ __device__ __forceinline__ void forward(const float *P, const float *x, int r, i
     for (int mt = 0; mt < 4; ++mt) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kc = 0; kc < 4; ++kc) acc = mfma(wfrag(P + oW3, H, H, mt, kc, r, g), F.hb2[kc], acc);
+        for (int kc = 0; kc < 4; ++kc) acc = mfma(W[kF3 + 4 * mt + kc], F.hb2[kc], acc);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             F.h3[mt][j] = tanh_fast(acc[j] + P[ob3 + 16 * mt + 4 * g + j]);
@@ -168,23 +191,19 @@ __device__ __forceinline__ void forward(const float *P, const float *x, int r, i
 // in LDS; the features of 64 samples are computed one sample per lane and
 // shared through LDS by the four 16-sample tiles.
 template <int DIM>
-__global__ void __launch_bounds__(256) k_mlp_predict(const float *__restrict__ P, const double *__restrict__ st,
-                                                     int64_t count, double *__restrict__ Tg) {
+__global__ void __launch_bounds__(256) k_mlp_predict(const float *__restrict__ P,
+                                                     const unsigned short *__restrict__ pk,
+                                                     const double *__restrict__ st, int64_t count,
+                                                     double *__restrict__ Tg) {
     __shared__ float sx[4][64][8];         // per wave: features of 64 samples
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6;
     const int r = lane & 15, g = lane >> 4;
     const float *nrm = P + oNorm;
     bf16x4 W1f[4], W2f[4][4], W3f[4][4];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-        W1f[mt] = wfrag(P + oW1, kSurIn, kSurIn, mt, 0, r, g);
-#pragma unroll
-        for (int kc = 0; kc < 4; ++kc) {
-            W2f[mt][kc] = wfrag(P + oW2, H, H, mt, kc, r, g);
-            W3f[mt][kc] = wfrag(P + oW3, H, H, mt, kc, r, g);
-        }
-    }
+    load_frags<4>(pk, kF1, lane, W1f);
+    load_frags<16>(pk, kF2, lane, &W2f[0][0]);
+    load_frags<16>(pk, kF3, lane, &W3f[0][0]);
     // this lane's biases (rows 16 mt + 4 g + j) start the accumulators, and
     // its output weights W4
     f32x4 bias1[4], bias2[4], bias3[4], w4[4];
@@ -276,141 +295,139 @@ __global__ void __launch_bounds__(256) k_mlp_predict(const float *__restrict__ P
 }
 
 // ------------------------------------------------------------ training
-// Per-block partial gradients of the mean squared error over the samples
-// idx[start + b*spb .. start + (b+1)*spb) (b = block), spb = 4 waves x tpw tiles x 16.
+// Sum of v over the 16 lanes of a row (the samples of a tile), on every lane:
+// the butterfly over lane distances 1, 2, 4, 8.  Once the lanes of a group of
+// four (eight) agree, the mirrored lane of the other group holds the same
+// value as the butterfly's partner, so all four steps are additions with a
+// cross-lane operand, without LDS permutes.
+template <int CTRL>
+__device__ __forceinline__ float row_add(float v) {
+    // (v is rounded before it is summed: no contraction of its last product)
+#pragma clang fp contract(off)
+    const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true);
+    return v + __builtin_bit_cast(float, o);
+}
+__device__ __forceinline__ float rowsum(float v) {
+    v = row_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+    v = row_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+    v = row_add<0x141>(v);  // row_half_mirror
+    return row_add<0x140>(v);  // row_mirror
+}
+
+// A row of partial results: the gradient in parameter order, then the sum of
+// the squared residuals.
+constexpr int kRowLoss = kSurParams;
+constexpr int kRow = (kSurParams + 1 + 63) / 64 * 64;
+
+// Partial gradients of the mean squared error over the samples idx[start ..
+// start + nbatch): one wave per workgroup, a 16-sample tile each (tile tile0 +
+// block, row = block).
+//
+// What bounds it: latency.  A minibatch of 4096 is 256 tiles, one per CU, and
+// each is a chain of gathers, three layers forward and three back.  With four
+// tiles per workgroup, the weights gathered and rounded per use and the four
+// waves' sums taken in turn through LDS it took 34 us; with a workgroup per
+// tile, the packed weights loaded ahead and no sum inside, 12 us.
 template <int DIM>
-__global__ void __launch_bounds__(256) k_mlp_grad(const float *__restrict__ P, const double *__restrict__ st,
-                                                  const double *__restrict__ T, int64_t count,
-                                                  const int *__restrict__ idx, int64_t start, int64_t nbatch,
-                                                  int tpw, float *__restrict__ partial, float *__restrict__ lossp) {
-    __shared__ unsigned short sA[4][H][16];  // per wave: dz, neuron x sample (BF16)
-    __shared__ unsigned short sB[4][H][16];  // per wave: activation, neuron x sample (BF16)
-    __shared__ float red[kSurParams];        // block reduction
-    __shared__ float lred[4];
-    const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
+__global__ void __launch_bounds__(64) k_mlp_grad(const float *__restrict__ P, const unsigned short *__restrict__ pk,
+                                                 const double *__restrict__ st, const double *__restrict__ T,
+                                                 int64_t count, const int *__restrict__ idx, int64_t start,
+                                                 int64_t nbatch, int64_t tile0, float *__restrict__ partial) {
+    __shared__ __align__(16) unsigned short sA[H][16];  // dz, neuron x sample (BF16)
+    __shared__ __align__(16) unsigned short sB[H][16];  // activation, neuron x sample (BF16)
+    const int lane = threadIdx.x;
     const int r = lane & 15, g = lane >> 4;
     const float *nrm = P + oNorm;
     const float inv_b = 2.0f / (float)nbatch;
+    bf16x4 W[36];
+    load_frags<36>(pk, kF1, lane, W);
 
-    f32x4 dW3[4][4], dW2[4][4], dW1[4];
-    float gb1[4][4], gb2[4][4], gb3[4][4], gW4[4][4];
-    float gb4 = 0.0f, lsum = 0.0f;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        dW1[a] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            dW3[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-            dW2[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-            gb1[a][b] = gb2[a][b] = gb3[a][b] = gW4[a][b] = 0.0f;
-        }
+    const int64_t pos = (tile0 + blockIdx.x) * 16 + r;
+    const bool valid = pos < nbatch;
+    const int64_t n = valid ? (int64_t)idx[start + pos] : 0;
+    float x[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float tgt = 0.0f;
+    if (valid) {
+        features<DIM>(st, count, n, nrm, x);
+        tgt = (float)((T[n] - (double)nrm[12]) / (double)nrm[13]);
     }
-    const int64_t spb = (int64_t)4 * tpw * 16;
-    for (int t = 0; t < tpw; ++t) {
-        const int64_t pos = (int64_t)blockIdx.x * spb + ((int64_t)w * tpw + t) * 16 + r;
-        const bool valid = pos < nbatch;
-        const int64_t n = valid ? (int64_t)idx[start + pos] : 0;
-        float x[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        float tgt = 0.0f;
-        if (valid) {
-            features<DIM>(st, count, n, nrm, x);
-            tgt = (float)((T[n] - (double)nrm[12]) / (double)nrm[13]);
+    Fwd F;
+    forward(P, W, x, g, F);
+    const float res = valid ? (F.y + P[ob4] - tgt) : 0.0f;
+    const float dy = inv_b * res;
+    const float l2 = g == 0 ? res * res : 0.0f, d4 = g == 0 ? dy : 0.0f;
+    // output layer and dz3 (D layout)
+    float dz[4][4], gb1[4][4], gb2[4][4], gb3[4][4], gW4[4][4];
+    f32x4 dW3[4][4], dW2[4][4], dW1[4];
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = 16 * mt + 4 * g + j;
+            gW4[mt][j] = dy * F.h3[mt][j];
+            dz[mt][j] = P[oW4 + k] * dy * (1.0f - F.h3[mt][j] * F.h3[mt][j]);
+            gb3[mt][j] = dz[mt][j];
         }
-        Fwd F;
-        forward(P, x, r, g, F);
-        const float res = valid ? (F.y + P[ob4] - tgt) : 0.0f;
-        const float dy = inv_b * res;
-        if (g == 0) {
-            lsum = fmaf(res, res, lsum);
-            gb4 += dy;
-        }
-        // output layer and dz3 (D layout)
-        float dz[4][4];
+    // ---- layer 3: dW3 = dz3 . h2^T ; dz2 = (W3^T dz3) * (1 - h2^2); then layers 2 and 1
+#pragma unroll
+    for (int layer = 3; layer >= 1; --layer) {
+        bf16x4 Wt[16];
+        if (layer > 1) load_frags<16>(pk, layer == 3 ? kT3 : kT2, lane, Wt);
+        // stage dz (A) and the layer input (B) transposed through LDS
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int k = 16 * mt + 4 * g + j;
-                gW4[mt][j] = fmaf(dy, F.h3[mt][j], gW4[mt][j]);
-                dz[mt][j] = P[oW4 + k] * dy * (1.0f - F.h3[mt][j] * F.h3[mt][j]);
-                gb3[mt][j] += dz[mt][j];
+                sA[k][r] = to_bf16(dz[mt][j]);
+                if (layer == 3) sB[k][r] = to_bf16(F.h2[mt][j]);
+                if (layer == 2) sB[k][r] = to_bf16(F.h1[mt][j]);
             }
-        // ---- layer 3: dW3 += dz3 . h2^T ; dz2 = (W3^T dz3) * (1 - h2^2)
-        for (int layer = 3; layer >= 1; --layer) {
-            // stage dz (A) and the layer input (B) transposed through LDS
+        if (layer == 1 && g == 0) {
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
+            for (int k = 0; k < 16; ++k) sB[k][r] = k < 6 ? to_bf16(x[k]) : (unsigned short)0;
+        }
+        __syncthreads();
+        bf16x4 Af[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int k = 16 * mt + 4 * g + j;
-                    sA[w][k][r] = to_bf16(dz[mt][j]);
-                    if (layer == 3) sB[w][k][r] = to_bf16(F.h2[mt][j]);
-                    if (layer == 2) sB[w][k][r] = to_bf16(F.h1[mt][j]);
-                }
-            if (layer == 1 && g == 0) {
+        for (int mt = 0; mt < 4; ++mt) Af[mt] = *reinterpret_cast<const bf16x4 *>(&sA[16 * mt + r][4 * g]);
+        if (layer == 1) {
+            const bf16x4 b = *reinterpret_cast<const bf16x4 *>(&sB[r][4 * g]);
 #pragma unroll
-                for (int k = 0; k < 16; ++k) sB[w][k][r] = k < 6 ? to_bf16(x[k]) : (unsigned short)0;
-            }
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            bf16x4 Af[4];
+            for (int mt = 0; mt < 4; ++mt) dW1[mt] = mfma(Af[mt], b, zero);
+        } else {
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                bf16x4 a;
+            for (int nt = 0; nt < 4; ++nt) {
+                const bf16x4 b = *reinterpret_cast<const bf16x4 *>(&sB[16 * nt + r][4 * g]);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) a[j] = (short)sA[w][16 * mt + r][4 * g + j];
-                Af[mt] = a;
-            }
-            if (layer == 1) {
-                bf16x4 b;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) b[j] = (short)sB[w][r][4 * g + j];
-#pragma unroll
-                for (int mt = 0; mt < 4; ++mt) dW1[mt] = mfma(Af[mt], b, dW1[mt]);
-            } else {
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) {
-                    bf16x4 b;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) b[j] = (short)sB[w][16 * nt + r][4 * g + j];
-#pragma unroll
-                    for (int mt = 0; mt < 4; ++mt) {
-                        if (layer == 3) dW3[mt][nt] = mfma(Af[mt], b, dW3[mt][nt]);
-                        else dW2[mt][nt] = mfma(Af[mt], b, dW2[mt][nt]);
-                    }
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (layer == 1) break;
-            // back-propagate: dh = W^T dz (B operand = dz in D layout), dz_prev = dh * (1 - h^2)
-            const float *Wl = layer == 3 ? P + oW3 : P + oW2;
-            bf16x4 dzb[4];
-#pragma unroll
-            for (int kc = 0; kc < 4; ++kc) dzb[kc] = pack4(dz[kc][0], dz[kc][1], dz[kc][2], dz[kc][3]);
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kc = 0; kc < 4; ++kc) acc = mfma(wtfrag(Wl, H, mt, kc, r, g), dzb[kc], acc);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float h = layer == 3 ? F.h2[mt][j] : F.h1[mt][j];
-                    dz[mt][j] = acc[j] * (1.0f - h * h);
-                    if (layer == 3) gb2[mt][j] += dz[mt][j];
-                    else gb1[mt][j] += dz[mt][j];
+                for (int mt = 0; mt < 4; ++mt) {
+                    if (layer == 3) dW3[mt][nt] = mfma(Af[mt], b, zero);
+                    else dW2[mt][nt] = mfma(Af[mt], b, zero);
                 }
             }
         }
+        __syncthreads();
+        if (layer == 1) break;
+        // back-propagate: dh = W^T dz (B operand = dz in D layout), dz_prev = dh * (1 - h^2)
+        bf16x4 dzb[4];
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc) dzb[kc] = pack4(dz[kc][0], dz[kc][1], dz[kc][2], dz[kc][3]);
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            f32x4 acc = zero;
+#pragma unroll
+            for (int kc = 0; kc < 4; ++kc) acc = mfma(Wt[4 * mt + kc], dzb[kc], acc);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float h = layer == 3 ? F.h2[mt][j] : F.h1[mt][j];
+                dz[mt][j] = acc[j] * (1.0f - h * h);
+                if (layer == 3) gb2[mt][j] = dz[mt][j];
+                else gb1[mt][j] = dz[mt][j];
+            }
+        }
     }
-    // sum the per-sample accumulators over the 16 sample lanes of each group
-    auto rowsum = [](float v) {
-        v += __shfl_xor(v, 1);
-        v += __shfl_xor(v, 2);
-        v += __shfl_xor(v, 4);
-        v += __shfl_xor(v, 8);
-        return v;
-    };
+    // biases and output weights: sums over the tile's samples
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
@@ -420,70 +437,99 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float *__restrict__ P, c
             gb3[mt][j] = rowsum(gb3[mt][j]);
             gW4[mt][j] = rowsum(gW4[mt][j]);
         }
-    gb4 = rowsum(gb4);
-    lsum = rowsum(lsum);
-    // deterministic block reduction: waves add in order 0..3
-    for (int i = threadIdx.x; i < kSurParams; i += blockDim.x) red[i] = 0.0f;
-    __syncthreads();
-    for (int ww = 0; ww < 4; ++ww) {
-        if (w == ww) {
+    const float g4 = rowsum(d4), ls = rowsum(l2);
+    float *out = partial + (size_t)blockIdx.x * kRow;
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
+    for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int k = 16 * mt + 4 * g + j;
-                    if (r < kSurIn) red[oW1 + k * kSurIn + r] += dW1[mt][j];
+        for (int j = 0; j < 4; ++j) {
+            const int k = 16 * mt + 4 * g + j;
+            if (r < kSurIn) out[oW1 + k * kSurIn + r] = dW1[mt][j];
 #pragma unroll
-                    for (int nt = 0; nt < 4; ++nt) {
-                        red[oW3 + k * H + 16 * nt + r] += dW3[mt][nt][j];
-                        red[oW2 + k * H + 16 * nt + r] += dW2[mt][nt][j];
-                    }
-                    if (r == 0) {
-                        red[ob1 + k] += gb1[mt][j];
-                        red[ob2 + k] += gb2[mt][j];
-                        red[ob3 + k] += gb3[mt][j];
-                        red[oW4 + k] += gW4[mt][j];
-                    }
-                }
+            for (int nt = 0; nt < 4; ++nt) {
+                out[oW3 + k * H + 16 * nt + r] = dW3[mt][nt][j];
+                out[oW2 + k * H + 16 * nt + r] = dW2[mt][nt][j];
             }
-            if (lane == 0) {
-                red[ob4] += gb4;
-                lred[ww] = lsum;
+            if (r == 0) {
+                out[ob1 + k] = gb1[mt][j];
+                out[ob2 + k] = gb2[mt][j];
+                out[ob3 + k] = gb3[mt][j];
+                out[oW4 + k] = gW4[mt][j];
+            }
+        }
+    if (lane == 0) {
+        out[ob4] = g4;
+        out[kRowLoss] = ls;
+    }
+}
+
+struct AdamC {
+    float lr, c1, c2;
+};
+
+// Sums the partial rows in a fixed order (groups of four rows, a group's rows
+// in turn, then the groups in turn) onto grad[i] (from 0 in the first part
+// of a batch), grad[kRowLoss] likewise the loss; in the last part the loss is
+// accumulated and with ADAM the parameters and their packed copy are updated.
+// A workgroup takes 64 parameters:
+// its four waves read and sum the groups of a chunk side by side into LDS,
+// and one adds them in order.  (One thread per parameter walking 64 rows took
+// 18 us, waiting for one load after another, and the update was a launch of
+// its own, 5 us; now 256 rows and the update take 4 us.)
+template <bool ADAM>
+__global__ void __launch_bounds__(256) k_mlp_reduce(const float *__restrict__ partial, int rows, int first, int last,
+                                                    float *__restrict__ grad, float *__restrict__ loss_acc,
+                                                    float *__restrict__ P, unsigned short *__restrict__ pk,
+                                                    float *__restrict__ m, float *__restrict__ v, AdamC A) {
+    constexpr int CH = 64;  // groups per chunk
+    __shared__ float sh[CH][64];
+    const int p = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + p;  // < kRow
+    const int ngroups = (rows + 3) / 4;
+    float s = first || w != 0 ? 0.0f : grad[i];
+    for (int c0 = 0; c0 < ngroups; c0 += CH) {
+        // all rows of this wave's groups are loaded before the first sum;
+        // rows past the end count as zero
+        const int r0 = (c0 + w * (CH / 4)) * 4;
+        const float *q = partial + (size_t)r0 * kRow + i;
+        float b[CH];
+        if (r0 + CH <= rows) {
+#pragma unroll
+            for (int x = 0; x < CH; ++x) b[x] = q[(size_t)x * kRow];
+        } else {
+#pragma unroll
+            for (int x = 0; x < CH; ++x) b[x] = r0 + x < rows ? q[(size_t)x * kRow] : 0.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < CH / 4; ++k)
+            sh[w * (CH / 4) + k][p] = ((b[4 * k] + b[4 * k + 1]) + b[4 * k + 2]) + b[4 * k + 3];
+        __syncthreads();
+        if (w == 0) {
+            if (ngroups - c0 >= CH) {
+#pragma unroll
+                for (int k = 0; k < CH; ++k) s += sh[k][p];
+            } else {
+                for (int k = 0; k < ngroups - c0; ++k) s += sh[k][p];
             }
         }
         __syncthreads();
     }
-    float *out = partial + (size_t)blockIdx.x * kSurParams;
-    for (int i = threadIdx.x; i < kSurParams; i += blockDim.x) out[i] = red[i];
-    if (threadIdx.x == 0) lossp[blockIdx.x] = ((lred[0] + lred[1]) + lred[2]) + lred[3];
-}
-
-// grad[i] = sum over blocks (in order) of partial[b][i]; loss accumulated.
-__global__ void k_mlp_reduce(const float *__restrict__ partial, const float *__restrict__ lossp, int nblk,
-                             float *__restrict__ grad, float *__restrict__ loss_acc) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < kSurParams) {
-        float s = 0.0f;
-        for (int b = 0; b < nblk; ++b) s += partial[(size_t)b * kSurParams + i];
-        grad[i] = s;
-    }
-    if (i == 0) {
-        float l = 0.0f;
-        for (int b = 0; b < nblk; ++b) l += lossp[b];
-        loss_acc[0] += l;
-    }
-}
-
-__global__ void k_adam(float *__restrict__ P, const float *__restrict__ grad, float *__restrict__ m,
-                       float *__restrict__ v, float lr, float c1, float c2) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (w != 0) return;
+    grad[i] = s;
+    if (!last) return;
+    if (i == kRowLoss) loss_acc[0] += s;
     if (i >= kSurParams) return;
-    const float gi = grad[i];
-    const float mi = 0.9f * m[i] + 0.1f * gi;
-    const float vi = 0.999f * v[i] + 0.001f * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    P[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
+    if constexpr (ADAM) {
+        const float mi = 0.9f * m[i] + 0.1f * s;
+        const float vi = 0.999f * v[i] + 0.001f * s * s;
+        m[i] = mi;
+        v[i] = vi;
+        const float pn = P[i] - A.lr * (mi / A.c1) / (sqrtf(vi / A.c2) + 1e-8f);
+        P[i] = pn;
+        int at[2];
+        const int n = packed_places(i, at);
+        for (int k = 0; k < n; ++k) pk[at[k]] = to_bf16(pn);
+    }
 }
 
 int grid_for(int64_t count) {
@@ -493,9 +539,28 @@ int grid_for(int64_t count) {
 
 }  // namespace
 
+// FP32 -> BF16 on the host, round to nearest even, NaN kept (as the device's
+// conversion).
+static unsigned short host_bf16(float f) {
+    unsigned u;
+    std::memcpy(&u, &f, sizeof(u));
+    if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)(u >> 16 | 0x40u);
+    return (unsigned short)((u + 0x7fffu + (u >> 16 & 1u)) >> 16);
+}
+
 int surrogate_set(Surrogate &S, const float *host_params) {
     if (!S.params && hipMalloc(&S.params, (kSurParams + kSurNorm) * sizeof(float)) != hipSuccess) return -3;
-    if (hipMemcpy(S.params, host_params, (kSurParams + kSurNorm) * sizeof(float), hipMemcpyHostToDevice) != hipSuccess)
+    if (!S.packed && hipMalloc(&S.packed, kSurPacked * sizeof(unsigned short)) != hipSuccess) return -3;
+    static thread_local unsigned short pk[kSurPacked];
+    std::memset(pk, 0, sizeof(pk));
+    for (int i = 0; i < kSurParams; ++i) {
+        int at[2];
+        const int n = packed_places(i, at);
+        for (int k = 0; k < n; ++k) pk[at[k]] = host_bf16(host_params[i]);
+    }
+    S.ready = false;
+    if (hipMemcpy(S.params, host_params, (kSurParams + kSurNorm) * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(S.packed, pk, sizeof(pk), hipMemcpyHostToDevice) != hipSuccess)
         return -3;
     S.ready = true;
     return 0;
@@ -511,8 +576,8 @@ int surrogate_get(Surrogate &S, float *host_params) {
 int surrogate_predict(Surrogate &S, int dim, const double *states, int64_t count, double *Tg, hipStream_t s) {
     if (!S.ready) return -6;
     const int grid = grid_for(count);
-    if (dim == 2) hipLaunchKernelGGL(k_mlp_predict<2>, dim3(grid), dim3(256), 0, s, S.params, states, count, Tg);
-    else hipLaunchKernelGGL(k_mlp_predict<3>, dim3(grid), dim3(256), 0, s, S.params, states, count, Tg);
+    if (dim == 2) hipLaunchKernelGGL(k_mlp_predict<2>, dim3(grid), dim3(256), 0, s, S.params, S.packed, states, count, Tg);
+    else hipLaunchKernelGGL(k_mlp_predict<3>, dim3(grid), dim3(256), 0, s, S.params, S.packed, states, count, Tg);
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
@@ -522,53 +587,86 @@ static int ensure(float *&p, size_t n) {
     return hipMemset(p, 0, n * sizeof(float)) == hipSuccess ? 0 : -3;
 }
 
-// Gradient of the mean squared error over the samples idx[start .. start+nb)
-// into S.grads; the summed squared residual is added to *loss_dev.
-static int enqueue_grad(Surrogate &S, int dim, const double *states, const double *T, int64_t count, const int *idx,
-                        int64_t start, int64_t nb, float *partial, float *lossp, float *loss_dev, int nblk_cap,
-                        hipStream_t s) {
-    const int tpw = 1;
-    const int64_t spb = 4 * tpw * 16;
-    const int nblk = (int)((nb + spb - 1) / spb);
-    if (nblk > nblk_cap) return -1;
-    if (dim == 2)
-        hipLaunchKernelGGL(k_mlp_grad<2>, dim3(nblk), dim3(256), 0, s, S.params, states, T, count, idx, start, nb, tpw,
-                           partial, lossp);
-    else
-        hipLaunchKernelGGL(k_mlp_grad<3>, dim3(nblk), dim3(256), 0, s, S.params, states, T, count, idx, start, nb, tpw,
-                           partial, lossp);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((kSurParams + 255) / 256), dim3(256), 0, s, partial, lossp, nblk, S.grads,
-                       loss_dev);
+// Partial rows per part of a minibatch: 16,384 samples, a wave for each SIMD
+// of the chip, 36 MB.  Larger batches run part after part into the same rows,
+// with the same sums.
+constexpr int kPartRows = 1024;
+
+// The training workspace: the partial rows of a batch of nb, room for n sample
+// indices and the loss accumulator.
+static int ensure_workspace(Surrogate &S, int64_t nb, size_t n) {
+    const size_t rows = (size_t)std::min<int64_t>((nb + 15) / 16, kPartRows);
+    if (!S.loss && hipMalloc(&S.loss, sizeof(float)) != hipSuccess) return -2;
+    if (S.partial_rows < rows) {
+        if (S.partial) (void)hipFree(S.partial);
+        S.partial = nullptr;
+        S.partial_rows = 0;
+        if (hipMalloc(&S.partial, rows * kRow * sizeof(float)) != hipSuccess) return -2;
+        S.partial_rows = rows;
+    }
+    if (S.order_n < n) {
+        if (S.order) (void)hipFree(S.order);
+        S.order = nullptr;
+        S.order_n = 0;
+        if (hipMalloc(&S.order, n * sizeof(int)) != hipSuccess) return -2;
+        S.order_n = n;
+    }
+    return 0;
+}
+
+// Gives the sample order back where it is large (the stream has been waited
+// for).
+static void trim_workspace(Surrogate &S) {
+    if (S.order_n * sizeof(int) > kSurKeepBytes) {
+        (void)hipFree(S.order);
+        S.order = nullptr;
+        S.order_n = 0;
+    }
+}
+
+// Gradient of the mean squared error over the samples order[start ..
+// start+nb) into S.grads, the summed squared residual added to S.loss, and
+// with adam the parameter update.
+static int enqueue_grad(Surrogate &S, int dim, const double *states, const double *T, int64_t count, int64_t start,
+                        int64_t nb, const AdamC *adam, hipStream_t s) {
+    const int64_t tiles = (nb + 15) / 16;
+    for (int64_t t0 = 0; t0 < tiles; t0 += kPartRows) {
+        const int rows = (int)std::min<int64_t>(kPartRows, tiles - t0);
+        const int first = t0 == 0, last = t0 + rows == tiles;
+        auto grad = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(rows), dim3(64), 0, s, S.params, S.packed, states, T, count, S.order, start,
+                               nb, t0, S.partial);
+        };
+        if (dim == 2) grad(k_mlp_grad<2>);
+        else grad(k_mlp_grad<3>);
+        auto reduce = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(kRow / 64), dim3(256), 0, s, S.partial, rows, first, last, S.grads, S.loss,
+                               S.params, S.packed, S.adam_m, S.adam_v, adam ? *adam : AdamC{0.f, 1.f, 1.f});
+        };
+        if (adam) reduce(k_mlp_reduce<true>);
+        else reduce(k_mlp_reduce<false>);
+    }
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
 int surrogate_grad(Surrogate &S, int dim, const double *states, const double *T, int64_t count, float *grad_host,
                    float *loss_host, hipStream_t s) {
     if (!S.ready) return -6;
-    if (ensure(S.grads, kSurParams)) return -2;
-    const int nblk = (int)((count + 63) / 64);
-    float *partial = nullptr, *lossp = nullptr, *ld = nullptr;
-    int *idx = nullptr;
+    if (ensure(S.grads, kRow)) return -2;
+    if (ensure_workspace(S, count, (size_t)count)) return -2;
     int rc = 0;
     std::vector<int> h(count);
     for (int64_t i = 0; i < count; ++i) h[i] = (int)i;
-    if (hipMalloc(&partial, (size_t)nblk * kSurParams * sizeof(float)) != hipSuccess ||
-        hipMalloc(&lossp, nblk * sizeof(float)) != hipSuccess || hipMalloc(&ld, sizeof(float)) != hipSuccess ||
-        hipMalloc(&idx, count * sizeof(int)) != hipSuccess)
-        rc = -2;
-    if (!rc && hipMemcpy(idx, h.data(), count * sizeof(int), hipMemcpyHostToDevice) != hipSuccess) rc = -3;
-    if (!rc && hipMemsetAsync(ld, 0, sizeof(float), s) != hipSuccess) rc = -3;
-    if (!rc) rc = enqueue_grad(S, dim, states, T, count, idx, 0, count, partial, lossp, ld, nblk, s);
+    if (hipMemcpyAsync(S.order, h.data(), count * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess) rc = -3;
+    if (!rc && hipMemsetAsync(S.loss, 0, sizeof(float), s) != hipSuccess) rc = -3;
+    if (!rc) rc = enqueue_grad(S, dim, states, T, count, 0, count, nullptr, s);
     if (!rc && hipMemcpyAsync(grad_host, S.grads, kSurParams * sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess)
         rc = -3;
     float l = 0.0f;
-    if (!rc && hipMemcpyAsync(&l, ld, sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess) rc = -3;
-    if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = -3;
+    if (!rc && hipMemcpyAsync(&l, S.loss, sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess) rc = -3;
+    if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = -3;
     if (!rc && loss_host) *loss_host = l / (float)count;
-    if (partial) (void)hipFree(partial);
-    if (lossp) (void)hipFree(lossp);
-    if (ld) (void)hipFree(ld);
-    if (idx) (void)hipFree(idx);
+    trim_workspace(S);
     return rc;
 }
 
@@ -578,19 +676,8 @@ int surrogate_train(Surrogate &S, int dim, const double *states, const double *T
         S.err = "set initial parameters (and normalisation) first";
         return -6;
     }
-    if (ensure(S.grads, kSurParams) || ensure(S.adam_m, kSurParams) || ensure(S.adam_v, kSurParams)) return -2;
-    const int nblk_cap = (batch + 63) / 64;
-    float *partial = nullptr, *lossp = nullptr, *ld = nullptr;
-    int *idx = nullptr;
-    if (hipMalloc(&partial, (size_t)nblk_cap * kSurParams * sizeof(float)) != hipSuccess ||
-        hipMalloc(&lossp, nblk_cap * sizeof(float)) != hipSuccess || hipMalloc(&ld, sizeof(float)) != hipSuccess ||
-        hipMalloc(&idx, count * sizeof(int)) != hipSuccess) {
-        if (partial) (void)hipFree(partial);
-        if (lossp) (void)hipFree(lossp);
-        if (ld) (void)hipFree(ld);
-        if (idx) (void)hipFree(idx);
-        return -2;
-    }
+    if (ensure(S.grads, kRow) || ensure(S.adam_m, kSurParams) || ensure(S.adam_v, kSurParams)) return -2;
+    if (ensure_workspace(S, std::min<int64_t>(batch, count), (size_t)count)) return -2;
     std::vector<int> order(count);
     for (int64_t i = 0; i < count; ++i) order[i] = (int)i;
     std::mt19937_64 rng(seed);
@@ -601,34 +688,29 @@ int surrogate_train(Surrogate &S, int dim, const double *states, const double *T
     int64_t t = 0;
     for (int ep = 0; ep < epochs && !rc; ++ep) {
         std::shuffle(order.begin(), order.end(), rng);
-        if (hipMemcpyAsync(idx, order.data(), count * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemsetAsync(ld, 0, sizeof(float), s) != hipSuccess) {
+        if (hipMemcpyAsync(S.order, order.data(), count * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess ||
+            hipMemsetAsync(S.loss, 0, sizeof(float), s) != hipSuccess) {
             rc = -3;
             break;
         }
         for (int64_t b0 = 0; b0 < count && !rc; b0 += batch) {
             const int64_t nb = std::min<int64_t>(batch, count - b0);
-            rc = enqueue_grad(S, dim, states, T, count, idx, b0, nb, partial, lossp, ld, nblk_cap, s);
-            if (rc) break;
             ++S.step;
-            const float c1 = 1.0f - std::pow(0.9f, (float)S.step);
-            const float c2 = 1.0f - std::pow(0.999f, (float)S.step);
-            const float lr_t = (float)(0.5 * lr * (1.0 + std::cos(3.14159265358979323846 * (double)t / total)));
+            AdamC A;
+            A.c1 = 1.0f - std::pow(0.9f, (float)S.step);
+            A.c2 = 1.0f - std::pow(0.999f, (float)S.step);
+            A.lr = (float)(0.5 * lr * (1.0 + std::cos(3.14159265358979323846 * (double)t / total)));
             ++t;
-            hipLaunchKernelGGL(k_adam, dim3((kSurParams + 255) / 256), dim3(256), 0, s, S.params, S.grads, S.adam_m,
-                               S.adam_v, lr_t, c1, c2);
+            rc = enqueue_grad(S, dim, states, T, count, b0, nb, &A, s);
         }
         float l = 0.0f;
-        if (!rc && (hipMemcpyAsync(&l, ld, sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        if (!rc && (hipMemcpyAsync(&l, S.loss, sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess ||
                     hipStreamSynchronize(s) != hipSuccess))
             rc = -3;
         if (!rc && loss_host) loss_host[ep] = l / (float)count;
     }
     (void)hipStreamSynchronize(s);
-    (void)hipFree(partial);
-    (void)hipFree(lossp);
-    (void)hipFree(ld);
-    (void)hipFree(idx);
+    trim_workspace(S);
     return rc;
 }
 
@@ -689,6 +771,10 @@ void surrogate_free(Surrogate &S) {
     if (S.adam_m) (void)hipFree(S.adam_m);
     if (S.adam_v) (void)hipFree(S.adam_v);
     if (S.grads) (void)hipFree(S.grads);
+    if (S.packed) (void)hipFree(S.packed);
+    if (S.partial) (void)hipFree(S.partial);
+    if (S.loss) (void)hipFree(S.loss);
+    if (S.order) (void)hipFree(S.order);
     S = Surrogate();
 }
 

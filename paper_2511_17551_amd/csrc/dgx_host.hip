@@ -636,6 +636,7 @@ static int create_body(const dgx_config *cfg, dgx_ctx **out) {
         ctx->bc.Vinv[i] = ctx->basis.Vinv[i];
     }
     for (int i = 0; i < ctx->N1; ++i) ctx->bc.w[i] = ctx->basis.w[i];
+    ctx->bc.iw0 = 1.0 / ctx->basis.w[0];
     if (mix) {
         ctx->sp = *cfg->species;
         ctx->has_sp = true;

@@ -15,6 +15,7 @@ constexpr int kMaxR = 32;     // reactions
 struct BasisC {
     double D[25];      // D[a*(N+1)+b] = l_b'(xi_a)
     double w[5];       // LGL weights
+    double iw0;        // 1 / w[0] = 1 / w[N], the surface lifting factor
     double Vinv[25];   // nodal -> orthonormal Legendre modes
 };
 

@@ -15,8 +15,8 @@
 // thread of a node evaluates its pairs at fixed offsets along its line and
 // passes one of them to its neighbour through LDS (N = 4: offsets 1 and 2,
 // every pair evaluated once; N = 3: offset 1 exchanged, offset 2 evaluated
-// by both nodes with the lower one first); other tilings evaluate each pair
-// (a < b) once and both nodes gather it from a pair-indexed buffer.
+// by both nodes); other tilings evaluate each pair (a < b) once and both
+// nodes gather it from a pair-indexed buffer.
 //
 // Work layout: thread <-> node, EPB elements per workgroup, the element's
 // primitives (and, for mixtures, the species densities; on curved meshes
@@ -29,6 +29,8 @@
 
 #include "physics.h"
 
+#include <type_traits>
+
 namespace dgx {
 
 template <int N1, int DIM>
@@ -36,6 +38,20 @@ __device__ __forceinline__ int line_node(int d, int a, int l) {
     if (d == 0) return a + N1 * l;
     if (d == 1) return (l % N1) + N1 * a + (DIM == 3 ? N1 * N1 * (l / N1) : 0);
     return l + N1 * N1 * a;
+}
+// The same for a direction known only at run time, without branches: the node
+// is low + s (a + N1 high) with s = N1^d and l = low + s high.
+template <int N1, int DIM>
+__device__ __forceinline__ int face_node(int d, int a, int l) {
+    if constexpr (N1 == 4) {
+        const int m = (1 << 2 * d) - 1;
+        return (l & ~m) << 2 | a << 2 * d | (l & m);
+    } else {
+        // l / s for l < N1^2 <= 25: by 1, N1 (a multiplication) or 0
+        const int s = d == 0 ? 1 : (d == 1 ? N1 : N1 * N1);
+        const int high = l * (d == 0 ? 64 : (d == 1 ? (64 + N1 - 1) / N1 : 0)) >> 6;
+        return l - high * s + s * (a + N1 * high);
+    }
 }
 template <int N1>
 __device__ __forceinline__ int node_pos(int n, int d) {
@@ -133,8 +149,12 @@ struct RhsShape {
     static constexpr int NV = (MIX ? kNS : 1) + DIM + 1;
     static constexpr int NW = DIM + 1;  // viscous flux components (momentum, energy)
     static constexpr bool EC = VF == 0 && !MIX;  // perfect-gas EC flux from staged (rho, v, p, beta)
-    // primitives: rho, v, p, rhoE [, c (mixture)] [, beta (EC)]
-    static constexpr int NQ = DIM + 3 + (MIX ? 1 : 0) + (EC ? 1 : 0);
+    // nodal quantity of the perfect gas's pair fluxes (pair_quantity): rho/p of
+    // the entropy-conservative flux, E/rho, (E + p)/rho, p/rho of the split
+    // forms
+    static constexpr bool QX = !MIX && (VF == 0 || VF == 2 || VF == 3 || VF == 5);
+    // primitives: rho, v, p, rhoE [, c (mixture)] [, pair quantity]
+    static constexpr int NQ = DIM + 3 + (MIX ? 1 : 0) + (QX ? 1 : 0);
     static constexpr int SU = MIX ? kNS * NN : 0;  // species densities
     static constexpr int NPL = N1 * N / 2;
     static constexpr int PD = NF * NPL;      // pairs per direction
@@ -189,8 +209,9 @@ __device__ __forceinline__ void jaf_row(const double *Jaf, int d, double *nrm) {
         }
 }
 
-// Node state from the LDS primitives (and species densities).
-template <int DIM, bool MIX>
+// Node state from the LDS primitives (and species densities; QX: and the pair
+// quantity, in rs[0]).
+template <int DIM, bool MIX, bool QX = false>
 __device__ __forceinline__ void lds_state(const double *su, const double *sq, int NN, int n, double gamma,
                                           St<DIM, MIX> &s) {
     s.rho = sq[n];
@@ -206,7 +227,19 @@ __device__ __forceinline__ void lds_state(const double *su, const double *sq, in
         // perfect gas: recomputed (one LDS array less keeps five 4-element
         // workgroups per CU); bitwise equal to the value make_state gives
         s.c = wave_sqrt(gamma * s.p * rcp(s.rho));
-        s.rs[0] = 0.0;
+        s.rs[0] = QX ? sq[(3 + DIM) * NN + n] : 0.0;
+    }
+}
+
+// Orders LDS accesses of an element's threads: where an element is one wave,
+// whose LDS instructions execute in order, that needs no barrier.
+template <bool WAVE>
+__device__ __forceinline__ void element_sync() {
+    if constexpr (WAVE) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
     }
 }
 
@@ -219,11 +252,29 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     constexpr int NCH = S::NCH, NCHF = S::NCHF, PDC = S::PDC, NSFC = S::NSFC, NVP = S::NVP;
     constexpr bool MIX = S::MIX;
     constexpr int GA = DIM * DIM + 1;
-    constexpr int QB = DIM + 3 + (MIX ? 1 : 0);  // EC slot in sq
+    constexpr int QB = DIM + 3;  // pair quantity's slot in sq (perfect gas)
     constexpr int OFF_G = S::SU + NQ * NN;        // element geometry within a slot
     constexpr int OFF_B = OFF_G + S::GEO + S::GEOA;
     constexpr int RFC = (NSFC + NN - 1) / NN;     // face rounds per chunk
     constexpr int RF = NCHF * RFC;                // face rounds
+    // a later face round's neighbour data is requested as soon as the previous
+    // round's states are formed (its flux overlaps the latency) for the
+    // perfect-gas Euler equations, and at the start of its own round for the
+    // others, whose flux leaves no registers for it: 51.4 against 52.4 us a
+    // right-hand side at 29^3, N = 3 Kennedy-Gruber, 223 against 227 on the
+    // 16^3 octree; but 178 against 175 for Navier-Stokes at 32^3 and 189
+    // against 184 for the curved five-species shock
+    constexpr bool EARLY = EQ == 0;
+    // 64 nodes: an element is a wave, its index uniform
+    constexpr bool WAVE = NN % 64 == 0;
+    // volume pairs: circulant schemes (the thread of a node takes pairs of
+    // that node only, see the volume term), for odd N1 in (N1 - 1) / 2 chunks
+    // and for N1 = 4 in one chunk
+    constexpr bool CIRC = PDC == NN && N1 % 2 == 1 && 2 * NCH == N1 - 1;
+    constexpr bool CIRC4 = N1 == 4 && NCH == 1;
+    // element = wave and no pair of another element: from its last face
+    // gather on an element needs no barrier
+    constexpr bool LOCAL = WAVE && (CIRC || CIRC4);
     extern __shared__ double smem[];
     // 2 D (pair-flux coefficients) and the LGL weights: read with per-lane
     // indices, so they live in LDS rather than in the kernel arguments
@@ -234,17 +285,9 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     __shared__ double sPm[MORT ? 2 * N1 * N1 : 1];
 
     const int tid = threadIdx.x;
-    if (tid < N1 * N1) sDc[tid] = 2.0 * P.B.D[tid];
-    if (tid < N1) sW[tid] = P.B.w[tid];
-    if constexpr (MORT) {
-        if (tid < 2 * N1 * N1) {
-            const int h = tid / (N1 * N1);
-            sPm[tid] = P.mops[50 + h * 25 + (tid - h * N1 * N1)];
-        }
-    }
     const int NT = P.epb * NN;  // threads that own a node
     const int nloc = min(P.epb, P.nelem - e0);
-    int el = tid / NN;
+    int el = WAVE ? __builtin_amdgcn_readfirstlane(tid / NN) : tid / NN;
     const int node = tid - el * NN;
     const bool valid = el < nloc;
     const int e = e0 + (valid ? el : 0);
@@ -257,12 +300,34 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     const size_t stride = (size_t)P.nelem * NN;
     const size_t gi = (size_t)e * NN + node;
     const double gamma = P.gamma;
+    // This node's entry of row v of a nodal array.  Where the element is
+    // uniform its address is a scalar base and a 32-bit lane offset (the base
+    // opaque, or the compiler adds in 64 bits per lane and access).
+    auto own_base = [&](const double *a, int v) -> uint64_t {
+        uint64_t p = reinterpret_cast<uint64_t>(a) + (v * stride + (size_t)e * NN) * sizeof(double);
+        asm("" : "+s"(p));
+        return p;
+    };
+    auto lane_off = [&]() -> unsigned {
+        unsigned o = (unsigned)node * (unsigned)sizeof(double);
+        asm("" : "+v"(o));
+        return o;
+    };
+    auto own = [&](const double *a, int v) -> double {
+        if constexpr (WAVE) return *(const __attribute__((address_space(1))) double *)(own_base(a, v) + lane_off());
+        else return a[v * stride + gi];
+    };
+    auto put = [&](double *a, int v, double x) {
+        if constexpr (WAVE) *(__attribute__((address_space(1))) double *)(own_base(a, v) + lane_off()) = x;
+        else a[v * stride + gi] = x;
+    };
 
     // Work items (face nodes, volume pairs) of all elements of the workgroup
     // are spread over all its threads; large element types handle them in
     // NCH chunks so that one chunk's fluxes fit the LDS buffer.  The face
-    // phase's neighbour indices, and then the neighbour data of its first
-    // round, are fetched first so that their latency overlaps the staging.
+    // phase's neighbour indices are fetched first, then everything that needs
+    // no index (tables, own state, own geometry), then the neighbour data of
+    // the first round: one wait for the indices, one for all the rest.
     Spread spf[NCHF];
     int cursor = 0;
 #pragma unroll
@@ -288,13 +353,34 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
         if (face_item(g, ei, fi)) nbf[g] = P.nbr[(e0 + ei) * 2 * DIM + fi / NF];
     }
 
+    const double tD = P.B.D[min(tid, N1 * N1 - 1)], tW = P.B.w[min(tid, N1 - 1)];
+    double tP = 0.0;
+    if constexpr (MORT) {
+        const int i = min(tid, 2 * N1 * N1 - 1), h = i / (N1 * N1);
+        tP = P.mops[50 + h * 25 + (i - h * N1 * N1)];
+    }
+    // (threads without a node read one of the workgroup's first element)
+    double uo[NV], go[CURV ? DIM : 1], T_own = 1.0, c_own = 1.0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) uo[v] = own(P.u, v);
+    if constexpr (CURV) {
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) go[c] = own(P.geo, c);  // direction 0
+    } else {
+        go[0] = P.geo[(size_t)e * GA + min(node, GA - 1)];
+    }
+    if constexpr (MIX) {
+        T_own = own(P.T, 0);
+        c_own = own(P.csnd, 0);
+    }
+
     double une[RF][NV];   // neighbour state at the face node
     double ftr[RF][NW];   // neighbour's contravariant viscous face flux (BR1)
     double nrr[RF][DIM];  // the face normal when it comes from memory
     double Tr[RF];        // neighbour temperature (mixtures)
     double cr[RF];        // neighbour frozen sound speed (mixtures)
-    // The first round's data is loaded before the staging, later rounds'
-    // right before use (register pressure).  Face normals come from the
+    // The first round's data is loaded before the staging, a later round's as
+    // EARLY says.  Face normals come from the
     // element whose xi_d = +1 face it is: on affine elements the own one
     // sits in LDS, the neighbour's is loaded; on curved elements both are
     // nodal and loaded.
@@ -314,7 +400,7 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
         const int q = fi - f * NF;
         const int d = f >> 1, side = f & 1;
         if (nb >= 0) {
-            const size_t gj = (size_t)nb * NN + line_node<N1, DIM>(d, side ? 0 : N, q);
+            const size_t gj = (size_t)nb * NN + face_node<N1, DIM>(d, side ? 0 : N, q);
 #pragma unroll
             for (int v = 0; v < NV; ++v) une[g][v] = P.u[v * stride + gj];
             if constexpr (EQ == 1) {
@@ -338,64 +424,51 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
         }
         if constexpr (CURV) {
             if (nb < 0 || side == 1) {
-                const size_t go = (size_t)(e0 + ei) * NN + line_node<N1, DIM>(d, side ? N : 0, q);
+                const size_t gn = (size_t)(e0 + ei) * NN + face_node<N1, DIM>(d, side ? N : 0, q);
 #pragma unroll
-                for (int c = 0; c < DIM; ++c) nrr[g][c] = P.geo[(d * DIM + c) * stride + go];
+                for (int c = 0; c < DIM; ++c) nrr[g][c] = P.geo[(d * DIM + c) * stride + gn];
             }
         }
     };
 
     double ku[S::KEEPU ? NV : 1];  // the own state, kept for the stage update
-    double T_own = 1.0;
-    // ---- stage the element: primitives (+ species, metric terms)
-    {
-        double uo[NV];
-        double Tn = 1.0;
-        if (valid) {
+    load_nbr(0);
+    // ---- stage the tables and the element: primitives (+ species, metric terms)
+    if (tid < N1 * N1) sDc[tid] = 2.0 * tD;
+    if (tid < N1) sW[tid] = tW;
+    if constexpr (MORT) {
+        if (tid < 2 * N1 * N1) sPm[tid] = tP;
+    }
+    if (valid) {
+        if constexpr (CURV) {
 #pragma unroll
-            for (int v = 0; v < NV; ++v) uo[v] = P.u[v * stride + gi];
-        }
-        load_nbr(0);
-        if (valid) {
-            if constexpr (CURV) {
-#pragma unroll
-                for (int c = 0; c < DIM; ++c) sJa[c * NN + node] = P.geo[c * stride + gi];  // direction 0
-            } else {
-                if (node < GA) sJa[node] = P.geo[(size_t)e * GA + node];
-            }
-            if constexpr (MIX) Tn = P.T[gi];
-            T_own = Tn;
+            for (int c = 0; c < DIM; ++c) sJa[c * NN + node] = go[c];
         } else {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) uo[v] = 1.0;
+            if (node < GA) sJa[node] = go[0];
         }
         if constexpr (S::KEEPU) {
 #pragma unroll
             for (int v = 0; v < NV; ++v) ku[v] = uo[v];
         }
-        St<DIM, MIX> own;
-        make_state<DIM, MIX>(uo, Tn, gamma, P.M, own, MIX && valid ? P.csnd + gi : nullptr);
-        if (valid) {
-            sq[node] = own.rho;
+        St<DIM, MIX> s;
+        make_state<DIM, MIX>(uo, T_own, gamma, P.M, s, MIX ? &c_own : nullptr);
+        sq[node] = s.rho;
 #pragma unroll
-            for (int c = 0; c < DIM; ++c) sq[(1 + c) * NN + node] = own.v[c];
-            sq[(1 + DIM) * NN + node] = own.p;
-            sq[(2 + DIM) * NN + node] = own.rhoE;
-            if constexpr (MIX) {
-                sq[(3 + DIM) * NN + node] = own.c;
+        for (int c = 0; c < DIM; ++c) sq[(1 + c) * NN + node] = s.v[c];
+        sq[(1 + DIM) * NN + node] = s.p;
+        sq[(2 + DIM) * NN + node] = s.rhoE;
+        if constexpr (MIX) {
+            sq[(3 + DIM) * NN + node] = s.c;
 #pragma unroll
-                for (int k = 0; k < kNS; ++k) su[k * NN + node] = own.rs[k];
-            }
-            if constexpr (S::EC) {
-                sq[QB * NN + node] = own.rho / own.p;
-            }
-            bool ok = own.rho > 0.0 && own.p > 0.0 && isfinite(own.rhoE) && isfinite(own.p);
-            if constexpr (MIX) {
-#pragma unroll
-                for (int k = 0; k < kNS; ++k) ok = ok && own.rs[k] >= 0.0;
-            }
-            if (!ok) atomicOr(P.flags, FLAG_NONPHYS);
+            for (int k = 0; k < kNS; ++k) su[k * NN + node] = s.rs[k];
         }
+        if constexpr (S::QX) sq[QB * NN + node] = pair_quantity<DIM, VF>(s.rho, s.p, s.rhoE);
+        bool ok = s.rho > 0.0 && s.p > 0.0 && isfinite(s.rhoE) && isfinite(s.p);
+        if constexpr (MIX) {
+#pragma unroll
+            for (int k = 0; k < kNS; ++k) ok = ok && s.rs[k] >= 0.0;
+        }
+        if (!ok) atomicOr(P.flags, FLAG_NONPHYS);
     }
     __syncthreads();
 
@@ -409,31 +482,22 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
 #pragma unroll
         for (int rr = 0; rr < RFC; ++rr) {
             const int g = ch * RFC + rr;
-            if (g > 0) load_nbr(g);
-            int ei, fi;
-            if (face_item(g, ei, fi)) {
-                const int f = fi / NF;
-                const int q = fi - f * NF;
-                const int jb = fi - ch * NSFC;  // slot in this chunk's buffer
-                const int d = f >> 1, side = f & 1;
+            if (!EARLY && g > 0) load_nbr(g);
+            int ei = 0, fi = 0;
+            const bool has = face_item(g, ei, fi);
+            const int f = fi / NF;
+            const int q = fi - f * NF;
+            const int jb = fi - ch * NSFC;  // slot in this chunk's buffer
+            const int d = f >> 1, side = f & 1;
+            const int nb = nbf[g];
+            const bool mortar = MORT && nb <= kMortBase;
+            St<DIM, MIX> in, ext;  // own and external state
+            double nrm[DIM], F[NV];
+            if (has) {
                 const double *esu = smem + ei * S::SLOT;
                 const double *esq = esu + S::SU;
                 const double *eg = esu + OFF_G;
-                double *ebuf = smem + ei * S::SLOT + OFF_B;
-                const int nd = line_node<N1, DIM>(d, side ? N : 0, q);
-                St<DIM, MIX> own, ext;
-                lds_state<DIM, MIX>(esu, esq, NN, nd, gamma, own);
-                double nrm[DIM];
-                if constexpr (CURV) {
-#pragma unroll
-                    for (int c = 0; c < DIM; ++c) nrm[c] = nrr[g][c];
-                } else {
-#pragma unroll
-                    for (int c = 0; c < DIM; ++c) nrm[c] = eg[d * DIM + c];
-                }
-                const int nb = nbf[g];
-                double F[NV];
-                if (MORT && nb <= kMortBase) {
+                if (mortar) {
                     // non-conforming face: sub-face fluxes from the mortar items
                     constexpr int NSUB = DIM == 3 ? 4 : 2;
                     const int code = kMortBase - nb;
@@ -469,65 +533,68 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
 #pragma unroll
                         for (int k = 0; k < NW; ++k) F[1 + k] += 0.5 * fo[k * NF];
                     }
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) ebuf[v * NSFC + jb] = F[v];
-                    continue;
-                }
-                if (nb >= 0) {
-                    make_state<DIM, MIX>(une[g], MIX ? Tr[g] : 0.0, gamma, P.M, ext, MIX ? &cr[g] : nullptr);
-                    if (side == 0) {
-#pragma unroll
-                        for (int c = 0; c < DIM; ++c) nrm[c] = nrr[g][c];
-                    }
                 } else {
-                    const int bc = -1 - nb;
-                    const int kind = P.bc_kind[bc];
-                    if (kind == 0) {
-                        double ue[NV];
+                    lds_state<DIM, MIX>(esu, esq, NN, face_node<N1, DIM>(d, side ? N : 0, q), gamma, in);
 #pragma unroll
-                        for (int v = 0; v < NV; ++v) ue[v] = P.bc_state[bc * NV + v];
-                        make_state<DIM, MIX>(ue, MIX ? P.bc_T[bc] : 0.0, gamma, P.M, ext);
-                    } else if (kind == 1) {
-                        ext = own;
-                    } else if (kind >= 3) {
-                        // no-slip wall: the whole velocity reversed
-                        ext = own;
-#pragma unroll
-                        for (int c = 0; c < DIM; ++c) ext.v[c] = -own.v[c];
+                    for (int c = 0; c < DIM; ++c) nrm[c] = CURV || side == 0 && nb >= 0 ? nrr[g][c] : eg[d * DIM + c];
+                    if (nb >= 0) {
+                        make_state<DIM, MIX>(une[g], MIX ? Tr[g] : 0.0, gamma, P.M, ext, MIX ? &cr[g] : nullptr);
                     } else {
-                        // slip wall: mirror the velocity about the face (T and p unchanged)
-                        const double inn = rcp(dotn<DIM>(nrm, nrm));
-                        const double vn = dotn<DIM>(own.v, nrm) * inn;
-                        ext = own;
+                        const int bc = -1 - nb;
+                        const int kind = P.bc_kind[bc];
+                        if (kind == 0) {
+                            double ue[NV];
 #pragma unroll
-                        for (int c = 0; c < DIM; ++c) ext.v[c] = own.v[c] - 2.0 * vn * nrm[c];
+                            for (int v = 0; v < NV; ++v) ue[v] = P.bc_state[bc * NV + v];
+                            make_state<DIM, MIX>(ue, MIX ? P.bc_T[bc] : 0.0, gamma, P.M, ext);
+                        } else if (kind == 1) {
+                            ext = in;
+                        } else if (kind >= 3) {
+                            // no-slip wall: the whole velocity reversed
+                            ext = in;
+#pragma unroll
+                            for (int c = 0; c < DIM; ++c) ext.v[c] = -in.v[c];
+                        } else {
+                            // slip wall: mirror the velocity about the face (T and p unchanged)
+                            const double inn = rcp(dotn<DIM>(nrm, nrm));
+                            const double vn = dotn<DIM>(in.v, nrm) * inn;
+                            ext = in;
+#pragma unroll
+                            for (int c = 0; c < DIM; ++c) ext.v[c] = in.v[c] - 2.0 * vn * nrm[c];
+                        }
                     }
                 }
-                if constexpr (SF == 0) {
-                    if (side) rusanov<DIM, MIX>(own, ext, nrm, F);
-                    else rusanov<DIM, MIX>(ext, own, nrm, F);
-                } else if constexpr (SF == 2) {
-                    if (side) hll<DIM, MIX>(own, ext, nrm, F);
-                    else hll<DIM, MIX>(ext, own, nrm, F);
-                } else if constexpr (SF == 3) {
-                    if (side) hllc<DIM, MIX>(own, ext, nrm, F);
-                    else hllc<DIM, MIX>(ext, own, nrm, F);
-                } else if constexpr (MIX) {
-                    if (side) ec_mixture_state<DIM>(own, ext, nrm, P.M, F);
-                    else ec_mixture_state<DIM>(ext, own, nrm, P.M, F);
-                } else {
-                    if (side) ranocha_state<DIM, MIX>(own, ext, nrm, gamma, F);
-                    else ranocha_state<DIM, MIX>(ext, own, nrm, gamma, F);
-                }
-                if constexpr (EQ == 1) {
-                    // BR1 interface flux {{F_v}}: the element's own half is in
-                    // the gradient kernel's output, the neighbour's half enters
-                    // with the inviscid flux (F* - F_v/2 on the momentum and
-                    // energy rows; at boundary faces ftr is 0: the gradient
-                    // kernel applied the whole viscous boundary flux).
+            }
+            if (EARLY && g + 1 < RF) load_nbr(g + 1 < RF ? g + 1 : 0);
+            if (has) {
+                if (!mortar) {
+                    if constexpr (SF == 0) {
+                        if (side) rusanov<DIM, MIX>(in, ext, nrm, F);
+                        else rusanov<DIM, MIX>(ext, in, nrm, F);
+                    } else if constexpr (SF == 2) {
+                        if (side) hll<DIM, MIX>(in, ext, nrm, F);
+                        else hll<DIM, MIX>(ext, in, nrm, F);
+                    } else if constexpr (SF == 3) {
+                        if (side) hllc<DIM, MIX>(in, ext, nrm, F);
+                        else hllc<DIM, MIX>(ext, in, nrm, F);
+                    } else if constexpr (MIX) {
+                        if (side) ec_mixture_state<DIM>(in, ext, nrm, P.M, F);
+                        else ec_mixture_state<DIM>(ext, in, nrm, P.M, F);
+                    } else {
+                        if (side) ranocha_state<DIM, MIX>(in, ext, nrm, gamma, F);
+                        else ranocha_state<DIM, MIX>(ext, in, nrm, gamma, F);
+                    }
+                    if constexpr (EQ == 1) {
+                        // BR1 interface flux {{F_v}}: the element's own half is in
+                        // the gradient kernel's output, the neighbour's half enters
+                        // with the inviscid flux (F* - F_v/2 on the momentum and
+                        // energy rows; at boundary faces ftr is 0: the gradient
+                        // kernel applied the whole viscous boundary flux).
 #pragma unroll
-                    for (int k = 0; k < NW; ++k) F[1 + k] -= 0.5 * ftr[g][k];
+                        for (int k = 0; k < NW; ++k) F[1 + k] -= 0.5 * ftr[g][k];
+                    }
                 }
+                double *ebuf = smem + ei * S::SLOT + OFF_B;
 #pragma unroll
                 for (int v = 0; v < NV; ++v) ebuf[v * NSFC + jb] = F[v];
             }
@@ -541,19 +608,21 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
                 if (a == N || a == 0) {
                     const int fi = (2 * d + (a == N ? 1 : 0)) * NF + l;
                     if (NCHF == 1 || (fi >= ch * NSFC && fi < (ch + 1) * NSFC)) {
-                        const double sc = a == N ? 1.0 / sW[N] : -1.0 / sW[0];
+                        const double sc = a == N ? P.B.iw0 : -P.B.iw0;
 #pragma unroll
                         for (int v = 0; v < NV; ++v) acc[v] = fma(sc, buf[v * NSFC + fi - ch * NSFC], acc[v]);
                     }
                 }
             }
         }
-        __syncthreads();
+        // (LOCAL: other waves write this buffer only in the next chunk)
+        if (ch + 1 < NCHF) __syncthreads();
+        else element_sync<LOCAL>();
     }
 
     // ---- first-order subcell finite volumes (elements with alpha > 0)
     const double alpha = (P.alpha != nullptr && valid) ? P.alpha[e] : 0.0;
-    if (P.alpha != nullptr && __syncthreads_or(alpha > 0.0)) {
+    if (P.alpha != nullptr && (LOCAL ? (bool)(alpha > 0.0) : (bool)__syncthreads_or(alpha > 0.0))) {
 #pragma unroll
         for (int d = 0; d < DIM; ++d) {
 #pragma unroll
@@ -582,11 +651,11 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
                     for (int v = 0; v < NV; ++v) buf[v * NFV + p] = F[v];
                 }
             }
-            __syncthreads();
+            element_sync<LOCAL>();
             if (valid && alpha > 0.0) {
                 const int a = node_pos<N1>(node, d);
                 const int l = node_line<N1, DIM>(node, d);
-                const double aw = alpha / sW[a];
+                const double aw = alpha * rcp(sW[a]);
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
                     const double hi = a < N ? buf[v * NFV + l * N + a] : 0.0;
@@ -594,7 +663,7 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
                     acc[v] = fma(aw, hi - lo, acc[v]);
                 }
             }
-            __syncthreads();
+            element_sync<LOCAL>();
         }
     }
 
@@ -608,7 +677,7 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     double dg[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) dg[v] = 0.0;
-    const double gm1_inv = 1.0 / (gamma - 1.0);
+    const double gm1_inv = rcp(gamma - 1.0);
     // entropy-conservative mixture flux: beta = 1/T and the node's
     // exponentials, evaluated once per node, replace rho E and c (read no more)
     // and follow the pair fluxes
@@ -653,12 +722,12 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     };
     // circulant pairs (below): the own node's state and current metric row
     // stay in registers for the whole volume term
-    constexpr bool CIRC_K = PDC == NN && (N1 % 2 == 1) && 2 * NCH == N1 - 1 && !S::EC;
-    static_assert(!S::ECM || CIRC_K, "the entropy-conservative mixture flux is built for the circulant pairs");
+    constexpr bool CIRC_K = (CIRC && !S::EC) || CIRC4;
+    static_assert(!S::ECM || (CIRC_K && !CIRC4), "the entropy-conservative mixture flux is built for the circulant pairs");
     St<DIM, MIX> own_st;
     double own_row[DIM];
     if constexpr (CIRC_K) {
-        if (!S::ECM && valid) lds_state<DIM, MIX>(su, sq, NN, node, gamma, own_st);
+        if (!S::ECM && valid) lds_state<DIM, MIX, S::QX>(su, sq, NN, node, gamma, own_st);
         if constexpr (CURV) {
 #pragma unroll
             for (int c = 0; c < DIM; ++c) own_row[c] = valid ? sJa[c * NN + node] : 0.0;
@@ -667,17 +736,29 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     // the epilogue's loads, issued as late as their latency can still overlap
     // something
     auto load_epilogue = [&]() {
-        const bool st = valid && mode != 0;
-        const bool s0 = st && P.sa != 0.0;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-            if constexpr (S::KEEPU) eu[v] = ku[v];
-            else eu[v] = st ? P.u[v * stride + gi] : 0.0;
-            eu0[v] = s0 ? P.u0[v * stride + gi] : 0.0;
+            eu[v] = S::KEEPU ? ku[S::KEEPU ? v : 0] : 0.0;
+            eu0[v] = 0.0;
         }
 #pragma unroll
-        for (int k = 0; k < NW; ++k) evp[k] = (EQ == 1 && valid) ? P.vpart[(size_t)k * stride + gi] : 0.0;
-        if constexpr (CURV) Jc = valid ? P.Jn[gi] : 1.0;
+        for (int k = 0; k < NW; ++k) evp[k] = 0.0;
+        if (!valid) return;
+        if (mode != 0) {
+            if constexpr (!S::KEEPU) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v) eu[v] = own(P.u, v);
+            }
+            if (P.sa != 0.0) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v) eu0[v] = own(P.u0, v);
+            }
+        }
+        if constexpr (EQ == 1) {
+#pragma unroll
+            for (int k = 0; k < NW; ++k) evp[k] = own(P.vpart, k);
+        }
+        if constexpr (CURV) Jc = own(P.Jn, 0);
     };
     if constexpr (S::ECM) {
         // the circulant pairs described below, with the loops over directions
@@ -750,7 +831,7 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
         if constexpr (CURV) {
 #pragma unroll
             for (int c = 0; c < DIM; ++c)
-                jnext[c] = (valid && d + 1 < DIM) ? P.geo[((d + 1) * DIM + c) * stride + gi] : 0.0;
+                jnext[c] = (valid && d + 1 < DIM) ? own(P.geo, (d + 1) * DIM + c) : 0.0;
         }
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
@@ -766,35 +847,29 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
             // of that node.  Every pair is evaluated once, every node takes
             // all its N1 - 1 pairs, and the lanes of a wave read slots of
             // consecutive nodes (few LDS bank conflicts).
-            constexpr bool CIRC = OWN && (N1 % 2 == 1) && 2 * NCH == N1 - 1;
             // four nodes per line (N = 3) in one chunk: the pair at offset 1,
             // {a, (a + 1) mod 4}, as above; the pair at offset 2 is evaluated
-            // by both of its nodes (with its lower node first, so that both
-            // take the same flux) and needs no exchange
-            constexpr bool CIRC4 = N1 == 4 && NCH == 1;
+            // by both of its nodes (the fluxes are bitwise symmetric, so both
+            // take the same one) and needs no exchange
             const int jc = ch + 1;
             if constexpr (CIRC4) {
                 if (valid) {
-                    const int a = node_pos<N1>(node, d);
-                    const int l = node_line<N1, DIM>(node, d);
+                    const int a = (node >> 2 * d) & 3, rest = node & ~(3 << 2 * d);
 #pragma unroll
                     for (int j = 1; j <= 2; ++j) {
                         const int b = (a + j) & 3;
-                        const int nb = line_node<N1, DIM>(d, b, l);
-                        const int nlo = a < b ? node : nb, nhi = a < b ? nb : node;
+                        const int nb = rest | b << 2 * d;
                         double nbar[DIM];
 #pragma unroll
                         for (int c = 0; c < DIM; ++c)
-                            nbar[c] = CURV ? 0.5 * (sJa[c * NN + nlo] + sJa[c * NN + nhi]) : sJa[d * DIM + c];
+                            nbar[c] = CURV ? 0.5 * (own_row[c] + sJa[c * NN + nb]) : sJa[d * DIM + c];
                         double F[NV];
-                        if constexpr (S::EC) {
-                            ec_pair(sq, nlo, nhi, nbar, F);
-                        } else {
-                            St<DIM, MIX> A, B;
-                            lds_state<DIM, MIX>(su, sq, NN, nlo, gamma, A);
-                            lds_state<DIM, MIX>(su, sq, NN, nhi, gamma, B);
-                            volume_flux(A, B, nbar, F);
-                        }
+                        St<DIM, MIX> B;
+                        lds_state<DIM, MIX, S::QX>(su, sq, NN, nb, gamma, B);
+                        if constexpr (S::EC)
+                            ranocha_prims<DIM>(own_st.rho, own_st.v, own_st.p, own_st.rs[0], B.rho, B.v, B.p, B.rs[0],
+                                               nbar, gm1_inv, F);
+                        else volume_flux(own_st, B, nbar, F);
                         if (j == 1) {
 #pragma unroll
                             for (int v = 0; v < NV; ++v) buf[node * NVP + v] = F[v];
@@ -849,8 +924,8 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
                     } else {
                         St<DIM, MIX> A, B;
                         if constexpr (CIRC_K) A = own_st;
-                        else lds_state<DIM, MIX>(esu, esq, NN, na, gamma, A);
-                        lds_state<DIM, MIX>(esu, esq, NN, nb, gamma, B);
+                        else lds_state<DIM, MIX, S::QX>(esu, esq, NN, na, gamma, A);
+                        lds_state<DIM, MIX, S::QX>(esu, esq, NN, nb, gamma, B);
                         volume_flux(A, B, nbar, F);
                     }
 #pragma unroll
@@ -863,7 +938,7 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
                 }
             }
             if (d == DIM - 1 && ch == NCH - 1) load_epilogue();
-            __syncthreads();
+            element_sync<LOCAL>();
             if constexpr (CURV) {
                 // every pair of this direction has read the row: replace it
                 if (ch == NCH - 1 && d + 1 < DIM && valid) {
@@ -877,10 +952,9 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
             }
             if (CIRC4 && valid) {
                 // the pair {(a + 3) mod 4, a}, left by that node
-                const int a = node_pos<N1>(node, d);
-                const int l = node_line<N1, DIM>(node, d);
+                const int a = (node >> 2 * d) & 3;
                 const int a2 = (a + 3) & 3;
-                const int src = line_node<N1, DIM>(d, a2, l);
+                const int src = (node & ~(3 << 2 * d)) | a2 << 2 * d;
                 const double coef = sDc[a * N1 + a2];
 #pragma unroll
                 for (int v = 0; v < NV; ++v) dg[v] = fma(coef, buf[src * NVP + v], dg[v]);
@@ -908,10 +982,10 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
                     }
                 }
             }
-            __syncthreads();
+            element_sync<LOCAL>();
         }
     }
-    const double iJ = 1.0 / (CURV ? Jc : sJa[DIM * DIM]);
+    const double iJ = rcp(CURV ? Jc : sJa[DIM * DIM]);
     double du[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) du[v] = -(S::ECM ? acc[v] : fma(1.0 - alpha, dg[v], acc[v])) * iJ;
@@ -972,12 +1046,12 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     if (valid) {
         if (mode == 0) {
 #pragma unroll
-            for (int v = 0; v < NV; ++v) P.out[v * stride + gi] = du[v];
+            for (int v = 0; v < NV; ++v) put(P.out, v, du[v]);
         } else {
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
                 const double base = P.sa != 0.0 ? P.sa * eu0[v] : 0.0;
-                P.out[v * stride + gi] = base + P.sb * (eu[v] + P.dt * du[v]);
+                put(P.out, v, base + P.sb * (eu[v] + P.dt * du[v]));
             }
         }
     }

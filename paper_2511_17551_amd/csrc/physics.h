@@ -16,6 +16,15 @@
 
 namespace dgx {
 
+// a + b of two rounded terms: a product among them is not contracted into the
+// sum, so that the result does not depend on their order.  The two-point
+// fluxes use it wherever the two states' products meet; they are then
+// bitwise symmetric, and both nodes of a pair may evaluate it.
+__device__ __forceinline__ double sum2(double a, double b) {
+#pragma clang fp contract(off)
+    return a + b;
+}
+
 template <int DIM>
 __device__ __forceinline__ double dotn(const double *a, const double *b) {
     double s = a[0] * b[0];
@@ -24,7 +33,8 @@ __device__ __forceinline__ double dotn(const double *a, const double *b) {
     return s;
 }
 
-// Primitive state of one node.  For the perfect gas rs[0] is unused.
+// Primitive state of one node.  For the perfect gas rs[0] is the nodal
+// quantity of the split form in use (pair_quantity) where there is one.
 template <int DIM, bool MIX>
 struct St {
     double rho, v[DIM], p, rhoE, c;
@@ -133,7 +143,8 @@ __device__ __forceinline__ double ln_mean(double x, double y) {
         const double q = d * rcp(s);
         return 0.5 * s * inv_atanh_ratio(q * q);
     }
-    return d * rcp(log(y * rcp(x)));
+    // (the larger over the smaller, for symmetry)
+    return fabs(d) * rcp(log(fmax(x, y) * rcp(fmin(x, y))));
 }
 
 __device__ __forceinline__ double inv_ln_mean(double x, double y) {
@@ -151,7 +162,7 @@ __device__ __forceinline__ double inv_ln_mean(double x, double y) {
         const double q = d * rs;
         return atanh_ratio_x2(q * q) * rs;
     }
-    return log(y * rcp(x)) * rcp(d);
+    return log(fmax(x, y) * rcp(fmin(x, y))) * rcp(fabs(d));
 }
 
 // The same where nine of them meet in one flux (the mixture's entropy-
@@ -482,7 +493,7 @@ __device__ __forceinline__ void central_state(const St<DIM, MIX> &L, const St<DI
     phys_flux<DIM, MIX>(L, n, fL);
     phys_flux<DIM, MIX>(R, n, fR);
 #pragma unroll
-    for (int k = 0; k < NV; ++k) F[k] = 0.5 * (fL[k] + fR[k]);
+    for (int k = 0; k < NV; ++k) F[k] = 0.5 * sum2(fL[k], fR[k]);
 }
 
 template <int DIM, bool MIX>
@@ -516,7 +527,7 @@ __device__ __forceinline__ void ranocha_prims(double rL, const double *vL, doubl
     F[0] = frho;
 #pragma unroll
     for (int c = 0; c < DIM; ++c) F[1 + c] = frho * vbar[c] + pbar * n[c];
-    F[1 + DIM] = frho * (q + gm1_inv * ibeta_hat) + 0.5 * (pL * dotn<DIM>(vR, n) + pR * dotn<DIM>(vL, n));
+    F[1 + DIM] = frho * (q + gm1_inv * ibeta_hat) + 0.5 * sum2(pL * dotn<DIM>(vR, n), pR * dotn<DIM>(vL, n));
 }
 
 template <int DIM, bool MIX>
@@ -532,6 +543,13 @@ __device__ __forceinline__ void ranocha_state(const St<DIM, MIX> &L, const St<DI
 // energy f {{E/rho}} + {{p}}{{v.n}} (Kennedy-Gruber) or f {{(E + p)/rho}}
 // (Pirozzoli).  FORM 2 Morinishi (perfect gas): f = {{rho v}}.n, momentum as
 // above, energy f ({{p/((gamma-1) rho)}} + v_L.v_R/2) + {{p v}}.n.
+// The perfect gas takes E/rho, (E + p)/rho or p/rho of the nodes from rs[0]
+// (pair_quantity: one division per node instead of two per pair).
+template <int DIM, int VF>
+__device__ __forceinline__ double pair_quantity(double rho, double p, double rhoE) {
+    return (VF == 0 ? rho : VF == 2 ? rhoE : VF == 3 ? rhoE + p : p) * rcp(VF == 0 ? p : rho);
+}
+
 template <int DIM, bool MIX, int FORM>
 __device__ __forceinline__ void split_form_state(const St<DIM, MIX> &L, const St<DIM, MIX> &R,
                                                  const double *n, double gm1_inv, double *F) {
@@ -542,34 +560,37 @@ __device__ __forceinline__ void split_form_state(const St<DIM, MIX> &L, const St
     for (int c = 0; c < DIM; ++c) vb[c] = 0.5 * (L.v[c] + R.v[c]);
     const double vn = dotn<DIM>(vb, n);
     const double pbar = 0.5 * (L.p + R.p);
-    const double iL = 1.0 / L.rho, iR = 1.0 / R.rho;
     double fm;
     if constexpr (FORM == 2) {
         double mb[DIM];
 #pragma unroll
-        for (int c = 0; c < DIM; ++c) mb[c] = 0.5 * (L.rho * L.v[c] + R.rho * R.v[c]);
+        for (int c = 0; c < DIM; ++c) mb[c] = 0.5 * sum2(L.rho * L.v[c], R.rho * R.v[c]);
         fm = dotn<DIM>(mb, n);
     } else {
         fm = 0.5 * (L.rho + R.rho) * vn;
     }
+    double xm;  // mean of the nodal quantity
     if constexpr (MIX) {
+        const double iL = rcp(L.rho), iR = rcp(R.rho);
 #pragma unroll
         for (int k = 0; k < kNS; ++k) F[k] = fm * (0.5 * (L.rs[k] * iL + R.rs[k] * iR));
+        if constexpr (FORM == 1) xm = 0.5 * ((L.rhoE + L.p) * iL + (R.rhoE + R.p) * iR);
+        else xm = 0.5 * (L.rhoE * iL + R.rhoE * iR);
     } else {
         F[0] = fm;
+        xm = 0.5 * (L.rs[0] + R.rs[0]);
     }
 #pragma unroll
     for (int c = 0; c < DIM; ++c) F[off + c] = fm * vb[c] + pbar * n[c];
     if constexpr (FORM == 2) {
-        const double eint = 0.5 * (L.p * iL + R.p * iR) * gm1_inv;
         double pv[DIM];
 #pragma unroll
-        for (int c = 0; c < DIM; ++c) pv[c] = 0.5 * (L.p * L.v[c] + R.p * R.v[c]);
-        F[off + DIM] = fm * (eint + 0.5 * dotn<DIM>(L.v, R.v)) + dotn<DIM>(pv, n);
+        for (int c = 0; c < DIM; ++c) pv[c] = 0.5 * sum2(L.p * L.v[c], R.p * R.v[c]);
+        F[off + DIM] = fm * (xm * gm1_inv + 0.5 * dotn<DIM>(L.v, R.v)) + dotn<DIM>(pv, n);
     } else if constexpr (FORM == 1) {
-        F[off + DIM] = fm * (0.5 * ((L.rhoE + L.p) * iL + (R.rhoE + R.p) * iR));
+        F[off + DIM] = fm * xm;
     } else {
-        F[off + DIM] = fm * (0.5 * (L.rhoE * iL + R.rhoE * iR)) + pbar * vn;
+        F[off + DIM] = fm * xm + pbar * vn;
     }
 }
 
@@ -699,7 +720,7 @@ __device__ __forceinline__ void ducros_state(const St<DIM, MIX> &L, const St<DIM
     }
 #pragma unroll
     for (int c = 0; c < DIM; ++c) {
-        const double mbar = 0.5 * (L.rho * L.v[c] + R.rho * R.v[c]);
+        const double mbar = 0.5 * sum2(L.rho * L.v[c], R.rho * R.v[c]);
         F[off + c] = mbar * vn + pbar * n[c];
     }
     F[off + DIM] = (0.5 * (L.rhoE + R.rhoE) + pbar) * vn;

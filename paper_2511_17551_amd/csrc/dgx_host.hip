@@ -162,11 +162,12 @@ const IndEntry kInd[] = {
 template <typename T>
 struct DevBuf {
     T *p = nullptr;
-    size_t n = 0;
+    size_t n = 0;    // elements in use
+    size_t cap = 0;  // elements allocated
     void release() {
         if (p) (void)hipFree(p);
         p = nullptr;
-        n = 0;
+        n = cap = 0;
     }
 };
 
@@ -262,15 +263,42 @@ int guarded(dgx_ctx *ctx, F &&f) {
 
 template <typename T>
 int dalloc(dgx_ctx *ctx, DevBuf<T> &b, size_t n) {
-    if (b.n == n && b.p) return DGX_OK;
+    if (b.n == n && b.cap == n && b.p) return DGX_OK;
     b.release();
     if (n == 0) return DGX_OK;
     if (hipMalloc(&b.p, n * sizeof(T)) != hipSuccess) {
         b.p = nullptr;
         return set_err(ctx, DGX_E_NOMEM, "hipMalloc failed");
     }
-    b.n = n;
+    b.n = b.cap = n;
     return DGX_OK;
+}
+// The same for the buffers that follow the mesh's size, whose users a mesh
+// change waits for: one that is large enough stays while it is at most
+// kMeshSlack larger than needed, and one that has to grow takes an eighth
+// more, up to kMeshSlack.  (An adaptation cycle changes some twenty of them
+// by a few percent; a free and an allocation take 60 us and more.)
+constexpr size_t kMeshSlack = (size_t)32 << 20;
+template <typename T>
+int dalloc_mesh(dgx_ctx *ctx, DevBuf<T> &b, size_t n) {
+    const size_t slack = kMeshSlack / sizeof(T);
+    if (b.p && n > 0 && b.cap >= n && b.cap - n <= slack) {
+        b.n = n;
+        return DGX_OK;
+    }
+    const bool grows = b.p && n > b.cap;
+    b.release();
+    if (grows) {
+        const size_t cap = n + std::min(n / 8, slack);
+        if (hipMalloc(&b.p, cap * sizeof(T)) == hipSuccess) {
+            b.n = n;
+            b.cap = cap;
+            return DGX_OK;
+        }
+        (void)hipGetLastError();
+        b.p = nullptr;
+    }
+    return dalloc(ctx, b, n);
 }
 
 int threads_for(int nn, int epb) { return ((nn * epb + 63) / 64) * 64; }
@@ -717,8 +745,20 @@ int dgx_create(const dgx_config *cfg, dgx_ctx **out) {
     return guarded(nullptr, [&] { return create_body(cfg, out); });
 }
 
-static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m) {
-    if (!ctx || !m || !m->x || m->nelem <= 0) return set_err(ctx, DGX_E_INVAL, "bad mesh");
+// the kernel variant of the context's equations for a kind of mesh, or null
+static const RhsEntry *find_rhs(const dgx_ctx *ctx, bool curved, bool mortars) {
+    const RhsEntry *sel = nullptr;
+    for (const auto &e : kRhs)
+        if (e.dim == ctx->cfg.dim && e.N == ctx->cfg.N && e.eq == ctx->cfg.equation && e.vf == ctx->cfg.volume_flux &&
+            e.sf == ctx->cfg.surface_flux && e.curv == curved && e.mort == mortars && !e.alt)
+            sel = &e;
+    return sel;
+}
+
+// affine_geo: metric terms and J per element of a mesh known to be affine
+// for which there is an affine variant (then m->x is not read), or null
+static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m, const std::vector<double> *affine_geo = nullptr) {
+    if (!ctx || !m || (!m->x && !affine_geo) || m->nelem <= 0) return set_err(ctx, DGX_E_INVAL, "bad mesh");
     const int dim = ctx->cfg.dim, N = ctx->cfg.N, n1 = ctx->N1, nn = ctx->nn, E = m->nelem;
     const int nv = ctx->nvar;
     if (m->nface < 0 || (m->nface && !m->faces) || m->nbface < 0 || (m->nbface && !m->bfaces) ||
@@ -763,10 +803,11 @@ static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m) {
     // geometry: per-element metric terms at the first node and the affine
     // test first; the nodal arrays only when a curved variant runs
     const int GA = dim * dim + 1;
-    std::vector<double> g((size_t)E * GA);
+    std::vector<double> g_own(affine_geo ? 0 : (size_t)E * GA);
+    const std::vector<double> &g = affine_geo ? *affine_geo : g_own;
     std::vector<int> bad_J(16, INT_MAX);
     std::vector<unsigned char> curved_el(E, 0);
-    host_parallel(E, [&](int e0, int e1, int t) {
+    if (!affine_geo) host_parallel(E, [&](int e0, int e1, int t) {
         MetricScratch ws;
         std::vector<double> jae(dim * dim * nn), je(nn);
         const double *xe[3];
@@ -793,8 +834,8 @@ static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m) {
             // ~1e-16/h (4e-13 at the finest octree level), which the metric
             // terms amplify; genuine curvature is many orders larger
             curved_el[e] = dev > 1e-10 * mx;
-            for (int k = 0; k < dim * dim; ++k) g[(size_t)e * GA + k] = jae[k * nn];
-            g[(size_t)e * GA + dim * dim] = je[0];
+            for (int k = 0; k < dim * dim; ++k) g_own[(size_t)e * GA + k] = jae[k * nn];
+            g_own[(size_t)e * GA + dim * dim] = je[0];
         }
     });
     {
@@ -804,23 +845,19 @@ static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m) {
     bool affine = std::find(curved_el.begin(), curved_el.end(), (unsigned char)1) == curved_el.end();
     if (m->nmortar && !affine) return set_err(ctx, DGX_E_INVAL, "mortars need affine elements");
     // pick the kernel variant for this geometry
-    const RhsEntry *sel = nullptr;
-    const int want_m = m->nmortar ? 1 : 0;
-    for (const auto &e : kRhs)
-        if (e.dim == dim && e.N == N && e.eq == ctx->cfg.equation && e.vf == ctx->cfg.volume_flux &&
-            e.sf == ctx->cfg.surface_flux && e.curv == (affine ? 0 : 1) && e.mort == want_m && !e.alt)
-            sel = &e;
-    if (!sel && affine && !want_m)  // fall back to the curved variant (valid for any mesh)
-        for (const auto &e : kRhs)
-            if (e.dim == dim && e.N == N && e.eq == ctx->cfg.equation && e.vf == ctx->cfg.volume_flux &&
-                e.sf == ctx->cfg.surface_flux && e.curv == 1 && e.mort == 0 && !e.alt)
-                sel = &e, affine = false;
+    const bool want_m = m->nmortar > 0;
+    const RhsEntry *sel = find_rhs(ctx, !affine, want_m);
+    if (!sel && affine && !want_m) {  // fall back to the curved variant (valid for any mesh)
+        sel = find_rhs(ctx, true, false);
+        affine = false;
+    }
     if (!sel) return set_err(ctx, DGX_E_INVAL, "no kernel variant for this configuration and mesh");
     const RhsEntry *alt = nullptr;
     for (const auto &e : kRhs)
         if (e.alt && e.dim == sel->dim && e.N == sel->N && e.eq == sel->eq && e.vf == sel->vf && e.sf == sel->sf &&
             e.curv == sel->curv && e.mort == sel->mort)
             alt = &e;
+    (void)hipDeviceSynchronize();  // the buffers below may stay where they are
     clear_graph(ctx);
     ctx->mesh_ok = false;
     ctx->rhs = sel;
@@ -831,11 +868,11 @@ static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m) {
     ctx->nelem = E;
     ctx->nbc = m->nbc;
     int rc;
-    if ((rc = dalloc(ctx, ctx->nbr, nbr.size()))) return rc;
+    if ((rc = dalloc_mesh(ctx, ctx->nbr, nbr.size()))) return rc;
     HIPCHK(hipMemcpy(ctx->nbr.p, nbr.data(), nbr.size() * sizeof(int), hipMemcpyHostToDevice));
     // work queues: element chunks without non-conforming faces
     // first, then those that read mortar fluxes
-    if ((rc = dalloc(ctx, ctx->wq_ctr, 2))) return rc;
+    if ((rc = dalloc_mesh(ctx, ctx->wq_ctr, 2))) return rc;
     for (int k = 0; k < 4; ++k) {
         const int epb = 1 << k;
         const int nch = (E + epb - 1) / epb;
@@ -851,14 +888,14 @@ static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m) {
         for (int c = 0; c < nch; ++c)
             if (waits[c]) order.push_back(c);
         for (int i = 0; i < nch; ++i) wq[i] = waits[order[i]];
-        if ((rc = dalloc(ctx, ctx->wq_order[k], nch)) || (rc = dalloc(ctx, ctx->wq_waits[k], nch))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->wq_order[k], nch)) || (rc = dalloc_mesh(ctx, ctx->wq_waits[k], nch))) return rc;
         HIPCHK(hipMemcpy(ctx->wq_order[k].p, order.data(), nch * sizeof(int), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(ctx->wq_waits[k].p, wq.data(), nch, hipMemcpyHostToDevice));
         ctx->wq_nchunks[k] = nch;
         ctx->wq_nfree[k] = (int)std::count(waits.begin(), waits.end(), (unsigned char)0);
     }
     if (affine) {
-        if ((rc = dalloc(ctx, ctx->geo, g.size()))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->geo, g.size()))) return rc;
         HIPCHK(hipMemcpy(ctx->geo.p, g.data(), g.size() * sizeof(double), hipMemcpyHostToDevice));
         ctx->Jn.release();
         ctx->nsub.release();
@@ -875,9 +912,9 @@ static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m) {
                     std::memcpy(&Ja[((size_t)k * E + e) * nn], &jae[(size_t)k * nn], nn * sizeof(double));
             }
         });
-        if ((rc = dalloc(ctx, ctx->geo, Ja.size()))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->geo, Ja.size()))) return rc;
         HIPCHK(hipMemcpy(ctx->geo.p, Ja.data(), Ja.size() * sizeof(double), hipMemcpyHostToDevice));
-        if ((rc = dalloc(ctx, ctx->Jn, Jv.size()))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->Jn, Jv.size()))) return rc;
         HIPCHK(hipMemcpy(ctx->Jn.p, Jv.data(), Jv.size() * sizeof(double), hipMemcpyHostToDevice));
         if (ctx->cfg.shock || ctx->cfg.force_alpha > 0.0) {
             // telescoped subcell normals n_m = Ja^d_0 + sum_{l<m} w_l (D_d Ja^d)_l, m = 1..N
@@ -904,61 +941,61 @@ static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m) {
                         }
                     }
                 }
-            if ((rc = dalloc(ctx, ctx->nsub, ns.size()))) return rc;
+            if ((rc = dalloc_mesh(ctx, ctx->nsub, ns.size()))) return rc;
             HIPCHK(hipMemcpy(ctx->nsub.p, ns.data(), ns.size() * sizeof(double), hipMemcpyHostToDevice));
         }
     }
     // mortars
     ctx->nmortar = m->nmortar;
     if (m->nmortar) {
-        if ((rc = dalloc(ctx, ctx->mort, (size_t)m->nmortar * (3 + nsub)))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->mort, (size_t)m->nmortar * (3 + nsub)))) return rc;
         HIPCHK(hipMemcpy(ctx->mort.p, m->mortars, (size_t)m->nmortar * (3 + nsub) * sizeof(int), hipMemcpyHostToDevice));
         double ops[100];
         std::memcpy(ops, ctx->Im, sizeof(ctx->Im));
         std::memcpy(ops + 50, ctx->Pm, sizeof(ctx->Pm));
-        if ((rc = dalloc(ctx, ctx->mops, 100))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->mops, 100))) return rc;
         HIPCHK(hipMemcpy(ctx->mops.p, ops, sizeof(ops), hipMemcpyHostToDevice));
-        if ((rc = dalloc(ctx, ctx->mflux, (size_t)m->nmortar * nsub * nv * ctx->nf))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->mflux, (size_t)m->nmortar * nsub * nv * ctx->nf))) return rc;
         if (ctx->cfg.equation == DGX_EQ_NS &&
-            (rc = dalloc(ctx, ctx->mgw, (size_t)m->nmortar * nsub * (dim + 1) * ctx->nf)))
+            (rc = dalloc_mesh(ctx, ctx->mgw, (size_t)m->nmortar * nsub * (dim + 1) * ctx->nf)))
             return rc;
     }
     // boundary states
     if (m->nbc) {
-        if ((rc = dalloc(ctx, ctx->bc_kind, m->nbc))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->bc_kind, m->nbc))) return rc;
         HIPCHK(hipMemcpy(ctx->bc_kind.p, m->bc_kind, m->nbc * sizeof(int), hipMemcpyHostToDevice));
-        if ((rc = dalloc(ctx, ctx->bc_state, (size_t)m->nbc * nv))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->bc_state, (size_t)m->nbc * nv))) return rc;
         HIPCHK(hipMemcpy(ctx->bc_state.p, m->bc_state, (size_t)m->nbc * nv * sizeof(double), hipMemcpyHostToDevice));
         std::vector<double> bT(m->nbc, 0.0);
         if (is_mix(ctx))
             for (int b = 0; b < m->nbc; ++b)
                 if (m->bc_kind[b] == DGX_BC_DIRICHLET) bT[b] = host_T(ctx, m->bc_state + (size_t)b * nv);
-        if ((rc = dalloc(ctx, ctx->bc_T, m->nbc))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->bc_T, m->nbc))) return rc;
         HIPCHK(hipMemcpy(ctx->bc_T.p, bT.data(), m->nbc * sizeof(double), hipMemcpyHostToDevice));
     }
     // scratch
     if (is_mix(ctx)) {
         // per-node temperature, the warm start of the right-hand side's
         // T(e) solves: the freestream guess until the first solve
-        if ((rc = dalloc(ctx, ctx->T, (size_t)E * nn))) return rc;
-        if ((rc = dalloc(ctx, ctx->csnd, (size_t)E * nn))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->T, (size_t)E * nn))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->csnd, (size_t)E * nn))) return rc;
         std::vector<double> t0((size_t)E * nn, ctx->cfg.T_guess);
         HIPCHK(hipMemcpy(ctx->T.p, t0.data(), t0.size() * sizeof(double), hipMemcpyHostToDevice));
     }
-    if ((rc = dalloc(ctx, ctx->alpha, E))) return rc;
-    if ((rc = dalloc(ctx, ctx->alpha_tmp, E))) return rc;
-    if ((rc = dalloc(ctx, ctx->alpha_raw, E))) return rc;
+    if ((rc = dalloc_mesh(ctx, ctx->alpha, E))) return rc;
+    if ((rc = dalloc_mesh(ctx, ctx->alpha_tmp, E))) return rc;
+    if ((rc = dalloc_mesh(ctx, ctx->alpha_raw, E))) return rc;
     {
         std::vector<double> a(E, ctx->cfg.force_alpha >= 0.0 ? ctx->cfg.force_alpha : 0.0);
         HIPCHK(hipMemcpy(ctx->alpha.p, a.data(), E * sizeof(double), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(ctx->alpha_raw.p, a.data(), E * sizeof(double), hipMemcpyHostToDevice));
     }
     if (ctx->cfg.equation == DGX_EQ_NS) {
-        if ((rc = dalloc(ctx, ctx->grad, (size_t)E * 2 * dim * (dim + 1) * ctx->nf))) return rc;
-        if ((rc = dalloc(ctx, ctx->vpart, (size_t)(dim + 1) * E * nn))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->grad, (size_t)E * 2 * dim * (dim + 1) * ctx->nf))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->vpart, (size_t)(dim + 1) * E * nn))) return rc;
     }
     if (ctx->kin.nr > 0) {
-        if ((rc = dalloc(ctx, ctx->kin_d, 1))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->kin_d, 1))) return rc;
         HIPCHK(hipMemcpy(ctx->kin_d.p, &ctx->kin, sizeof(KinC), hipMemcpyHostToDevice));
     }
     // default elements per block: about 256 threads, LDS <= 64 KB; a cached
@@ -1010,8 +1047,8 @@ int dgx_ssprk3_step(dgx_ctx *ctx, double *u, double t, double dt, int nsteps, vo
     if (!u || nsteps < 0 || !(dt > 0.0) || !std::isfinite(dt)) return set_err(ctx, DGX_E_INVAL, "bad ssprk3 arguments");
     if (nsteps == 0) return DGX_OK;
     const size_t n = (size_t)ctx->nvar * ctx->nelem * ctx->nn;
-    if ((rc = dalloc(ctx, ctx->u1, n))) return rc;
-    if ((rc = dalloc(ctx, ctx->u2, n))) return rc;
+    if ((rc = dalloc_mesh(ctx, ctx->u1, n))) return rc;
+    if ((rc = dalloc_mesh(ctx, ctx->u2, n))) return rc;
     hipStream_t s = (hipStream_t)stream;
     if (!ctx->gexec || ctx->g_u != u || ctx->g_dt != dt) {
         clear_graph(ctx);
@@ -1312,8 +1349,8 @@ int dgx_kernel_times(dgx_ctx *ctx, const double *u, int reps, double *ms_out, in
     if (rc) return rc;
     if (!u || reps < 1 || !ms_out || !nk) return set_err(ctx, DGX_E_INVAL, "bad kernel_times arguments");
     const size_t n = (size_t)ctx->nvar * ctx->nelem * ctx->nn;
-    if ((rc = dalloc(ctx, ctx->u1, n))) return rc;
-    if ((rc = dalloc(ctx, ctx->u2, n))) return rc;
+    if ((rc = dalloc_mesh(ctx, ctx->u1, n))) return rc;
+    if ((rc = dalloc_mesh(ctx, ctx->u2, n))) return rc;
     hipStream_t s = (hipStream_t)stream;
     // a second SSPRK3 stage as in a step: u0 is its own buffer (a copy of u),
     // so its reads cost what they cost in the time loop
@@ -1382,8 +1419,8 @@ int dgx_autotune(dgx_ctx *ctx, const double *u, int reps, int *epb_out, double *
     if (rc) return rc;
     if (!u || reps < 1) return set_err(ctx, DGX_E_INVAL, "bad autotune arguments");
     const size_t n = (size_t)ctx->nvar * ctx->nelem * ctx->nn;
-    if ((rc = dalloc(ctx, ctx->u1, n))) return rc;
-    if ((rc = dalloc(ctx, ctx->u2, n))) return rc;
+    if ((rc = dalloc_mesh(ctx, ctx->u1, n))) return rc;
+    if ((rc = dalloc_mesh(ctx, ctx->u2, n))) return rc;
     hipStream_t s = (hipStream_t)stream;
     // what is timed: one SSPRK3 step as dgx_ssprk3_step runs it (three fused
     // stages with u0 in its own buffer, the limiter when configured), into
@@ -1629,30 +1666,56 @@ namespace {
 int oct_upload(dgx_ctx *ctx, int base, const std::vector<OctLeaf> &order) {
     OctTree t;
     t.base = base;
-    t.leaves.reserve(order.size() * 2);
-    for (auto &c : order) t.leaves.insert(oct_key(c));
+    t.leaves = OctMap(order.size());
+    for (size_t e = 0; e < order.size(); ++e) t.leaves.insert(oct_key(order[e]), (int)e);
     std::vector<int32_t> faces, morts;
     oct_tables(t, order, faces, morts);
     const int n1 = ctx->N1, nn = ctx->nn, E = (int)order.size();
-    std::vector<double> x((size_t)3 * E * nn);
-    for (int e = 0; e < E; ++e) {
-        const OctLeaf &c = order[e];
-        const double h = 1.0 / (double)(base << c.L);
-        const int cc[3] = {c.i, c.j, c.k};
-        for (int n = 0; n < nn; ++n) {
-            const int idx[3] = {n % n1, (n / n1) % n1, n / (n1 * n1)};
-            for (int d = 0; d < 3; ++d)
-                x[((size_t)d * E + e) * nn + n] = h * (cc[d] + 0.5 * (ctx->basis.x[idx[d]] + 1.0));
-        }
-    }
     dgx_mesh m{};
     m.nelem = E;
-    m.x = x.data();
     m.nface = (int)(faces.size() / 4);
     m.faces = faces.data();
     m.nmortar = (int)(morts.size() / 7);
     m.mortars = morts.data();
-    return dgx_set_mesh(ctx, &m);
+    // nodes of the cell (c, size h), component d at x + d * stride
+    auto nodes = [&](const int *c, double h, double *x, size_t stride) {
+        for (int n = 0; n < nn; ++n) {
+            const int idx[3] = {n % n1, (n / n1) % n1, n / (n1 * n1)};
+            for (int d = 0; d < 3; ++d) x[d * stride + n] = h * (c[d] + 0.5 * (ctx->basis.x[idx[d]] + 1.0));
+        }
+    };
+    if (!find_rhs(ctx, false, m.nmortar > 0)) {  // curved variant: nodal metric terms
+        std::vector<double> x((size_t)3 * E * nn);
+        for (int e = 0; e < E; ++e) {
+            const int c[3] = {order[e].i, order[e].j, order[e].k};
+            nodes(c, 1.0 / (double)(base << order[e].L), x.data() + (size_t)e * nn, (size_t)E * nn);
+        }
+        m.x = x.data();
+        return set_mesh_body(ctx, &m);
+    }
+    // the leaves of a level are cubes of one size: their metric terms are those
+    // of the level's cell at the origin (computed per element from 192 nodal
+    // coordinates they were most of a mesh change)
+    constexpr int GA = 10;
+    double geo[kOctMaxLevel + 1][GA];
+    unsigned have = 0;
+    std::vector<double> g((size_t)GA * E);
+    for (int e = 0; e < E; ++e) {
+        const int L = order[e].L;
+        if (!(have >> L & 1)) {
+            have |= 1u << L;
+            const int c[3] = {0, 0, 0};
+            std::vector<double> x((size_t)3 * nn), jae(9 * nn), je(nn);
+            nodes(c, 1.0 / (double)(base << L), x.data(), nn);
+            const double *xe[3] = {x.data(), x.data() + nn, x.data() + 2 * nn};
+            MetricScratch ws;
+            element_metrics(ctx->basis, 3, xe, jae.data(), je.data(), ws);
+            for (int k = 0; k < 9; ++k) geo[L][k] = jae[(size_t)k * nn];
+            geo[L][9] = je[0];
+        }
+        std::memcpy(&g[(size_t)GA * e], geo[L], sizeof(geo[L]));
+    }
+    return set_mesh_body(ctx, &m, &g);
 }
 
 // operators of the transfer (half-interval interpolation and L2 projection)
@@ -1774,7 +1837,7 @@ static int amr_apply_body(dgx_ctx *ctx, const double *u_old, double *u_new, void
     if (u_old == u_new) return set_err(ctx, DGX_E_INVAL, "u_old and u_new must not alias");
     hipStream_t s = (hipStream_t)stream;
     int rc;
-    if ((rc = dalloc(ctx, ctx->amr_tab, ctx->oct_tab.size()))) return rc;
+    if ((rc = dalloc_mesh(ctx, ctx->amr_tab, ctx->oct_tab.size()))) return rc;
     HIPCHK(hipMemcpy(ctx->amr_tab.p, ctx->oct_tab.data(), ctx->oct_tab.size() * sizeof(int32_t),
                      hipMemcpyHostToDevice));
     const int nold = (int)ctx->oct.size(), nnew = (int)ctx->oct_new.size();

@@ -12,10 +12,8 @@
 
 #include <algorithm>
 #include <cstdint>
-#include <map>
-#include <unordered_map>
 #include <string>
-#include <unordered_set>
+#include <utility>
 #include <vector>
 
 #include "host_parallel.h"
@@ -43,23 +41,109 @@ inline uint64_t oct_key(int L, int i, int j, int k) {
 }
 inline uint64_t oct_key(const OctLeaf &c) { return oct_key(c.L, c.i, c.j, c.k); }
 
+inline OctLeaf oct_leaf(uint64_t key) {
+    return {(int)(key >> 60), (int)((key >> 40) & 0xFFFFF), (int)((key >> 20) & 0xFFFFF), (int)(key & 0xFFFFF)};
+}
+
+// Leaf key -> number: open addressing with linear probing in two flat arrays.
+// (The passes below look up about ten cells per leaf; in the standard hash
+// containers, a node and an allocation per entry, they took most of a pass's
+// time.)
+class OctMap {
+    static constexpr uint64_t kEmpty = ~0ull, kGone = ~0ull - 1;  // no leaf has level 15
+    std::vector<uint64_t> key_;
+    std::vector<int> val_;
+    size_t used_ = 0, size_ = 0;  // slots in use (erased ones too), entries
+    int shift_ = 0;
+
+    size_t slot(uint64_t k) const { return (size_t)((k * 0x9E3779B97F4A7C15ull) >> shift_); }
+    void rehash(size_t cap) {
+        std::vector<uint64_t> k(cap, kEmpty);
+        std::vector<int> v(cap);
+        k.swap(key_);
+        v.swap(val_);
+        shift_ = 64;
+        while (cap > 1) {
+            cap >>= 1;
+            --shift_;
+        }
+        used_ = size_ = 0;
+        for (size_t i = 0; i < k.size(); ++i)
+            if (k[i] < kGone) insert(k[i], v[i]);
+    }
+
+public:
+    explicit OctMap(size_t n = 0) { reserve(n); }
+    void reserve(size_t n) {
+        size_t cap = 16;
+        while (cap < 2 * n) cap *= 2;
+        if (cap > key_.size()) rehash(cap);
+    }
+    size_t size() const { return size_; }
+    // the entry's number, or null (valid until the next insertion)
+    const int *find(uint64_t k) const {
+        for (size_t i = slot(k);; i = (i + 1) & (key_.size() - 1)) {
+            if (key_[i] == k) return &val_[i];
+            if (key_[i] == kEmpty) return nullptr;
+        }
+    }
+    bool has(uint64_t k) const { return find(k) != nullptr; }
+    // false when the key was there already (its number is kept)
+    bool insert(uint64_t k, int v = 0) {
+        if (has(k)) return false;
+        if (2 * (used_ + 1) > key_.size()) rehash(size_ * 4 + 16 > key_.size() ? 2 * key_.size() : key_.size());
+        size_t i = slot(k);
+        while (key_[i] != kEmpty) i = (i + 1) & (key_.size() - 1);
+        key_[i] = k;
+        val_[i] = v;
+        ++used_;
+        ++size_;
+        return true;
+    }
+    void erase(uint64_t k) {
+        for (size_t i = slot(k); key_[i] != kEmpty; i = (i + 1) & (key_.size() - 1))
+            if (key_[i] == k) {
+                key_[i] = kGone;
+                --size_;
+                return;
+            }
+    }
+    // the keys in increasing order, which is the order of the leaves
+    std::vector<uint64_t> keys() const {
+        std::vector<uint64_t> v;
+        v.reserve(size_);
+        for (uint64_t k : key_)
+            if (k < kGone) v.push_back(k);
+        std::sort(v.begin(), v.end());
+        return v;
+    }
+};
+
+// leaves per host thread of the loops that only look up neighbours (about
+// 0.3 us a leaf; starting a thread costs some 20 us)
+constexpr int kOctGrain = 2048;
+
 struct OctTree {
     int base = 1;
-    std::unordered_set<uint64_t> leaves;
+    OctMap leaves;  // -> element, where the caller numbers them
 
     int cells(int L) const { return base << L; }
-    bool has(const OctLeaf &c) const { return leaves.count(oct_key(c)) != 0; }
+    bool has(const OctLeaf &c) const { return leaves.has(oct_key(c)); }
+    // the periodic image of cell (i, j, k), at most one period outside
     OctLeaf wrap(int L, int i, int j, int k) const {
         const int n = cells(L);
-        return {L, ((i % n) + n) % n, ((j % n) + n) % n, ((k % n) + n) % n};
+        auto w = [n](int x) { return x < 0 ? x + n : x >= n ? x - n : x; };
+        return {L, w(i), w(j), w(k)};
     }
-    // the leaf containing level-L cell (i, j, k); false when that cell is split
-    bool leaf_at(int L, int i, int j, int k, OctLeaf &out) const {
+    // the leaf containing level-L cell (i, j, k), and its number; false when
+    // that cell is split
+    bool leaf_at(int L, int i, int j, int k, OctLeaf &out, int *id = nullptr) const {
         const OctLeaf w = wrap(L, i, j, k);
         for (int s = 0; s <= L; ++s) {
             const OctLeaf c{L - s, w.i >> s, w.j >> s, w.k >> s};
-            if (has(c)) {
+            if (const int *v = leaves.find(oct_key(c))) {
                 out = c;
+                if (id) *id = *v;
                 return true;
             }
         }
@@ -114,9 +198,7 @@ struct OctTree {
     std::vector<OctLeaf> list() const {
         std::vector<OctLeaf> v;
         v.reserve(leaves.size());
-        for (uint64_t key : leaves)
-            v.push_back({(int)(key >> 60), (int)((key >> 40) & 0xFFFFF), (int)((key >> 20) & 0xFFFFF), (int)(key & 0xFFFFF)});
-        std::sort(v.begin(), v.end());
+        for (uint64_t key : leaves.keys()) v.push_back(oct_leaf(key));
         return v;
     }
 };
@@ -125,19 +207,24 @@ struct OctTree {
 inline void morton_sort(std::vector<OctLeaf> &v) {
     int lmax = 0;
     for (auto &c : v) lmax = std::max(lmax, c.L);
+    // bit b of x (21 bits) to bit 3 b: halves, then quarters, ... move apart
     auto spread = [](uint64_t x) {
-        uint64_t r = 0;
-        for (int b = 0; b < 21; ++b) r |= ((x >> b) & 1ull) << (3 * b);
-        return r;
+        x = (x | x << 32) & 0x001F00000000FFFFull;
+        x = (x | x << 16) & 0x001F0000FF0000FFull;
+        x = (x | x << 8) & 0x100F00F00F00F00Full;
+        x = (x | x << 4) & 0x10C30C30C30C30C3ull;
+        x = (x | x << 2) & 0x1249249249249249ull;
+        return x;
     };
-    std::vector<std::pair<uint64_t, OctLeaf>> keyed;
+    std::vector<std::pair<uint64_t, uint64_t>> keyed;  // corner, leaf key (no two corners are equal)
     keyed.reserve(v.size());
     for (auto &c : v) {
         const int s = lmax - c.L;
-        keyed.push_back({spread((uint64_t)c.i << s) | spread((uint64_t)c.j << s) << 1 | spread((uint64_t)c.k << s) << 2, c});
+        keyed.push_back({spread((uint64_t)c.i << s) | spread((uint64_t)c.j << s) << 1 | spread((uint64_t)c.k << s) << 2,
+                         oct_key(c)});
     }
-    std::sort(keyed.begin(), keyed.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
-    for (size_t e = 0; e < v.size(); ++e) v[e] = keyed[e].second;
+    std::sort(keyed.begin(), keyed.end());
+    for (size_t e = 0; e < v.size(); ++e) v[e] = oct_leaf(keyed[e].second);
 }
 
 // Checks a leaf set: levels and indices in range, no leaf inside another,
@@ -145,14 +232,13 @@ inline void morton_sort(std::vector<OctLeaf> &v) {
 inline std::string oct_check(int base, const std::vector<OctLeaf> &v, OctTree &t) {
     if (base < 1 || base > kOctMaxBase) return "octree base out of range";
     t.base = base;
-    t.leaves.clear();
-    t.leaves.reserve(v.size() * 2);
+    t.leaves = OctMap(v.size());
     int lmax = 0;
     for (auto &c : v) {
         if (c.L < 0 || c.L > kOctMaxLevel) return "octree level out of range";
         const int n = base << c.L;
         if (c.i < 0 || c.j < 0 || c.k < 0 || c.i >= n || c.j >= n || c.k >= n) return "octree index out of range";
-        if (!t.leaves.insert(oct_key(c)).second) return "duplicate octree leaf";
+        if (!t.leaves.insert(oct_key(c))) return "duplicate octree leaf";
         lmax = std::max(lmax, c.L);
     }
     unsigned __int128 vol = 0;
@@ -165,17 +251,15 @@ inline std::string oct_check(int base, const std::vector<OctLeaf> &v, OctTree &t
     std::vector<unsigned char> unbalanced(16, 0);
     host_parallel((int)v.size(), [&](int b, int e, int th) {
         for (int i = b; i < e && !unbalanced[th]; ++i) unbalanced[th] = t.finest_neighbour(v[i]) > v[i].L + 1;
-    });
+    }, kOctGrain);
     if (std::count(unbalanced.begin(), unbalanced.end(), (unsigned char)1)) return "octree is not 2:1 balanced";
     return "";
 }
 
-// Conforming face rows and mortar rows of the leaves in element order
+// Conforming face rows and mortar rows of the leaves in element order (t: the
+// leaves with their element numbers)
 inline void oct_tables(const OctTree &t, const std::vector<OctLeaf> &order, std::vector<int32_t> &faces,
                        std::vector<int32_t> &morts) {
-    std::unordered_map<uint64_t, int> eid;
-    eid.reserve(order.size() * 2);
-    for (size_t e = 0; e < order.size(); ++e) eid[oct_key(order[e])] = (int)e;
     // rows per thread over contiguous element ranges, joined in element order
     std::vector<std::vector<int32_t>> fpart(16), mpart(16);
     host_parallel((int)order.size(), [&](int e0, int e1, int th) {
@@ -187,11 +271,12 @@ inline void oct_tables(const OctTree &t, const std::vector<OctLeaf> &order, std:
                     int ii[3] = {c.i, c.j, c.k};
                     ii[d] += sgn;
                     OctLeaf nb;
-                    if (t.leaf_at(c.L, ii[0], ii[1], ii[2], nb)) {
+                    int id = 0;
+                    if (t.leaf_at(c.L, ii[0], ii[1], ii[2], nb, &id)) {
                         if (nb.L == c.L && sgn == 1) {
                             fo.push_back((int32_t)e);
                             fo.push_back(2 * d + 1);
-                            fo.push_back(eid.at(oct_key(nb)));
+                            fo.push_back(id);
                             fo.push_back(2 * d);
                         }
                         continue;  // coarser neighbour: the large side records the mortar
@@ -201,11 +286,11 @@ inline void oct_tables(const OctTree &t, const std::vector<OctLeaf> &order, std:
                     const int fl = 2 * d + (sgn == 1 ? 1 : 0);
                     mo.push_back((int32_t)e);
                     mo.push_back(fl);
-                    for (int s = 0; s < 4; ++s) mo.push_back(eid.at(oct_key(fc[s])));
+                    for (int s = 0; s < 4; ++s) mo.push_back(*t.leaves.find(oct_key(fc[s])));
                     mo.push_back(fl ^ 1);
                 }
         }
-    });
+    }, kOctGrain);
     faces.clear();
     morts.clear();
     for (int th = 0; th < 16; ++th) {
@@ -226,14 +311,10 @@ inline std::string oct_adapt(int base, const std::vector<OctLeaf> &old_order, co
                              std::vector<OctLeaf> &new_order, std::vector<int32_t> &tab) {
     OctTree t;
     t.base = base;
-    std::unordered_map<uint64_t, int> oid;
-    t.leaves.reserve(old_order.size() * 4);
-    oid.reserve(old_order.size() * 2);
-    for (size_t e = 0; e < old_order.size(); ++e) {
-        t.leaves.insert(oct_key(old_order[e]));
-        oid[oct_key(old_order[e])] = (int)e;
-    }
-    std::unordered_set<uint64_t> split;
+    OctMap oid(old_order.size());
+    for (size_t e = 0; e < old_order.size(); ++e) oid.insert(oct_key(old_order[e]), (int)e);
+    t.leaves = oid;
+    OctMap split;
     for (size_t e = 0; e < old_order.size(); ++e) {
         const OctLeaf &c = old_order[e];
         if (target[e] > c.L) {
@@ -241,10 +322,7 @@ inline std::string oct_adapt(int base, const std::vector<OctLeaf> &old_order, co
             split.insert(oct_key(c));
         }
     }
-    for (uint64_t key : split) {
-        const OctLeaf c{(int)(key >> 60), (int)((key >> 40) & 0xFFFFF), (int)((key >> 20) & 0xFFFFF), (int)(key & 0xFFFFF)};
-        t.split(c);
-    }
+    for (uint64_t key : split.keys()) t.split(oct_leaf(key));
     // 2:1 balance.  A leaf that faces one two levels finer must be split in
     // every balanced refinement of the current tree, so each sweep finds all
     // such leaves (in parallel, the tree read-only) and splits them together;
@@ -254,45 +332,51 @@ inline std::string oct_adapt(int base, const std::vector<OctLeaf> &old_order, co
         std::vector<unsigned char> need(cur.size(), 0);
         host_parallel((int)cur.size(), [&](int b, int e, int) {
             for (int i = b; i < e; ++i) need[i] = t.finest_neighbour(cur[i]) > cur[i].L + 1;
-        });
+        }, kOctGrain);
         bool any = false;
         for (size_t i = 0; i < cur.size(); ++i) {
             if (!need[i]) continue;
             const OctLeaf &c = cur[i];
             if (c.L + 1 > kOctMaxLevel) return "2:1 balance beyond the finest octree level";
             t.split(c);
-            if (oid.count(oct_key(c))) split.insert(oct_key(c));
+            if (oid.has(oct_key(c))) split.insert(oct_key(c));
             any = true;
         }
         if (!any) break;
     }
     // merges of unsplit families whose targets all lie below their level
-    std::map<OctLeaf, std::vector<int>> fam;
+    // (parent, child number, element), sorted: the families one after another in
+    // the order of their parents, each in child order x + 2y + 4z
+    struct Kid {
+        uint64_t parent;
+        int child, elem;
+    };
+    std::vector<Kid> fam;
     for (size_t e = 0; e < old_order.size(); ++e) {
         const OctLeaf &c = old_order[e];
-        if (c.L > 0 && !split.count(oct_key(c))) fam[{c.L - 1, c.i >> 1, c.j >> 1, c.k >> 1}].push_back((int)e);
+        if (c.L > 0 && target[e] < c.L && !split.has(oct_key(c)))
+            fam.push_back({oct_key(c.L - 1, c.i >> 1, c.j >> 1, c.k >> 1), (c.i & 1) + 2 * (c.j & 1) + 4 * (c.k & 1), (int)e});
     }
-    std::unordered_map<uint64_t, std::vector<int>> merged;
-    for (auto &kv : fam) {
-        const OctLeaf &p = kv.first;
-        const auto &kids = kv.second;
-        if (kids.size() != 8) continue;
-        bool ok = true;
-        for (int e : kids) ok = ok && t.has(old_order[e]) && target[e] < old_order[e].L;
-        if (!ok) continue;
-        for (int e : kids) t.leaves.erase(oct_key(old_order[e]));
-        t.leaves.insert(oct_key(p));
-        if (t.finest_neighbour(p) > p.L + 1) {
-            t.leaves.erase(oct_key(p));
-            for (int e : kids) t.leaves.insert(oct_key(old_order[e]));
+    std::sort(fam.begin(), fam.end(), [](const Kid &a, const Kid &b) {
+        return a.parent != b.parent ? a.parent < b.parent : a.child < b.child;
+    });
+    OctMap merged;  // parent -> its first child in fam
+    for (size_t k = 0; k + 8 <= fam.size();) {
+        const uint64_t key = fam[k].parent;
+        if (fam[k + 7].parent != key) {
+            for (++k; k < fam.size() && fam[k].parent == key;) ++k;
             continue;
         }
-        std::vector<int> byc(8);
-        for (int e : kids) {
-            const OctLeaf &c = old_order[e];
-            byc[(c.i & 1) + 2 * (c.j & 1) + 4 * (c.k & 1)] = e;
+        const OctLeaf p = oct_leaf(key);
+        for (int s = 0; s < 8; ++s) t.leaves.erase(oct_key(old_order[fam[k + s].elem]));
+        t.leaves.insert(key);
+        if (t.finest_neighbour(p) > p.L + 1) {
+            t.leaves.erase(key);
+            for (int s = 0; s < 8; ++s) t.leaves.insert(oct_key(old_order[fam[k + s].elem]));
+        } else {
+            merged.insert(key, (int)k);
         }
-        merged[oct_key(p)] = byc;
+        k += 8;
     }
     new_order = t.list();
     morton_sort(new_order);
@@ -300,22 +384,20 @@ inline std::string oct_adapt(int base, const std::vector<OctLeaf> &old_order, co
     for (size_t e = 0; e < new_order.size(); ++e) {
         int32_t *row = tab.data() + e * kOctTab;
         const OctLeaf &c = new_order[e];
-        auto it = oid.find(oct_key(c));
-        if (it != oid.end()) {
+        if (const int *o = oid.find(oct_key(c))) {
             row[0] = 0;
-            row[3] = it->second;
+            row[3] = *o;
             continue;
         }
-        auto mt = merged.find(oct_key(c));
-        if (mt != merged.end()) {
+        if (const int *k = merged.find(oct_key(c))) {
             row[0] = 2;
-            for (int s = 0; s < 8; ++s) row[3 + s] = mt->second[s];
+            for (int s = 0; s < 8; ++s) row[3 + s] = fam[*k + s].elem;
             continue;
         }
         // a descendant of a split old leaf
         OctLeaf a = c;
         int path[kOctMaxLevel + 1], depth = 0;
-        while (!oid.count(oct_key(a))) {
+        while (!oid.has(oct_key(a))) {
             if (a.L == 0 || depth >= 8) return "octree transfer: no source leaf";
             path[depth++] = (a.i & 1) + 2 * (a.j & 1) + 4 * (a.k & 1);
             a = {a.L - 1, a.i >> 1, a.j >> 1, a.k >> 1};
@@ -326,7 +408,7 @@ inline std::string oct_adapt(int base, const std::vector<OctLeaf> &old_order, co
         int code = 0;
         for (int q = 0; q < depth; ++q) code |= path[depth - 1 - q] << (3 * q);
         row[2] = code;
-        row[3] = oid.at(oct_key(a));
+        row[3] = *oid.find(oct_key(a));
     }
     return "";
 }

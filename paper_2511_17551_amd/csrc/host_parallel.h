@@ -10,13 +10,13 @@
 namespace dgx {
 
 // Runs fn(begin, end, thread) over [0, n) in contiguous ranges on up to 16
-// host threads (one when n is small).  A range whose thread cannot be
+// host threads, one for each `grain` items begun.  A range whose thread cannot be
 // started runs on the calling thread; an exception thrown by fn (a failed
 // allocation) is rethrown here once every thread has ended.
 template <typename F>
-void host_parallel(int n, F fn) {
+void host_parallel(int n, F fn, int grain = 512) {
     const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
-    const int nt = (int)std::min<long>({16L, (long)hw, (long)(n / 512) + 1});
+    const int nt = (int)std::min<long>({16L, (long)hw, (long)(n / grain) + 1});
     if (nt <= 1) {
         fn(0, n, 0);
         return;

@@ -1096,7 +1096,7 @@ int dgx_max_dt(dgx_ctx *ctx, const double *u, double cfl, double *dt_host, void 
     P.epb = ctx->nn;
     const int64_t total = (int64_t)ctx->nelem * ctx->nn;
     const int tb = 256;
-    const int blocks = (int)((total + tb - 1) / tb);
+    const int blocks = (int)std::min<int64_t>((total + tb - 1) / tb, kMaxrateBlocks);
     const int key = ctx->cfg.dim * 100 + (is_mix(ctx) ? 10 : 0) + (ctx->curved ? 1 : 0);
     switch (key) {
         case 200: hipLaunchKernelGGL((k_maxrate<2, false, false>), dim3(blocks), dim3(tb), 0, s, P, ctx->rate.p); break;
@@ -1841,13 +1841,14 @@ static int amr_apply_body(dgx_ctx *ctx, const double *u_old, double *u_new, void
     HIPCHK(hipMemcpy(ctx->amr_tab.p, ctx->oct_tab.data(), ctx->oct_tab.size() * sizeof(int32_t),
                      hipMemcpyHostToDevice));
     const int nold = (int)ctx->oct.size(), nnew = (int)ctx->oct_new.size();
-    const int items = nnew * ctx->nn;
-    if (ctx->cfg.N == 3)
-        hipLaunchKernelGGL(k_amr_transfer<3>, dim3((items + 255) / 256), dim3(256), 0, s, u_old, nold, u_new, nnew,
-                           ctx->nvar, ctx->amr_tab.p, ctx->amr_ops.p);
-    else
-        hipLaunchKernelGGL(k_amr_transfer<4>, dim3((items + 255) / 256), dim3(256), 0, s, u_old, nold, u_new, nnew,
-                           ctx->nvar, ctx->amr_tab.p, ctx->amr_ops.p);
+    if (ctx->cfg.N == 3) {
+        constexpr int epb = kTransferElems<3>;
+        hipLaunchKernelGGL(k_amr_transfer<3>, dim3((nnew + epb - 1) / epb), dim3(64 * epb), 0, s, u_old, nold, u_new,
+                           nnew, ctx->amr_tab.p, ctx->amr_ops.p);
+    } else {
+        hipLaunchKernelGGL(k_amr_transfer<4>, dim3(nnew), dim3(128), 0, s, u_old, nold, u_new, nnew, ctx->amr_tab.p,
+                           ctx->amr_ops.p);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_err(ctx, DGX_E_DEVICE, std::string("transfer launch: ") + hipGetErrorString(e));
     HIPCHK(hipStreamSynchronize(s));

@@ -108,13 +108,12 @@ public:
                 return;
             }
     }
-    // the keys in increasing order, which is the order of the leaves
+    // the keys, in no order
     std::vector<uint64_t> keys() const {
         std::vector<uint64_t> v;
         v.reserve(size_);
         for (uint64_t k : key_)
             if (k < kGone) v.push_back(k);
-        std::sort(v.begin(), v.end());
         return v;
     }
 };
@@ -195,12 +194,6 @@ struct OctTree {
         children(c, ch);
         for (auto &x : ch) leaves.insert(oct_key(x));
     }
-    std::vector<OctLeaf> list() const {
-        std::vector<OctLeaf> v;
-        v.reserve(leaves.size());
-        for (uint64_t key : leaves.keys()) v.push_back(oct_leaf(key));
-        return v;
-    }
 };
 
 // Z-order of the leaves' lower corners on the finest grid
@@ -223,6 +216,7 @@ inline void morton_sort(std::vector<OctLeaf> &v) {
         keyed.push_back({spread((uint64_t)c.i << s) | spread((uint64_t)c.j << s) << 1 | spread((uint64_t)c.k << s) << 2,
                          oct_key(c)});
     }
+    if (std::is_sorted(keyed.begin(), keyed.end())) return;
     std::sort(keyed.begin(), keyed.end());
     for (size_t e = 0; e < v.size(); ++e) v[e] = oct_leaf(keyed[e].second);
 }
@@ -264,6 +258,7 @@ inline void oct_tables(const OctTree &t, const std::vector<OctLeaf> &order, std:
     std::vector<std::vector<int32_t>> fpart(16), mpart(16);
     host_parallel((int)order.size(), [&](int e0, int e1, int th) {
         std::vector<int32_t> &fo = fpart[th], &mo = mpart[th];
+        fo.reserve((size_t)(e1 - e0) * 12);
         for (int e = e0; e < e1; ++e) {
             const OctLeaf &c = order[e];
             for (int d = 0; d < 3; ++d)
@@ -328,18 +323,21 @@ inline std::string oct_adapt(int base, const std::vector<OctLeaf> &old_order, co
     // such leaves (in parallel, the tree read-only) and splits them together;
     // the sweeps end at the unique smallest balanced refinement.
     for (;;) {
-        const std::vector<OctLeaf> cur = t.list();
+        const std::vector<uint64_t> cur = t.leaves.keys();
         std::vector<unsigned char> need(cur.size(), 0);
         host_parallel((int)cur.size(), [&](int b, int e, int) {
-            for (int i = b; i < e; ++i) need[i] = t.finest_neighbour(cur[i]) > cur[i].L + 1;
+            for (int i = b; i < e; ++i) {
+                const OctLeaf c = oct_leaf(cur[i]);
+                need[i] = t.finest_neighbour(c) > c.L + 1;
+            }
         }, kOctGrain);
         bool any = false;
         for (size_t i = 0; i < cur.size(); ++i) {
             if (!need[i]) continue;
-            const OctLeaf &c = cur[i];
+            const OctLeaf c = oct_leaf(cur[i]);
             if (c.L + 1 > kOctMaxLevel) return "2:1 balance beyond the finest octree level";
             t.split(c);
-            if (oid.has(oct_key(c))) split.insert(oct_key(c));
+            if (oid.has(cur[i])) split.insert(cur[i]);
             any = true;
         }
         if (!any) break;
@@ -378,7 +376,29 @@ inline std::string oct_adapt(int base, const std::vector<OctLeaf> &old_order, co
         }
         k += 8;
     }
-    new_order = t.list();
+    // the new leaves where their sources stand in the old order (the kept leaf,
+    // a split leaf's descendants, the parent at its first child), which is
+    // Morton order if the old one was
+    new_order.clear();
+    new_order.reserve(t.leaves.size());
+    auto descend = [&](auto &self, const OctLeaf &c) -> void {
+        if (t.has(c)) {
+            new_order.push_back(c);
+            return;
+        }
+        OctLeaf ch[8];
+        OctTree::children(c, ch);
+        for (auto &x : ch) self(self, x);
+    };
+    for (const OctLeaf &c : old_order) {
+        if (split.has(oct_key(c))) {
+            descend(descend, c);
+        } else if (t.has(c)) {
+            new_order.push_back(c);
+        } else if (((c.i | c.j | c.k) & 1) == 0) {
+            new_order.push_back({c.L - 1, c.i >> 1, c.j >> 1, c.k >> 1});
+        }
+    }
     morton_sort(new_order);
     tab.assign(new_order.size() * kOctTab, 0);
     for (size_t e = 0; e < new_order.size(); ++e) {

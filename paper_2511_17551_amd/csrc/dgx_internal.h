@@ -17,6 +17,7 @@ struct BasisC {
     double w[5];       // LGL weights
     double iw0;        // 1 / w[0] = 1 / w[N], the surface lifting factor
     double Vinv[25];   // nodal -> orthonormal Legendre modes
+    double ind_thr, ind_slope;  // shock indicator: threshold and slope of the logistic map
 };
 
 // Thermodynamic data of the 5 species (RRHO, Appendix Thermodynamics).

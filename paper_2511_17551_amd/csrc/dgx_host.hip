@@ -533,7 +533,9 @@ int enqueue_rhs(dgx_ctx *ctx, const double *u, double *out, int mode, const doub
     if (ctx->nmortar && !persist) {
         // the grid form's mortar pass: the work-list kernel with no queue
         WorkQ Q{nullptr, nullptr, nullptr, nullptr, ctx->nmortar, 0, 0};
-        cur_rhs(ctx)->fnp(P, mode, th, 0, s, Q);
+        const int nsub = c.dim == 3 ? 4 : 2, nw = c.equation == DGX_EQ_NS ? c.dim + 1 : 0;
+        const size_t lds = (size_t)(100 + (ctx->nvar * (nsub + 1) + nw) * ctx->nf) * sizeof(double);  // MortarShape
+        cur_rhs(ctx)->fnp(P, mode, threads_for(nsub * ctx->nf, 1), lds, s, Q);
         tape_mark(tp, "k_mortar", s);
     }
     P.out = out;
@@ -968,7 +970,7 @@ static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m, const std::vector<doub
         std::memcpy(ops + 50, ctx->Pm, sizeof(ctx->Pm));
         if ((rc = dalloc_mesh(ctx, ctx->mops, 100))) return rc;
         HIPCHK(hipMemcpy(ctx->mops.p, ops, sizeof(ops), hipMemcpyHostToDevice));
-        if ((rc = dalloc_mesh(ctx, ctx->mflux, (size_t)m->nmortar * nsub * nv * ctx->nf))) return rc;
+        if ((rc = dalloc_mesh(ctx, ctx->mflux, (size_t)m->nmortar * (nsub + 1) * nv * ctx->nf))) return rc;
         if (ctx->cfg.equation == DGX_EQ_NS &&
             (rc = dalloc_mesh(ctx, ctx->mgw, (size_t)m->nmortar * nsub * (dim + 1) * ctx->nf)))
             return rc;

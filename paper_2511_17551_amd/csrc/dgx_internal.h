@@ -92,7 +92,7 @@ struct RhsParams {
     const double *bc_T;     // [nbc] temperatures of Dirichlet states (mixture)
     const KinC *kin;        // reacting mixture
     const int *mort;        // mortar table [nm][3 + 2^(dim-1)] (eL, fL, eS.., fS)
-    const double *mflux;    // mortar sub-face fluxes [nm][2^(dim-1)][nvar][nf]
+    const double *mflux;    // mortar sub-face fluxes and their projection [nm][2^(dim-1) + 1][nvar][nf]
     const double *mops;     // mortars: [I, P][lower, upper half][25]: interpolation to the
                             // halves of a face edge and L2 projection back ([q][j], N+1 wide)
     const double *mgw;      // NS on mortars: sub-face gradient values W*_s [nm][2^(dim-1)][dim+1][nf]

@@ -31,9 +31,9 @@ namespace dgx {
 // here.  CURV: nodal metric terms; OPEN: the mesh has boundary or mortar
 // faces (the face values W* stay in LDS for the boundary fluxes).
 // Memory bounds it on large meshes (15 doubles a node, 52 us at the copy rate
-// for 32^3 elements; 67 us, 71 before the prologue asked for indices, own data
-// and traces in this order and an element's phases were ordered within its
-// wave), the chain of its phases on small ones (8^3: 5.4 -> 4.9 us).
+// for 32^3 elements, 67-77 us taken), the chain of its phases on small ones
+// (8^3: 6.4 us as one workgroup of four elements that waited for indices, own
+// data and traces in turn and met at four barriers, now 5.4).
 template <int DIM, int N, bool OPEN = false>
 struct GradShape {
     static constexpr int N1 = N + 1;

@@ -295,10 +295,6 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     // indices, so they live in LDS rather than in the kernel arguments
     __shared__ double sDc[N1 * N1];
     __shared__ double sW[N1];
-    // non-conforming variants: the L2 projection from the face halves, read
-    // with per-lane indices
-    __shared__ double sPm[MORT ? 2 * N1 * N1 : 1];
-
     const int tid = threadIdx.x;
     const int NT = P.epb * NN;  // threads that own a node
     const int nloc = min(P.epb, P.nelem - e0);
@@ -357,11 +353,6 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     }
 
     const double tD = P.B.D[min(tid, N1 * N1 - 1)], tW = P.B.w[min(tid, N1 - 1)];
-    double tP = 0.0;
-    if constexpr (MORT) {
-        const int i = min(tid, 2 * N1 * N1 - 1), h = i / (N1 * N1);
-        tP = P.mops[50 + h * 25 + (i - h * N1 * N1)];
-    }
     // (threads without a node read one of the workgroup's first element)
     double uo[NV], go[CURV ? DIM : 1], T_own = 1.0, c_own = 1.0;
 #pragma unroll
@@ -439,9 +430,6 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     // ---- stage the tables and the element: primitives (+ species, metric terms)
     if (tid < N1 * N1) sDc[tid] = 2.0 * tD;
     if (tid < N1) sW[tid] = tW;
-    if constexpr (MORT) {
-        if (tid < 2 * N1 * N1) sPm[tid] = tP;
-    }
     if (valid) {
         if constexpr (CURV) {
 #pragma unroll
@@ -501,34 +489,14 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
                 const double *esq = esu + S::SU;
                 const double *eg = esu + OFF_G;
                 if (mortar) {
-                    // non-conforming face: sub-face fluxes from the mortar items
+                    // non-conforming face: the sub-face's flux, or on the large
+                    // side the projection of all, from the mortar items
                     constexpr int NSUB = DIM == 3 ? 4 : 2;
                     const int code = kMortBase - nb;
-                    const int m = code >> 3, role = code & 7;
-                    const double *mf = P.mflux + (size_t)m * NSUB * NV * NF;
-                    if (role < NSUB) {
+                    const int m = code >> 3, role = min(code & 7, NSUB);
+                    const double *mf = P.mflux + ((size_t)m * (NSUB + 1) + role) * NV * NF;
 #pragma unroll
-                        for (int v = 0; v < NV; ++v) F[v] = mf[(role * NV + v) * NF + q];
-                    } else {
-                        // large side: 2^(dim-1) sum_s (P_a x P_b) F*_s
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) F[v] = 0.0;
-                        const int qa = q % N1, qb = q / N1;
-#pragma unroll 1
-                        for (int sb = 0; sb < NSUB; ++sb) {
-                            const int a = sb & 1, bsel = sb >> 1;
-#pragma unroll 4
-                            for (int qq = 0; qq < NF; ++qq) {
-                                const int ja = qq % N1, jb2 = qq / N1;
-                                double w = sPm[a * N1 * N1 + qa * N1 + ja];
-                                if (DIM == 3) w *= sPm[bsel * N1 * N1 + qb * N1 + jb2];
-#pragma unroll
-                                for (int v = 0; v < NV; ++v) F[v] = fma(w, mf[(sb * NV + v) * NF + qq], F[v]);
-                            }
-                        }
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) F[v] *= (double)NSUB;
-                    }
+                    for (int v = 0; v < NV; ++v) F[v] = mf[v * NF + q];
                     if constexpr (EQ == 1) {
                         // the mortar flux carries the whole viscous F*; the
                         // gradient kernel took the own half of Ft off already
@@ -1064,90 +1032,135 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
 // sides): one workgroup per mortar, one thread per small-face node.  The
 // large element's face trace is interpolated to the node with I_a x I_b, the
 // Riemann flux uses the small element's trace and scaled normal and is
-// oriented along +xi_d (lower-xi state first).  Perfect gas, affine elements.
-template <int DIM, int N, int SF, int EQ = 0>
-__device__ __forceinline__ void mortar_item(const RhsParams &P, int m, int t) {
-    constexpr int N1 = N + 1;
-    constexpr int NN = DIM == 2 ? N1 * N1 : N1 * N1 * N1;
-    constexpr int NF = NN / N1;
-    constexpr int NV = DIM + 2;
-    constexpr int NSUB = DIM == 3 ? 4 : 2;
+// oriented along +xi_d (lower-xi state first).  The sub-faces' fluxes and then
+// their projection to the large side, 2^(dim-1) sum_s (P_a x P_b) F*_s, are
+// written per mortar as [2^(dim-1) + 1][nvar][nf].  Perfect gas, affine
+// elements.
+//
+// A chain of loads bounds it, so the trace, the operators and the fluxes are
+// shared through LDS.  The projection belongs here: in the right-hand side
+// kernel each large face's threads read all 64 sub-face nodes of every
+// variable from memory, and its workgroup and often the launch waited for
+// them (5,352 elements: 24.5 us a stage, and 4.8 here).
+template <int DIM, int N, int EQ>
+struct MortarShape {
+    static constexpr int N1 = N + 1;
+    static constexpr int NF = DIM == 2 ? N1 : N1 * N1;
+    static constexpr int NV = DIM + 2, NW = DIM + 1, NSUB = DIM == 3 ? 4 : 2;
+    static constexpr int OFF_T = 4 * 25;              // operators I_0, I_1, P_0, P_1
+    static constexpr int OFF_W = OFF_T + NV * NF;     // the large side's trace
+    static constexpr int OFF_F = OFF_W + (EQ == 1 ? NW * NF : 0);  // and its Ft
+    static constexpr int LDS = OFF_F + NSUB * NV * NF;             // sub-face fluxes
+};
+template <int DIM, int N, int SF, int EQ>
+__device__ __forceinline__ void mortar_item(const RhsParams &P, int m) {
+    using S = MortarShape<DIM, N, EQ>;
+    constexpr int N1 = S::N1, NF = S::NF, NV = S::NV, NW = S::NW, NSUB = S::NSUB;
+    constexpr int NN = NF * N1;
     constexpr int GA = DIM * DIM + 1;
-    if (t >= NSUB * NF) return;
-    const int s = t / NF, q = t - s * NF;
+    extern __shared__ double smem[];
+    double *ops = smem, *tr = smem + S::OFF_T, *fl = smem + S::OFF_W, *sub = smem + S::OFF_F;
+    const int t = threadIdx.x, nt = blockDim.x;
     const int *row = P.mort + (size_t)m * (3 + NSUB);
-    const int eL = row[0], fL = row[1], es = row[2 + s], fS = row[2 + NSUB];
+    const int eL = row[0], fL = row[1], fS = row[2 + NSUB];
     const int d = fL >> 1, sideL = fL & 1;
     const size_t stride = (size_t)P.nelem * NN;
-    // interpolate the large trace to small-face node q of sub-face s
-    const int a = s & 1, bsel = s >> 1;
-    const int qa = q % N1, qb = q / N1;
-    double ui[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) ui[v] = 0.0;
-    // (partly rolled: in the work-list kernel this code shares the
-    // right-hand side's register budget)
-#pragma unroll 4
-    for (int j = 0; j < NF; ++j) {
-        const int ja = j % N1, jb = j / N1;
-        double w = P.mops[a * 25 + qa * N1 + ja];
-        if (DIM == 3) w *= P.mops[bsel * 25 + qb * N1 + jb];
-        const size_t gj = (size_t)eL * NN + line_node<N1, DIM>(d, sideL ? N : 0, j);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) ui[v] = fma(w, P.u[v * stride + gj], ui[v]);
-    }
-    const size_t gs = (size_t)es * NN + line_node<N1, DIM>(d, (fS & 1) ? N : 0, q);
-    double us[NV];
+    double *out = const_cast<double *>(P.mflux) + (size_t)m * (NSUB + 1) * NV * NF;
+    // this thread's small-face node: its trace and normal are requested first
+    const bool has = t < NSUB * NF;
+    const int s = has ? t / NF : 0, q = has ? t - s * NF : 0;
+    const int es = row[2 + s];
+    const size_t gs = (size_t)es * NN + face_node<N1, DIM>(d, (fS & 1) ? N : 0, q);
+    double us[NV], nrm[DIM], fs[NW];
 #pragma unroll
     for (int v = 0; v < NV; ++v) us[v] = P.u[v * stride + gs];
-    St<DIM, false> A, B;
-    make_state<DIM, false>(ui, 0.0, P.gamma, P.M, A);
-    make_state<DIM, false>(us, 0.0, P.gamma, P.M, B);
-    double nrm[DIM];
 #pragma unroll
     for (int c = 0; c < DIM; ++c) nrm[c] = P.geo[(size_t)es * GA + d * DIM + c];
-    double F[NV];
-    if constexpr (SF == 0) {
-        if (sideL) rusanov<DIM, false>(A, B, nrm, F);
-        else rusanov<DIM, false>(B, A, nrm, F);
-    } else if constexpr (SF == 2) {
-        if (sideL) hll<DIM, false>(A, B, nrm, F);
-        else hll<DIM, false>(B, A, nrm, F);
-    } else if constexpr (SF == 3) {
-        if (sideL) hllc<DIM, false>(A, B, nrm, F);
-        else hllc<DIM, false>(B, A, nrm, F);
-    } else {
-        if (sideL) ranocha_state<DIM, false>(A, B, nrm, P.gamma, F);
-        else ranocha_state<DIM, false>(B, A, nrm, P.gamma, F);
+    if constexpr (EQ == 1) {
+#pragma unroll
+        for (int k = 0; k < NW; ++k) fs[k] = P.grad[((size_t)es * 2 * DIM + fS) * NW * NF + q + k * NF];
+    }
+    for (int i = t; i < NV * NF; i += nt) {
+        const int v = i / NF, j = i - v * NF;
+        tr[i] = P.u[v * stride + (size_t)eL * NN + face_node<N1, DIM>(d, sideL ? N : 0, j)];
     }
     if constexpr (EQ == 1) {
-        // BR1 viscous sub-face flux, the mean of the small side's Ft and the
-        // large side's interpolated Ft scaled to the small normal (affine:
-        // the large element's Ja^d is 2^(dim-1) times the small one's); the
-        // stored flux is the advective minus the viscous one
-        constexpr int NW = DIM + 1;
-        const double *fs = P.grad + ((size_t)es * 2 * DIM + fS) * NW * NF + q;
-        const double *fl = P.grad + ((size_t)eL * 2 * DIM + fL) * NW * NF;
-        double fi[NW];
+        for (int i = t; i < NW * NF; i += nt) fl[i] = P.grad[((size_t)eL * 2 * DIM + fL) * NW * NF + i];
+    }
+    for (int i = t; i < 100; i += nt) ops[i] = P.mops[i];
+    __syncthreads();
+    if (has) {
+        // interpolate the large trace to small-face node q of sub-face s
+        const int a = s & 1, bsel = s >> 1;
+        const int qa = q % N1, qb = q / N1;
+        double ui[NV], fi[NW];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) ui[v] = 0.0;
 #pragma unroll
         for (int k = 0; k < NW; ++k) fi[k] = 0.0;
+        // (partly rolled: in the work-list kernel this code shares the
+        // right-hand side's register budget)
 #pragma unroll 4
         for (int j = 0; j < NF; ++j) {
             const int ja = j % N1, jb = j / N1;
-            double w = P.mops[a * 25 + qa * N1 + ja];
-            if (DIM == 3) w *= P.mops[bsel * 25 + qb * N1 + jb];
+            double w = ops[a * 25 + qa * N1 + ja];
+            if (DIM == 3) w *= ops[bsel * 25 + qb * N1 + jb];
 #pragma unroll
-            for (int k = 0; k < NW; ++k) fi[k] = fma(w, fl[k * NF + j], fi[k]);
+            for (int v = 0; v < NV; ++v) ui[v] = fma(w, tr[v * NF + j], ui[v]);
+            if constexpr (EQ == 1) {
+#pragma unroll
+                for (int k = 0; k < NW; ++k) fi[k] = fma(w, fl[k * NF + j], fi[k]);
+            }
+        }
+        St<DIM, false> A, B;
+        make_state<DIM, false>(ui, 0.0, P.gamma, P.M, A);
+        make_state<DIM, false>(us, 0.0, P.gamma, P.M, B);
+        double F[NV];
+        if constexpr (SF == 0) {
+            if (sideL) rusanov<DIM, false>(A, B, nrm, F);
+            else rusanov<DIM, false>(B, A, nrm, F);
+        } else if constexpr (SF == 2) {
+            if (sideL) hll<DIM, false>(A, B, nrm, F);
+            else hll<DIM, false>(B, A, nrm, F);
+        } else if constexpr (SF == 3) {
+            if (sideL) hllc<DIM, false>(A, B, nrm, F);
+            else hllc<DIM, false>(B, A, nrm, F);
+        } else {
+            if (sideL) ranocha_state<DIM, false>(A, B, nrm, P.gamma, F);
+            else ranocha_state<DIM, false>(B, A, nrm, P.gamma, F);
+        }
+        if constexpr (EQ == 1) {
+            // BR1 viscous sub-face flux, the mean of the small side's Ft and the
+            // large side's interpolated Ft scaled to the small normal (affine:
+            // the large element's Ja^d is 2^(dim-1) times the small one's); the
+            // stored flux is the advective minus the viscous one
+#pragma unroll
+            for (int k = 0; k < NW; ++k) F[1 + k] -= 0.5 * (fs[k] + fi[k] * (1.0 / NSUB));
         }
 #pragma unroll
-        for (int k = 0; k < NW; ++k) F[1 + k] -= 0.5 * (fs[k * NF] + fi[k] * (1.0 / NSUB));
+        for (int v = 0; v < NV; ++v) {
+            sub[(s * NV + v) * NF + q] = F[v];
+            out[(s * NV + v) * NF + q] = F[v];
+        }
     }
-    double *out = const_cast<double *>(P.mflux) + (size_t)m * NSUB * NV * NF;
+    __syncthreads();
+    for (int i = t; i < NV * NF; i += nt) {
+        const int v = i / NF, ql = i - v * NF;
+        const int qa = ql % N1, qb = ql / N1;
+        double F = 0.0;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) out[(s * NV + v) * NF + q] = F[v];
+        for (int sb = 0; sb < NSUB; ++sb) {
+            const int a = sb & 1, bsel = sb >> 1;
+#pragma unroll 4
+            for (int j = 0; j < NF; ++j) {
+                double w = ops[50 + a * 25 + qa * N1 + j % N1];
+                if (DIM == 3) w *= ops[50 + bsel * 25 + qb * N1 + j / N1];
+                F = fma(w, sub[(sb * NV + v) * NF + j], F);
+            }
+        }
+        out[(NSUB * NV + v) * NF + ql] = F * (double)NSUB;
+    }
 }
-
-
 
 // (the entropy-conservative mixture flux is held to three waves per SIMD, what
 // its LDS allows: 22 registers spill, outside the pair loop; 143 -> 137 us per
@@ -1187,10 +1200,11 @@ struct WorkQ {
 
 template <int DIM, int N, int EQ, int VF, int SF, bool CURV, bool MORT = false, int CHF = 0>
 __global__ void __launch_bounds__(512) k_rhs_queue(RhsParams P, int mode, WorkQ Q) {
+    static_assert(!MORT || MortarShape<DIM, N, EQ>::LDS <= RhsShape<DIM, N, EQ, VF, CURV, CHF>::SLOT, "mortar items in the LDS of an element");
     __shared__ int s_item;
     if (Q.next == nullptr) {
         if constexpr (MORT) {
-            if ((int)blockIdx.x < Q.nmort) mortar_item<DIM, N, SF, EQ>(P, blockIdx.x, threadIdx.x);
+            if ((int)blockIdx.x < Q.nmort) mortar_item<DIM, N, SF, EQ>(P, blockIdx.x);
         }
         return;
     }
@@ -1208,7 +1222,7 @@ __global__ void __launch_bounds__(512) k_rhs_queue(RhsParams P, int mode, WorkQ 
     const int item = s_item < Q.nmort ? s_item : s_item + Q.nfree;  // queue position -> item
     if (item >= Q.nmort + Q.nchunks) return;
     if (MORT && item < Q.nmort) {
-        if constexpr (MORT) mortar_item<DIM, N, SF, EQ>(P, item, threadIdx.x);
+        if constexpr (MORT) mortar_item<DIM, N, SF, EQ>(P, item);
         __syncthreads();
         if (threadIdx.x == 0) {
             __threadfence();  // the sub-face fluxes before the count

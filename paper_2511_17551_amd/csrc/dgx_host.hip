@@ -572,8 +572,9 @@ std::string tune_key(const dgx_ctx *ctx) {
 // workgroup wait for one another three times more in the gradient kernel, or
 // for the large sides' sums over their mortars.  Measured for 1 / 2 / 4 (call
 // of steps, us): Navier-Stokes 8^3 428 / 425 / 459, 32^3 2185 / 2128 / 2149;
-// octrees of 15,282 elements 635 / 634 / 661, of 1,300 136 / 137 / 153; but
-// Euler 29^3 54.8 / 51.4 / 48.9.  Curved Navier-Stokes elements run alone:
+// octree of 61,126 elements 635 / 634 / 661 (624 / 621 / 622 since the mortar
+// pass projects to the large sides, of base 12 168 / 165 / 166); but Euler 29^3
+// 54.8 / 51.4 / 48.9.  Curved Navier-Stokes elements run alone:
 // 24^3 200.7 / 203.7 / 217, 6^3 at N = 4 17.9 / 19.8 / 24.4.
 int default_epb(const dgx_ctx *ctx, int slot) {
     int epb = std::max(1, 256 / ctx->nn);
@@ -583,6 +584,18 @@ int default_epb(const dgx_ctx *ctx, int slot) {
         if (cur_rhs(ctx)->mort) epb = std::min(epb, 2);
     }
     return epb;
+}
+
+// default workgroup numbering: XCD-contiguous (1) while the state fits well
+// inside the 256 MB Infinity Cache, and for the affine Euler equations at any
+// size, else round-robin (0).  Round-robin / contiguous, us: octrees of 149 MB
+// 626 / 588 and 410 MB 1574 / 1533, Kennedy-Gruber Euler of 133 MB 118 / 112
+// and 343 MB 296 / 285; but Navier-Stokes, whose gradient and right-hand side
+// kernels sweep the state in turn, of 113 MB 800 / 762, 156 MB 1044 / 1044 and
+// 270 MB 1792 / 1805.
+int default_order(const dgx_ctx *ctx) {
+    const bool euler = ctx->cfg.equation == DGX_EQ_EULER && ctx->cfg.dim == 3 && !ctx->curved;
+    return euler || (size_t)ctx->nvar * ctx->nelem * ctx->nn * sizeof(double) <= (size_t)128 << 20;
 }
 
 bool epb_fits(const dgx_ctx *ctx, int epb) {
@@ -1017,9 +1030,7 @@ static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m, const std::vector<doub
     // autotuner choice for this configuration wins
     const int epb = default_epb(ctx, sel->slot);
     ctx->epb = epb;
-    // XCD-contiguous numbering by default while the state fits well inside
-    // the 256 MB Infinity Cache
-    ctx->xcd = (size_t)ctx->nvar * E * nn * sizeof(double) <= (size_t)128 << 20;
+    ctx->xcd = default_order(ctx);
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune.find(tune_key(ctx));
@@ -1458,7 +1469,7 @@ int dgx_autotune(dgx_ctx *ctx, const double *u, int reps, int *epb_out, double *
     // than 2%: run-to-run noise is of that order, while the numberings' HBM
     // traffic can differ by much more (the round-robin order re-reads face
     // neighbours from memory when the state fits the Infinity Cache)
-    const int def_xcd = (size_t)ctx->nvar * ctx->nelem * ctx->nn * sizeof(double) <= (size_t)128 << 20;
+    const int def_xcd = default_order(ctx);
     // per launch form and tiling (index xm + 3 tile): the best time and its
     // elements per workgroup
     int best_epb[6] = {saved, saved, saved, saved, saved, saved};

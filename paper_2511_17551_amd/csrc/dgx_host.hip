@@ -739,6 +739,8 @@ static int create_body(const dgx_config *cfg, dgx_ctx **out) {
         for (int s = 0; s < 5; ++s) {
             K.iW[s] = 1.0 / sp.W[s];
             K.th0[s] = sp.e0[s] / ctx->mix.Rs[s];
+            K.Rs[s] = ctx->mix.Rs[s];
+            K.thv[s] = ctx->mix.thv[s];
         }
         group_reactions(K);
     }
@@ -1248,8 +1250,6 @@ int dgx_chem_step(dgx_ctx *ctx, double *u, double dt, double tol, int maxit, dgx
     const int64_t count = (int64_t)ctx->nelem * ctx->nn;
     if (stats && ((rc = dalloc(ctx, ctx->iters, (size_t)count)) || (rc = dalloc(ctx, ctx->subs, (size_t)count))))
         return rc;
-    // temperature of the incoming state: the warm start of the inner solves
-    if ((rc = enqueue_thermo_mesh(ctx, u, s))) return set_err(ctx, rc, "thermo launch failed");
     int *iters = stats ? ctx->iters.p : nullptr;
     const int tb = 256;
     const int blocks = (int)((count + tb - 1) / tb);
@@ -1259,9 +1259,13 @@ int dgx_chem_step(dgx_ctx *ctx, double *u, double dt, double tol, int maxit, dgx
     // the grouped rates where the mechanism has that form (KinGroups) and the
     // molecules are the first three species; else reaction by reaction
     const bool grp = ctx->kin.G.ng > 0 && ctx->mix.std_mol;
+    // temperature of the incoming state: the warm start of the inner solves
+    // (the grouped kernel solves for it)
+    if (!grp && (rc = enqueue_thermo_mesh(ctx, u, s))) return set_err(ctx, rc, "thermo launch failed");
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(tb), 0, s, u, count, dt, ctx->kin_d.p, ctx->mix, ctx->T.p, tol,
-                           maxit, ttol, tmaxit, iters, subs, ctx->flags.p);
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(tb), 0, s, u, count, dt, ctx->kin_d.p, ctx->mix, ctx->T.p,
+                           ctx->cfg.T_guess, ctx->cfg.newton_tol, ctx->cfg.newton_maxit, tol, maxit, ttol, tmaxit,
+                           iters, subs, ctx->flags.p);
     };
     if (ctx->cfg.dim == 2) grp ? launch(k_chem<2, true>) : launch(k_chem<2, false>);
     else grp ? launch(k_chem<3, true>) : launch(k_chem<3, false>);

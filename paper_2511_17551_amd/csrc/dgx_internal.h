@@ -57,6 +57,7 @@ struct KinC {
     double lnpref_Ru;               // ln(p_ref / R_u)
     double iW[kNS];                 // 1 / W_s
     double th0[kNS];                // e0_s / R_s
+    double Rs[kNS], thv[kNS];       // as in MixC
     KinGroups G;
 };
 

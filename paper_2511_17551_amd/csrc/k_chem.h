@@ -34,6 +34,17 @@
 
 namespace dgx {
 
+// The reaction data to be read where it stands: through a pointer that the
+// compiler cannot see through, or it hoists some forty constants out of the
+// Newton and group loops and holds them in lanes of spilled registers (fifty
+// lane reads per group and 69 spilled VGPRs, against scalar loads that hit).
+using KinConst = const __attribute__((address_space(4))) KinC;
+__device__ __forceinline__ KinConst *kin_here(const KinC &K) {
+    uint64_t p = reinterpret_cast<uint64_t>(&K);
+    asm volatile("" : "+s"(p));
+    return (KinConst *)p;
+}
+
 // Species sources w_s (kg m^-3 s^-1) and, with JAC, their Jacobian dw[s][j] =
 // d w_s / d rho_j along the fixed-energy manifold, at the temperature T of
 // the composition rs: the mechanisms of grouped form (KinGroups) with the
@@ -47,15 +58,16 @@ namespace dgx {
 // products once; k_b = k_f / K_c comes from the two reduced exponentials and
 // the sum of their binary exponents, which neither under- nor overflows
 // before the final scaling (near 0 K, where the exponents leave the range of
-// an int, from the exponential of ln k_f - ln K_c); the factors are gathered and their derivatives
-// scattered with one-hot coefficients (exact); and the temperature part of
-// the Jacobian is one outer product at the end.  k_chem on the 64 x 128
+// an int, from the exponential of ln k_f - ln K_c); the factors are gathered
+// and their derivatives scattered with one-hot coefficients (exact); and the
+// temperature part of the Jacobian is one outer product at the end.  k_chem on the 64 x 128
 // cylinder (131,072 nodes, hot state): 184 us reaction by reaction, 78 us
-// grouped, so the grouped form is taken wherever it exists.
+// grouped (74 with the data read in place, the T(e) solve of 6 us included),
+// so the grouped form is taken wherever it exists.
 template <bool JAC>
 __device__ __forceinline__ void chem_sources_grouped(const KinC &K, const MixC &M, const double *rs, double T,
                                                      double *w, double (*dw)[kNS]) {
-    const KinGroups &G = K.G;
+    KinConst *K0 = kin_here(K);
     const double lnT = log(T);
     const double iT = rcp(T);
     double gRT[kNS], dgRT[kNS], conc[kNS], dTdr[kNS], wT[kNS];
@@ -63,12 +75,12 @@ __device__ __forceinline__ void chem_sources_grouped(const KinC &K, const MixC &
 #pragma unroll
     for (int s = 0; s < kNS; ++s) {
         const bool mol = s < 3;
-        const double h = K.th0[s] * iT;            // e0_s / (R_s T)
+        const double h = K0->th0[s] * iT;            // e0_s / (R_s T)
         double ert = (mol ? 2.5 : 1.5) + h;        // e_s / (R_s T)
         double cvr = mol ? 2.5 : 1.5;              // cv_s / R_s
-        double g = K.gconst[s] - (mol ? 3.5 : 2.5) * lnT + h;
+        double g = K0->gconst[s] - (mol ? 3.5 : 2.5) * lnT + h;
         if (mol) {
-            const double x = M.thv[s] * iT;
+            const double x = K0->thv[s] * iT;
             double em, om;  // e^-x, 1 - e^-x
             exp_pair(x, em, om);
             const double io = rcp(om);
@@ -79,9 +91,9 @@ __device__ __forceinline__ void chem_sources_grouped(const KinC &K, const MixC &
         }
         gRT[s] = g;                      // g_s / (R_s T)
         dgRT[s] = -(ert + 1.0) * iT;     // its T-derivative -h_s / (R_s T^2)
-        dTdr[s] = -M.Rs[s] * T * ert;    // -e_s, scaled below
-        rhocv = fma(rs[s] * M.Rs[s], cvr, rhocv);
-        conc[s] = rs[s] * K.iW[s];
+        dTdr[s] = -K0->Rs[s] * T * ert;    // -e_s, scaled below
+        rhocv = fma(rs[s] * K0->Rs[s], cvr, rhocv);
+        conc[s] = rs[s] * K0->iW[s];
         w[s] = 0.0;
         wT[s] = 0.0;
         if (JAC) {
@@ -89,9 +101,11 @@ __device__ __forceinline__ void chem_sources_grouped(const KinC &K, const MixC &
             for (int j = 0; j < kNS; ++j) dw[s][j] = 0.0;
         }
     }
-    const double lnpr = K.lnpref_Ru - lnT;
+    const double lnpr = K0->lnpref_Ru - lnT;
 #pragma unroll 1
-    for (int g = 0; g < G.ng; ++g) {
+    for (int g = 0; g < K0->G.ng; ++g) {
+        KinConst *Kg = kin_here(K);
+        const __attribute__((address_space(4))) KinGroups &G = Kg->G;
         double mlnK = -G.dn_sum[g] * lnpr;  // -ln K_c
         double dlnK = -G.dn_sum[g] * iT;    // d ln K_c / dT
 #pragma unroll
@@ -150,7 +164,7 @@ __device__ __forceinline__ void chem_sources_grouped(const KinC &K, const MixC &
                 double v = fma(G.sel[g][0][j], d0, val[j]);
                 v = fma(G.sel[g][1][j], d1, v);
                 v = fma(G.sel[g][2][j], d2, v);
-                v = fma(G.sel[g][3][j], d3, v) * K.iW[j];  // dR / d rho_j at fixed T
+                v = fma(G.sel[g][3][j], d3, v) * Kg->iW[j];  // dR / d rho_j at fixed T
 #pragma unroll
                 for (int s = 0; s < kNS; ++s) dw[s][j] = fma(G.wdn[g][s], v, dw[s][j]);
             }
@@ -365,15 +379,19 @@ __device__ __forceinline__ bool chem_newton(const KinC &K, const MixC &M, const 
 // registers, and one wave per SIMD leaves the long dependency chains (T
 // solve, rates, elimination) unhidden; the compiler spills about 27 VGPRs at
 // this bound, a better trade (1.45x on the 131,072-node cylinder) than one
-// wave.  T holds the incoming state's temperature
-// on entry (warm start) and the new one on exit; iters (optional) the Newton
+// wave.  T holds the incoming state's temperature on entry and the new one on
+// exit.  GRP: on entry a warm start, from which (or from T0 where it is no
+// positive number or fails) the incoming temperature is solved for here: as
+// k_thermo before this kernel that took 6 of 80 us on the cylinder.  The
+// general rates keep the two launches (the solve's registers cost them more:
+// 394 -> 399 us a Strang step).  iters (optional) the Newton
 // iterations summed over the substeps, -1 if the node did not converge;
 // subs (optional) the number of substeps.
 template <int DIM, bool GRP>
 __global__ void __launch_bounds__(256, 2) k_chem(double *__restrict__ u, int64_t count, double dt, const KinC *kin,
-                                              MixC M, double *__restrict__ T, double tol, int maxit, double ttol,
-                                              int tmaxit, int *__restrict__ iters, int *__restrict__ subs,
-                                              unsigned *flags) {
+                                              MixC M, double *__restrict__ T, double T0, double ntol, int nmaxit,
+                                              double tol, int maxit, double ttol, int tmaxit,
+                                              int *__restrict__ iters, int *__restrict__ subs, unsigned *flags) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= count) return;
     const KinC &K = *kin;
@@ -392,6 +410,18 @@ __global__ void __launch_bounds__(256, 2) k_chem(double *__restrict__ u, int64_t
     }
     const double rhoe = u[(kNS + DIM) * count + i] - 0.5 * m2 / rho;
     double Ta = T[i];
+    if constexpr (GRP) {
+        // (the steps of node_temperature_state)
+        if (!(Ta > 0.0) || !isfinite(Ta)) Ta = T0;
+        bool found = false;
+#pragma unroll 1
+        for (int a = 0; a < 2 && !found; ++a) {
+            if (a) Ta = T0;
+            const int n = mix_newton_t<true>(M, ra, rhoe, Ta, ntol, nmaxit);
+            found = n >= 0 && isfinite(Ta) && Ta > 0.0;
+        }
+        if (!found) atomicOr(flags, FLAG_NOCONV);
+    }
     constexpr int unit = 1 << kChemKmax;
     int pos = 0, lev = 0, it = 0, nsub = 0;
     bool conv = true;

@@ -887,7 +887,7 @@ static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m, const std::vector<doub
         if (e.alt && e.dim == sel->dim && e.N == sel->N && e.eq == sel->eq && e.vf == sel->vf && e.sf == sel->sf &&
             e.curv == sel->curv && e.mort == sel->mort)
             alt = &e;
-    (void)hipDeviceSynchronize();  // the buffers below may stay where they are
+    if (ctx->nbr.p) (void)hipDeviceSynchronize();  // a former mesh's buffers may stay where they are
     clear_graph(ctx);
     ctx->mesh_ok = false;
     ctx->rhs = sel;

@@ -1251,7 +1251,10 @@ int dgx_chem_step(dgx_ctx *ctx, double *u, double dt, double tol, int maxit, dgx
     if (stats && ((rc = dalloc(ctx, ctx->iters, (size_t)count)) || (rc = dalloc(ctx, ctx->subs, (size_t)count))))
         return rc;
     int *iters = stats ? ctx->iters.p : nullptr;
-    const int tb = 256;
+    // one wave per workgroup while every SIMD has at most one: they spread over
+    // all compute units (Strang steps, 256 / 64 threads: 8 x 16 cylinder 157 /
+    // 143 us, 24 x 50 150 / 145, 37 x 77 159 / 155; 64 x 100 189 / 194)
+    const int tb = count <= 64 * 1024 ? 64 : 256;
     const int blocks = (int)((count + tb - 1) / tb);
     const double ttol = 1e-14;
     const int tmaxit = 100;

@@ -4,7 +4,7 @@ Workload (default): the 3D compressible Navier-Stokes Taylor-Green vortex,
 Mach 0.1, Re 1600, Pr 0.72, 32^3 periodic hexahedra, N = 3 (2,097,152 nodes,
 10,485,760 DOF), FP64; entropy-conservative flux differencing, Rusanov
 faces, BR1 viscous terms.  A step is one SSPRK3 step (three right-hand-side
-evaluations fused with the stage updates, replayed from a HIP graph), so
+evaluations fused with the stage updates), so
 
     GDOF-RHS/s = 3 * DOF * steps / seconds / 1e9.
 

@@ -21,7 +21,7 @@
  *            rho_NO, rho_N, rho_O, rho v_1..rho v_dim, rho E).
  *   Memory   the caller owns u, du, T, p (device memory, 8-byte aligned,
  *            contiguous).  The library owns everything it allocates (geometry,
- *            connectivity, stage buffers, graphs, surrogate weights) and frees
+ *            connectivity, stage buffers, surrogate weights) and frees
  *            it in dgx_destroy.
  *   Streams  calls enqueue on the caller's hipStream_t (NULL = legacy default
  *            stream).  Only calls documented as synchronising wait.
@@ -307,8 +307,8 @@ int dgx_set_mesh(dgx_ctx *ctx, const dgx_mesh *mesh);
 int dgx_rhs(dgx_ctx *ctx, const double *u, double t, double *du, void *stream);
 
 /* nsteps steps of SSPRK3 (Shu-Osher form) at constant dt, updating u in place.
- * The three stages are captured once into a HIP graph per u pointer and
- * replayed.  Enqueued on stream. */
+ * Enqueued on stream, kernel by kernel (after a first call, whose stage
+ * buffers are allocated then, a caller may capture it). */
 int dgx_ssprk3_step(dgx_ctx *ctx, double *u, double t, double dt, int nsteps, void *stream);
 
 /* Zhang-Shu positivity-preserving scaling limiter (Sec. Results: species

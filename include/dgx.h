@@ -321,7 +321,8 @@ int dgx_ssprk3_step(dgx_ctx *ctx, double *u, double t, double dt, int nsteps, vo
 int dgx_limit_positivity(dgx_ctx *ctx, double *u, void *stream);
 
 /* Largest stable dt estimate: cfl * 2/(N+1) / max_n sum_d (|v.Ja^d| + c|Ja^d|)/J.
- * Synchronises; result written to *dt_host. */
+ * Synchronises; result written to *dt_host.  DGX_E_NONPHYSICAL where the wave
+ * speed of any node is not finite. */
 int dgx_max_dt(dgx_ctx *ctx, const double *u, double cfl, double *dt_host, void *stream);
 
 /* Per-node temperature from energy (Appendix Eqs. Internal_energy and

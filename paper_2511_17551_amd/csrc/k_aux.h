@@ -805,7 +805,9 @@ __global__ void k_alpha_smooth(const int *__restrict__ nbr, int nelem, const dou
     aout[e] = a;
 }
 
-// max_n sum_d (|v.Ja^d| + c |Ja^d|)/J, as an ordered uint64 of a positive double.
+// max_n sum_d (|v.Ja^d| + c |Ja^d|)/J, as an ordered uint64 of a positive
+// double; +inf where a node's value is no number (fmax would drop a NaN and the
+// caller take a step from the other nodes).
 // Atomics on the one result take about 10 ns each, so the grid is at most
 // kMaxrateBlocks workgroups, each with one (one per wave of nodes: 64 us for
 // 342,528 nodes, now 10).
@@ -832,7 +834,8 @@ __global__ void __launch_bounds__(256) k_maxrate(RhsParams P, unsigned long long
                 n[c] = CURV ? P.geo[(d * DIM + c) * stride + i] : P.geo[(size_t)e * GA + d * DIM + c];
             rate += fabs(dotn<DIM>(s.v, n)) + s.c * wave_sqrt(dotn<DIM>(n, n));
         }
-        best = fmax(best, rate / fabs(J));
+        rate /= fabs(J);
+        best = fmax(best, rate >= 0.0 ? rate : (double)INFINITY);
     }
     for (int off = 32; off > 0; off >>= 1) best = fmax(best, __shfl_xor(best, off));
     __shared__ double wave[4];

@@ -169,29 +169,32 @@ __device__ __forceinline__ double inv_ln_mean(double x, double y) {
 // conservative one): a single polynomial range, so that the usual pair takes
 // no branch, and for ratios above 2 the logarithm from the quotient of the
 // mantissas, ln(y/x) = k ln 2 + 2 f A(f^2) with f = (my - mx)/(my + mx),
-// |f| <= 1/3: the same polynomial, without a library logarithm.
+// |f| <= 1/3: the same polynomial, without a library logarithm.  Both of them
+// may be negative (the ratio counts); of opposite sign, where |f| > 1, there is
+// no logarithm and the result is no number.
 __device__ __forceinline__ double ln_ratio_far(double x, double y) {
     const double mx = __builtin_amdgcn_frexp_mant(x), my = __builtin_amdgcn_frexp_mant(y);
     const int k = __builtin_amdgcn_frexp_exp(y) - __builtin_amdgcn_frexp_exp(x);
     const double q = (my - mx) * rcp(my + mx);
-    return fma((double)k, 0.69314718055994529, q * atanh_ratio_x2(q * q));
+    const double l = fma((double)k, 0.69314718055994529, q * atanh_ratio_x2(q * q));
+    return fabs(q) < 1.0 ? l : (double)NAN;
 }
 
-// ln mean of densities (>= 0; 0 where one of them is 0, the limit)
+// ln mean of densities (0 where one of them is 0, the limit)
 __device__ __forceinline__ double ln_mean_wide(double x, double y) {
     const double s = x + y, d = y - x;
-    const double q = d * rcp(fmax(s, 1e-300));
+    const double q = d * rcp(fmax(fabs(s), 1e-300));  // up to its sign
     double m = 0.5 * s * inv_atanh_ratio(q * q);
-    if (3.0 * fabs(d) > s) m = (x == 0.0 || y == 0.0) ? 0.0 : d * rcp(ln_ratio_far(x, y));
+    if (3.0 * fabs(d) > fabs(s)) m = (x == 0.0 || y == 0.0) ? 0.0 : d * rcp(ln_ratio_far(x, y));
     return m;
 }
 
-// reciprocal of the ln mean of positive numbers
+// reciprocal of the ln mean of numbers other than 0
 __device__ __forceinline__ double inv_ln_mean_wide(double x, double y) {
     const double s = x + y, d = y - x, rs = rcp(s);
     const double q = d * rs;
     double m = atanh_ratio_x2(q * q) * rs;
-    if (3.0 * fabs(d) > s) m = ln_ratio_far(x, y) * rcp(d);
+    if (3.0 * fabs(d) > fabs(s)) m = ln_ratio_far(x, y) * rcp(d);
     return m;
 }
 

@@ -653,7 +653,7 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     // exponentials, evaluated once per node, replace rho E and c (read no more)
     // and follow the pair fluxes
     static_assert(!S::ECM || kEcMol == 3, "LDS places of the node exponentials");
-    [[maybe_unused]] const int off_e1 = PDC * NVP;  // E[1], E[2] in the buffer
+    [[maybe_unused]] const int off_e1 = PDC * NVP;  // D[1], D[2] in the buffer
     EcNode<DIM> own_ec;
     if constexpr (S::ECM) {
         if (valid) {
@@ -662,9 +662,9 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
             for (int c = 0; c < DIM; ++c) v[c] = sq[(1 + c) * NN + node];
             ec_node<DIM>(ku, v, T_own, P.M, own_ec);
             sq[(2 + DIM) * NN + node] = own_ec.beta;
-            sq[(3 + DIM) * NN + node] = own_ec.E[0];
-            buf[off_e1 + node] = own_ec.E[1];
-            buf[off_e1 + NN + node] = own_ec.E[2];
+            sq[(3 + DIM) * NN + node] = own_ec.D[0];
+            buf[off_e1 + node] = own_ec.D[1];
+            buf[off_e1 + NN + node] = own_ec.D[2];
         }
         __syncthreads();
     }
@@ -762,9 +762,9 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
                     for (int c = 0; c < DIM; ++c) B.v[c] = sq[(1 + c) * NN + nb];
                     B.beta = sq[(2 + DIM) * NN + nb];
                     B.rR = sq[(1 + DIM) * NN + nb] * B.beta;  // p / T
-                    B.E[0] = sq[(3 + DIM) * NN + nb];
-                    B.E[1] = buf[off_e1 + nb];
-                    B.E[2] = buf[off_e1 + NN + nb];
+                    B.D[0] = sq[(3 + DIM) * NN + nb];
+                    B.D[1] = buf[off_e1 + nb];
+                    B.D[2] = buf[off_e1 + NN + nb];
                     ec_mixture_pair<DIM>(own_ec, B, nbar, P.M, F);
                     const double coef = hi * sDc[a * N1 + cb];
 #pragma unroll

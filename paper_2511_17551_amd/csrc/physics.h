@@ -599,18 +599,26 @@ __device__ __forceinline__ void split_form_state(const St<DIM, MIX> &L, const St
 
 // What the entropy-conservative mixture flux takes of a node: beta = 1/T, the
 // gas constant density sum_s rho_s R_s and, per molecule among the first
-// three species, E = exp(-theta beta / 2) (a molecule elsewhere in the species
-// table takes its exponentials in the flux).
+// three species, D = exp(-theta beta / 2) - 1 (a molecule elsewhere in the
+// species table takes its exponentials in the flux).  D and not the exponential
+// itself: 1 - exp(-theta beta) = -D (2 + D) keeps its digits in hot gas, where
+// the square of the rounded exponential subtracted from 1 loses them (relative
+// error of the energy mean, rms, at 20,000 K 1.1e-16 against 1.4e-16, at 1e6 K
+// against 4e-15), and in cold gas, where only 1 + D is rounded at the size of 1,
+// the vibrational part is as small (1.2e-16 from 100 K on).  It costs two
+// instructions per molecule and node: the curved 16^3 right-hand side takes 135.7
+// us, with the exponentials 134.5.
 constexpr int kEcMol = 3;
 template <int DIM>
 struct EcNode {
-    double rs[kNS], v[DIM], rR, beta, E[kEcMol];
+    double rs[kNS], v[DIM], rR, beta, D[kEcMol];
 };
 
-__device__ __forceinline__ double exp_neg_half(double th, double beta) {
+__device__ __forceinline__ double expm1_neg_half(double th, double beta) {
     int n;
     const double p = expm1_reduced(-0.5 * th * beta, n);
-    return ldexp(1.0 + p, n);
+    const double s = ldexp(1.0, n);
+    return fma(s, p, s - 1.0);
 }
 
 template <int DIM>
@@ -622,12 +630,13 @@ __device__ __forceinline__ void ec_node(const double *rs, const double *v, doubl
     e.rR = mix_rR(M, rs);
     e.beta = rcp(T);
 #pragma unroll
-    for (int k = 0; k < kEcMol; ++k) e.E[k] = exp_neg_half(M.thv[k], e.beta);
+    for (int k = 0; k < kEcMol; ++k) e.D[k] = expm1_neg_half(M.thv[k], e.beta);
 }
 
-// exp(-theta bbar) sinh(z)/z, z = theta (bR - bL)/2, from the two E: the
-// series of sinh(z)/z to z^18 (remainder < 3e-20) for |z| < 1, else the
-// difference of the squares (a ratio above e^2, no cancellation).
+// exp(-theta bbar) sinh(z)/z, z = theta (bR - bL)/2, from the two exponentials
+// exp(-theta beta / 2): the series of sinh(z)/z to z^18 (remainder < 3e-20) for
+// |z| < 1, else the difference of the squares (a ratio above e^2, no
+// cancellation).
 __device__ __forceinline__ double exp_sinhc(double th, double db, double EL, double ER) {
     const double z = 0.5 * th * db, y = z * z;
     double r = poly_start(y, 1.0 / 121645100408832000.0, 1.0 / 355687428096000.0);
@@ -678,9 +687,9 @@ __device__ __forceinline__ void ec_mixture_pair(const EcNode<DIM> &L, const EcNo
         double eh = M.e0[k];
         if (M.mol[k]) {
             const double th = M.thv[k];
-            const double EL = k < kEcMol ? L.E[k < kEcMol ? k : 0] : exp_neg_half(th, L.beta);
-            const double ER = k < kEcMol ? R.E[k < kEcMol ? k : 0] : exp_neg_half(th, R.beta);
-            const double t = exp_sinhc(th, db, EL, ER) * inv_ln_mean_wide(fma(-EL, EL, 1.0), fma(-ER, ER, 1.0));
+            const double DL = k < kEcMol ? L.D[k < kEcMol ? k : 0] : expm1_neg_half(th, L.beta);
+            const double DR = k < kEcMol ? R.D[k < kEcMol ? k : 0] : expm1_neg_half(th, R.beta);
+            const double t = exp_sinhc(th, db, 1.0 + DL, 1.0 + DR) * inv_ln_mean_wide(-DL * (2.0 + DL), -DR * (2.0 + DR));
             eh = fma(M.Rs[k], fma(th, t, 2.5 * iblog), eh);
         } else {
             eh = fma(M.Rs[k], 1.5 * iblog, eh);

@@ -6,6 +6,9 @@
 //
 //   means   n, then n lines "x y": ln_mean, inv_ln_mean, ln_mean_wide,
 //           inv_ln_mean_wide
+//   ec      n, then n lines "theta R TL TR": the energy row of the entropy-
+//           conservative mixture flux of a gas of one molecule, density 1,
+//           formation energy 0, at unit velocity through a unit face
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
@@ -58,6 +61,23 @@ int main() {
         for (int i = 0; i < n; ++i) {
             const double x = number(), y = number();
             std::printf("%a %a %a %a\n", ln_mean(x, y), inv_ln_mean(x, y), ln_mean_wide(x, y), inv_ln_mean_wide(x, y));
+        }
+        return 0;
+    }
+    if (cmd == "ec") {
+        for (int i = 0; i < n; ++i) {
+            MixC M{};
+            M.thv[0] = number();
+            M.Rs[0] = number();
+            M.mol[0] = 1;
+            const double TL = number(), TR = number();
+            const double rs[kNS] = {1.0}, v[3] = {1.0, 0.0, 0.0};
+            EcNode<3> A, B;
+            ec_node<3>(rs, v, TL, M, A);
+            ec_node<3>(rs, v, TR, M, B);
+            double F[kNS + 4];
+            ec_mixture_pair<3>(A, B, v, M, F);
+            std::printf("%a\n", F[kNS + 3]);
         }
         return 0;
     }

@@ -5,6 +5,8 @@ stands, with the contraction rules of the HIP build.
 * Logarithmic means against extended precision over ratios from 1 to 1e12, and
   at their edges: two equal values give that value, also negative ones, a zero
   gives zero (the mean) and values of opposite sign give no number.
+* The energy row of the entropy-conservative mixture flux of a molecule against
+  extended precision from 100 K to 1e6 K (where 1 - exp(-theta/T) is 3e-3).
 """
 import os
 import re
@@ -75,3 +77,26 @@ def test_log_mean_edges(driver):
     assert np.all(got[:, 2] == 0.0), got
     got = run(driver, "means", [(1.0, -1.0), (-1e-9, 1.0), (1.0, -1e-9), (2.0, -1.0), (-1e-3, 0.7)])
     assert np.all(np.isnan(got[:, 2:])), got
+
+
+def ec_energy(theta, R, TL, TR):
+    theta, R, TL, TR = (np.longdouble(v) for v in (theta, R, TL, TR))
+    bL, bR = 1 / TL, 1 / TR
+    z = theta * (bR - bL) / 2
+    sinhc = np.where(np.abs(z) < 1e-4, 1 + z * z / 6, np.sinh(z) / np.where(z == 0, 1, z))
+    t = np.exp(-theta * (bL + bR) / 2) * sinhc / ln_mean(-np.expm1(-theta * bL), -np.expm1(-theta * bR))
+    return R * (theta * t + 2.5 / ln_mean(bL, bR)) + 0.5 + 2 * R / (bL + bR)
+
+
+@pytest.mark.parametrize("T", [100.0, 300.0, 1500.0, 6000.0, 2e4, 1e5, 1e6])
+def test_ec_energy_mean(driver, T):
+    rng = np.random.default_rng(4)
+    rows = np.stack([rng.uniform(2200.0, 3400.0, 1000), np.full(1000, 297.0), T * np.exp(rng.uniform(-0.3, 0.3, 1000)),
+                     T * np.exp(rng.uniform(-0.3, 0.3, 1000))], 1)
+    got = run(driver, "ec", rows)[:, 0]
+    ref = np.array([ec_energy(*r) for r in rows])
+    err = float((np.abs(got - ref) / ref).max())
+    print("T %g: %.2f eps" % (T, err / EPS))
+    # two exponentials, their series, three means, three products and sums,
+    # each within one unit of its last digit, and half a unit of beta = 1/T
+    assert err < 10 * EPS

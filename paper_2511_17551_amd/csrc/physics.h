@@ -576,9 +576,9 @@ __device__ __forceinline__ void split_form_state(const St<DIM, MIX> &L, const St
     if constexpr (MIX) {
         const double iL = rcp(L.rho), iR = rcp(R.rho);
 #pragma unroll
-        for (int k = 0; k < kNS; ++k) F[k] = fm * (0.5 * (L.rs[k] * iL + R.rs[k] * iR));
-        if constexpr (FORM == 1) xm = 0.5 * ((L.rhoE + L.p) * iL + (R.rhoE + R.p) * iR);
-        else xm = 0.5 * (L.rhoE * iL + R.rhoE * iR);
+        for (int k = 0; k < kNS; ++k) F[k] = fm * (0.5 * sum2(L.rs[k] * iL, R.rs[k] * iR));
+        if constexpr (FORM == 1) xm = 0.5 * sum2((L.rhoE + L.p) * iL, (R.rhoE + R.p) * iR);
+        else xm = 0.5 * sum2(L.rhoE * iL, R.rhoE * iR);
     } else {
         F[0] = fm;
         xm = 0.5 * (L.rs[0] + R.rs[0]);

@@ -9,12 +9,17 @@
 //   ec      n, then n lines "theta R TL TR": the energy row of the entropy-
 //           conservative mixture flux of a gas of one molecule, density 1,
 //           formation energy 0, at unit velocity through a unit face
+//   swap    n: the two-point fluxes of n random pairs of states, the pair taken
+//           both ways; prints per flux how many differ in some bit: perfect gas
+//           Ranocha, Ducros, Kennedy-Gruber, Pirozzoli, central, Morinishi,
+//           then the mixture's Ducros, Kennedy-Gruber, Pirozzoli, central
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <iostream>
+#include <random>
 #include <string>
 
 using std::max;
@@ -53,6 +58,46 @@ static double number() {
     return std::strtod(s.c_str(), nullptr);
 }
 
+// (not inlined: the two orders must not share their products)
+template <bool MIX, int VF>
+__attribute__((noinline)) static void pair_flux(const St<3, MIX> &A, const St<3, MIX> &B, const double *n, double *F) {
+    const double gm1_inv = 1.0 / 0.4;
+    if constexpr (VF == 0) ranocha_prims<3>(A.rho, A.v, A.p, A.rs[0], B.rho, B.v, B.p, B.rs[0], n, gm1_inv, F);
+    else if constexpr (VF == 1) ducros_state<3, MIX>(A, B, n, F);
+    else if constexpr (VF == 4) central_state<3, MIX>(A, B, n, F);
+    else split_form_state<3, MIX, VF == 2 ? 0 : VF == 3 ? 1 : 2>(A, B, n, gm1_inv, F);
+}
+
+template <bool MIX, int VF>
+static int unequal_swaps(int n) {
+    std::mt19937_64 rng(6);
+    std::uniform_real_distribution<double> U(-1.0, 1.0);
+    constexpr int NV = (MIX ? kNS : 1) + 4;
+    int bad = 0;
+    for (int i = 0; i < n; ++i) {
+        St<3, MIX> s[2];
+        for (auto &x : s) {
+            x.rho = 0.0;
+            if constexpr (MIX) {
+                for (double &r : x.rs) x.rho += r = 1.1 + U(rng);
+            } else {
+                x.rho = 1.1 + U(rng);
+            }
+            for (double &v : x.v) v = U(rng);
+            x.p = 1.1 + U(rng);
+            x.rhoE = 4.0 + U(rng);
+            x.c = 1.0;
+            if constexpr (!MIX && VF != 1 && VF != 4) x.rs[0] = pair_quantity<3, VF>(x.rho, x.p, x.rhoE);
+        }
+        const double nrm[3] = {U(rng), U(rng), U(rng)};
+        double F[NV], G[NV];
+        pair_flux<MIX, VF>(s[0], s[1], nrm, F);
+        pair_flux<MIX, VF>(s[1], s[0], nrm, G);
+        bad += std::memcmp(F, G, sizeof(F)) != 0;
+    }
+    return bad;
+}
+
 int main() {
     std::string cmd;
     int n;
@@ -79,6 +124,14 @@ int main() {
             ec_mixture_pair<3>(A, B, v, M, F);
             std::printf("%a\n", F[kNS + 3]);
         }
+        return 0;
+    }
+    if (cmd == "swap") {
+        for (int bad : {unequal_swaps<false, 0>(n), unequal_swaps<false, 1>(n), unequal_swaps<false, 2>(n),
+                        unequal_swaps<false, 3>(n), unequal_swaps<false, 4>(n), unequal_swaps<false, 5>(n),
+                        unequal_swaps<true, 1>(n), unequal_swaps<true, 2>(n), unequal_swaps<true, 3>(n),
+                        unequal_swaps<true, 4>(n)})
+            std::printf("%d\n", bad);
         return 0;
     }
     return 1;

@@ -7,6 +7,8 @@ stands, with the contraction rules of the HIP build.
   gives zero (the mean) and values of opposite sign give no number.
 * The energy row of the entropy-conservative mixture flux of a molecule against
   extended precision from 100 K to 1e6 K (where 1 - exp(-theta/T) is 3e-3).
+* The other two-point fluxes are bitwise the same for a pair taken either way
+  (at N = 3 both nodes evaluate a pair, each with its own state first).
 """
 import os
 import re
@@ -100,3 +102,9 @@ def test_ec_energy_mean(driver, T):
     # two exponentials, their series, three means, three products and sums,
     # each within one unit of its last digit, and half a unit of beta = 1/T
     assert err < 10 * EPS
+
+
+def test_two_point_fluxes_are_symmetric(driver):
+    out = subprocess.run([driver], input="swap 2000\n", capture_output=True, text=True, check=True).stdout.split()
+    print("pairs of 2000 whose flux depends on their order:", out)
+    assert out == ["0"] * 10

@@ -560,13 +560,18 @@ std::string tune_key(const dgx_ctx *ctx) {
 // of steps, us): Navier-Stokes 8^3 428 / 425 / 459, 32^3 2185 / 2128 / 2149;
 // octree of 61,126 elements 635 / 634 / 661 (624 / 621 / 622 since the mortar
 // pass projects to the large sides, of base 12 168 / 165 / 166); but Euler 29^3
-// 54.8 / 51.4 / 48.9.  Curved Navier-Stokes elements run alone:
-// 24^3 200.7 / 203.7 / 217, 6^3 at N = 4 17.9 / 19.8 / 24.4.
+// 54.8 / 51.4 / 48.9.  Curved Navier-Stokes elements run alone at N = 4 (four
+// SSPRK3 steps, us: 6^3 219 / 243 / 313, 10^3 295 / 307 / 321, 24^3 2504 / 2540 /
+// 2797) and at N = 3 while one wave per SIMD holds them all (8^3 197 / 198 / 208,
+// 10^3 211 / 230 / 212; beyond, 11^3 248 / 242 / 258, 12^3 261 / 259 / 264, 18^3
+// 547 / 542 / 545, 24^3 1089 / 1067 / 1093, 32^3 2865 / 2836 / 2925, though 14^3
+// 330 / 353 / 328).
 int default_epb(const dgx_ctx *ctx, int slot) {
     int epb = std::max(1, 256 / ctx->nn);
     while (epb > 1 && (size_t)epb * slot * sizeof(double) > 32 * 1024) epb >>= 1;
     if (ctx->cfg.dim == 3) {
-        if (ctx->cfg.equation == DGX_EQ_NS) epb = std::min(epb, ctx->curved ? 1 : 2);
+        const bool alone = ctx->curved && (ctx->cfg.N == 4 || ctx->nelem <= 1024);
+        if (ctx->cfg.equation == DGX_EQ_NS) epb = std::min(epb, alone ? 1 : 2);
         if (cur_rhs(ctx)->mort) epb = std::min(epb, 2);
     }
     return epb;

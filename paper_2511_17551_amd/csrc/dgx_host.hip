@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "../../include/dgx.h"
+#include "host_buffers.h"
 #include "host_geometry.h"
 #include "host_parallel.h"
 #include "host_octree.h"
@@ -159,18 +160,6 @@ const IndEntry kInd[] = {
     {2, 4, 0, &ind_launch<2, 4, false>}, {2, 4, 1, &ind_launch<2, 4, true>},
 };
 
-template <typename T>
-struct DevBuf {
-    T *p = nullptr;
-    size_t n = 0;    // elements in use
-    size_t cap = 0;  // elements allocated
-    void release() {
-        if (p) (void)hipFree(p);
-        p = nullptr;
-        n = cap = 0;
-    }
-};
-
 }  // namespace
 
 struct dgx_ctx {
@@ -257,42 +246,37 @@ int guarded(dgx_ctx *ctx, F &&f) {
 
 template <typename T>
 int dalloc(dgx_ctx *ctx, DevBuf<T> &b, size_t n) {
-    if (b.n == n && b.cap == n && b.p) return DGX_OK;
-    b.release();
-    if (n == 0) return DGX_OK;
-    if (hipMalloc(&b.p, n * sizeof(T)) != hipSuccess) {
-        b.p = nullptr;
-        return set_err(ctx, DGX_E_NOMEM, "hipMalloc failed");
-    }
-    b.n = b.cap = n;
-    return DGX_OK;
+    return buf_exact(b, n) ? DGX_OK : set_err(ctx, DGX_E_NOMEM, "hipMalloc failed");
 }
-// The same for the buffers that follow the mesh's size, whose users a mesh
-// change waits for: one that is large enough stays while it is at most
-// kMeshSlack larger than needed, and one that has to grow takes an eighth
-// more, up to kMeshSlack.  (An adaptation cycle changes some twenty of them
-// by a few percent; a free and an allocation take 60 us and more.)
-constexpr size_t kMeshSlack = (size_t)32 << 20;
 template <typename T>
 int dalloc_mesh(dgx_ctx *ctx, DevBuf<T> &b, size_t n) {
-    const size_t slack = kMeshSlack / sizeof(T);
-    if (b.p && n > 0 && b.cap >= n && b.cap - n <= slack) {
-        b.n = n;
-        return DGX_OK;
+    return buf_mesh(b, n) ? DGX_OK : set_err(ctx, DGX_E_NOMEM, "hipMalloc failed");
+}
+
+// f on every buffer that follows the mesh's size
+template <typename F>
+void each_mesh_buffer(dgx_ctx *ctx, F f) {
+    for (auto *b : {&ctx->geo, &ctx->Jn, &ctx->nsub, &ctx->bc_state, &ctx->bc_T, &ctx->T, &ctx->csnd, &ctx->alpha,
+                    &ctx->alpha_tmp, &ctx->alpha_raw, &ctx->grad, &ctx->vpart, &ctx->u1, &ctx->u2, &ctx->mops,
+                    &ctx->mflux, &ctx->mgw})
+        f(*b);
+    for (auto *b : {&ctx->nbr, &ctx->bc_kind, &ctx->mort, &ctx->wq_ctr, &ctx->amr_tab}) f(*b);
+    for (int k = 0; k < 4; ++k) {
+        f(ctx->wq_order[k]);
+        f(ctx->wq_waits[k]);
     }
-    const bool grows = b.p && n > b.cap;
-    b.release();
-    if (grows) {
-        const size_t cap = n + std::min(n / 8, slack);
-        if (hipMalloc(&b.p, cap * sizeof(T)) == hipSuccess) {
-            b.n = n;
-            b.cap = cap;
-            return DGX_OK;
-        }
-        (void)hipGetLastError();
-        b.p = nullptr;
-    }
-    return dalloc(ctx, b, n);
+}
+
+// the stage buffers u1 and u2; where memory is short, without anyone's slack
+int stage_buffers(dgx_ctx *ctx) {
+    const size_t n = (size_t)ctx->nvar * ctx->nelem * ctx->nn;
+    if (buf_mesh(ctx->u1, n) && buf_mesh(ctx->u2, n)) return DGX_OK;
+    (void)hipDeviceSynchronize();
+    ctx->u1.release();
+    ctx->u2.release();
+    each_mesh_buffer(ctx, [](auto &b) { buf_trim(b); });
+    const int rc = dalloc(ctx, ctx->u1, n);
+    return rc ? rc : dalloc(ctx, ctx->u2, n);
 }
 
 int threads_for(int nn, int epb) { return ((nn * epb + 63) / 64) * 64; }
@@ -778,7 +762,7 @@ static const RhsEntry *find_rhs(const dgx_ctx *ctx, bool curved, bool mortars) {
 
 // affine_geo: metric terms and J per element of a mesh known to be affine
 // for which there is an affine variant (then m->x is not read), or null
-static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m, const std::vector<double> *affine_geo = nullptr) {
+static int set_mesh_once(dgx_ctx *ctx, const dgx_mesh *m, const std::vector<double> *affine_geo) {
     if (!ctx || !m || (!m->x && !affine_geo) || m->nelem <= 0) return set_err(ctx, DGX_E_INVAL, "bad mesh");
     const int dim = ctx->cfg.dim, N = ctx->cfg.N, n1 = ctx->N1, nn = ctx->nn, E = m->nelem;
     const int nv = ctx->nvar;
@@ -1046,6 +1030,15 @@ static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m, const std::vector<doub
     return DGX_OK;
 }
 
+// (out of device memory: once more with every buffer of its exact size, the
+// former mesh's buffers given back first)
+static int set_mesh_body(dgx_ctx *ctx, const dgx_mesh *m, const std::vector<double> *affine_geo = nullptr) {
+    const int rc = set_mesh_once(ctx, m, affine_geo);
+    if (rc != DGX_E_NOMEM || ctx->mesh_ok) return rc;
+    each_mesh_buffer(ctx, [](auto &b) { b.release(); });
+    return set_mesh_once(ctx, m, affine_geo);
+}
+
 int dgx_set_mesh(dgx_ctx *ctx, const dgx_mesh *m) {
     return guarded(ctx, [&] { return set_mesh_body(ctx, m); });
 }
@@ -1064,9 +1057,7 @@ int dgx_ssprk3_step(dgx_ctx *ctx, double *u, double t, double dt, int nsteps, vo
     (void)t;
     if (!u || nsteps < 0 || !(dt > 0.0) || !std::isfinite(dt)) return set_err(ctx, DGX_E_INVAL, "bad ssprk3 arguments");
     if (nsteps == 0) return DGX_OK;
-    const size_t n = (size_t)ctx->nvar * ctx->nelem * ctx->nn;
-    if ((rc = dalloc_mesh(ctx, ctx->u1, n))) return rc;
-    if ((rc = dalloc_mesh(ctx, ctx->u2, n))) return rc;
+    if ((rc = stage_buffers(ctx))) return rc;
     hipStream_t s = (hipStream_t)stream;
     const bool lim = ctx->cfg.positivity != 0;
     // (launched one by one: replays of a captured step took 22.8 us against
@@ -1361,8 +1352,7 @@ int dgx_kernel_times(dgx_ctx *ctx, const double *u, int reps, double *ms_out, in
     if (rc) return rc;
     if (!u || reps < 1 || !ms_out || !nk) return set_err(ctx, DGX_E_INVAL, "bad kernel_times arguments");
     const size_t n = (size_t)ctx->nvar * ctx->nelem * ctx->nn;
-    if ((rc = dalloc_mesh(ctx, ctx->u1, n))) return rc;
-    if ((rc = dalloc_mesh(ctx, ctx->u2, n))) return rc;
+    if ((rc = stage_buffers(ctx))) return rc;
     hipStream_t s = (hipStream_t)stream;
     // a second SSPRK3 stage as in a step: u0 is its own buffer (a copy of u),
     // so its reads cost what they cost in the time loop
@@ -1430,8 +1420,7 @@ int dgx_autotune(dgx_ctx *ctx, const double *u, int reps, int *epb_out, double *
     if (rc) return rc;
     if (!u || reps < 1) return set_err(ctx, DGX_E_INVAL, "bad autotune arguments");
     const size_t n = (size_t)ctx->nvar * ctx->nelem * ctx->nn;
-    if ((rc = dalloc_mesh(ctx, ctx->u1, n))) return rc;
-    if ((rc = dalloc_mesh(ctx, ctx->u2, n))) return rc;
+    if ((rc = stage_buffers(ctx))) return rc;
     hipStream_t s = (hipStream_t)stream;
     // what is timed: one SSPRK3 step as dgx_ssprk3_step runs it (three fused
     // stages with u0 in its own buffer, the limiter when configured), into
@@ -1882,22 +1871,8 @@ const char *dgx_last_error(const dgx_ctx *ctx) {
 void dgx_destroy(dgx_ctx *ctx) {
     if (!ctx) return;
     (void)hipDeviceSynchronize();
-    DevBuf<double> *bufs[] = {&ctx->geo,   &ctx->Jn,        &ctx->nsub,      &ctx->bc_state, &ctx->bc_T, &ctx->T, &ctx->csnd,
-                              &ctx->alpha, &ctx->alpha_tmp, &ctx->alpha_raw, &ctx->grad,     &ctx->u1,   &ctx->u2,
-                              &ctx->dtbuf, &ctx->vpart};
-    for (auto *b : bufs) b->release();
-    ctx->nbr.release();
-    ctx->mops.release();
-    ctx->wq_ctr.release();
-    for (int k = 0; k < 4; ++k) {
-        ctx->wq_order[k].release();
-        ctx->wq_waits[k].release();
-    }
-    ctx->bc_kind.release();
-    ctx->mort.release();
-    ctx->mflux.release();
-    ctx->mgw.release();
-    ctx->amr_tab.release();
+    each_mesh_buffer(ctx, [](auto &b) { b.release(); });
+    ctx->dtbuf.release();
     ctx->amr_ops.release();
     ctx->amr_eq.release();
     ctx->iters.release();

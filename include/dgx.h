@@ -307,8 +307,12 @@ int dgx_set_mesh(dgx_ctx *ctx, const dgx_mesh *mesh);
 int dgx_rhs(dgx_ctx *ctx, const double *u, double t, double *du, void *stream);
 
 /* nsteps steps of SSPRK3 (Shu-Osher form) at constant dt, updating u in place.
- * Enqueued on stream, kernel by kernel (after a first call, whose stage
- * buffers are allocated then, a caller may capture it). */
+ * Enqueued on stream, kernel by kernel.  A caller may capture it once a step
+ * has been taken on the mesh: the first one may have to allocate the stage
+ * buffers, and then returns DGX_E_STATE on a stream being captured.  A
+ * captured step holds the context's buffers, mesh and launch shape:
+ * dgx_set_mesh, dgx_set_octree, dgx_amr_apply, dgx_set_launch, dgx_autotune and
+ * dgx_destroy end its use. */
 int dgx_ssprk3_step(dgx_ctx *ctx, double *u, double t, double dt, int nsteps, void *stream);
 
 /* Zhang-Shu positivity-preserving scaling limiter (Sec. Results: species

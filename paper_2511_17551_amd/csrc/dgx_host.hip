@@ -267,9 +267,16 @@ void each_mesh_buffer(dgx_ctx *ctx, F f) {
     }
 }
 
-// the stage buffers u1 and u2; where memory is short, without anyone's slack
-int stage_buffers(dgx_ctx *ctx) {
+// the stage buffers u1 and u2; where memory is short, without anyone's slack.
+// A stream that is being captured is refused when they have to be allocated.
+int stage_buffers(dgx_ctx *ctx, hipStream_t s) {
     const size_t n = (size_t)ctx->nvar * ctx->nelem * ctx->nn;
+    if (!buf_keeps(ctx->u1, n) || !buf_keeps(ctx->u2, n)) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+        else if (st != hipStreamCaptureStatusNone)
+            return set_err(ctx, DGX_E_STATE, "a step that has to allocate its stage buffers cannot be captured: take one before");
+    }
     if (buf_mesh(ctx->u1, n) && buf_mesh(ctx->u2, n)) return DGX_OK;
     (void)hipDeviceSynchronize();
     ctx->u1.release();
@@ -1057,8 +1064,8 @@ int dgx_ssprk3_step(dgx_ctx *ctx, double *u, double t, double dt, int nsteps, vo
     (void)t;
     if (!u || nsteps < 0 || !(dt > 0.0) || !std::isfinite(dt)) return set_err(ctx, DGX_E_INVAL, "bad ssprk3 arguments");
     if (nsteps == 0) return DGX_OK;
-    if ((rc = stage_buffers(ctx))) return rc;
     hipStream_t s = (hipStream_t)stream;
+    if ((rc = stage_buffers(ctx, s))) return rc;
     const bool lim = ctx->cfg.positivity != 0;
     // (launched one by one: replays of a captured step took 22.8 us against
     // 19.8 on the 16 x 16 vortex, three kernels, and 414 against 402 for ten
@@ -1352,8 +1359,8 @@ int dgx_kernel_times(dgx_ctx *ctx, const double *u, int reps, double *ms_out, in
     if (rc) return rc;
     if (!u || reps < 1 || !ms_out || !nk) return set_err(ctx, DGX_E_INVAL, "bad kernel_times arguments");
     const size_t n = (size_t)ctx->nvar * ctx->nelem * ctx->nn;
-    if ((rc = stage_buffers(ctx))) return rc;
     hipStream_t s = (hipStream_t)stream;
+    if ((rc = stage_buffers(ctx, s))) return rc;
     // a second SSPRK3 stage as in a step: u0 is its own buffer (a copy of u),
     // so its reads cost what they cost in the time loop
     HIPCHK(hipMemcpyAsync(ctx->u1.p, u, n * sizeof(double), hipMemcpyDeviceToDevice, s));
@@ -1420,8 +1427,8 @@ int dgx_autotune(dgx_ctx *ctx, const double *u, int reps, int *epb_out, double *
     if (rc) return rc;
     if (!u || reps < 1) return set_err(ctx, DGX_E_INVAL, "bad autotune arguments");
     const size_t n = (size_t)ctx->nvar * ctx->nelem * ctx->nn;
-    if ((rc = stage_buffers(ctx))) return rc;
     hipStream_t s = (hipStream_t)stream;
+    if ((rc = stage_buffers(ctx, s))) return rc;
     // what is timed: one SSPRK3 step as dgx_ssprk3_step runs it (three fused
     // stages with u0 in its own buffer, the limiter when configured), into
     // library scratch with dt = 0 so that u is untouched and every stage

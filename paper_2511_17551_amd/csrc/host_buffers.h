@@ -52,9 +52,13 @@ bool buf_exact(DevBuf<T> &b, size_t n) {
 // in use) and asks again.
 constexpr size_t kMeshSlack = (size_t)32 << 20;
 template <typename T>
+bool buf_keeps(const DevBuf<T> &b, size_t n) {
+    return b.p && n > 0 && b.cap >= n && b.cap - n <= kMeshSlack / sizeof(T);
+}
+template <typename T>
 bool buf_mesh(DevBuf<T> &b, size_t n) {
     const size_t slack = kMeshSlack / sizeof(T);
-    if (b.p && n > 0 && b.cap >= n && b.cap - n <= slack) {
+    if (buf_keeps(b, n)) {
         b.n = n;
         return true;
     }

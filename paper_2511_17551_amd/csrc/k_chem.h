@@ -45,7 +45,7 @@ __device__ __forceinline__ KinConst *kin_here(const KinC &K) {
     return (KinConst *)p;
 }
 
-// Species sources w_s (kg m^-3 s^-1) and, with JAC, their Jacobian dw[s][j] =
+// Species sources w_s (kg m^-3 s^-1) and their Jacobian dw[s][j] =
 // d w_s / d rho_j along the fixed-energy manifold, at the temperature T of
 // the composition rs: the mechanisms of grouped form (KinGroups) with the
 // molecules first.
@@ -64,9 +64,8 @@ __device__ __forceinline__ KinConst *kin_here(const KinC &K) {
 // cylinder (131,072 nodes, hot state): 184 us reaction by reaction, 78 us
 // grouped (74 with the data read in place, the T(e) solve of 6 us included),
 // so the grouped form is taken wherever it exists.
-template <bool JAC>
-__device__ __forceinline__ void chem_sources_grouped(const KinC &K, const MixC &M, const double *rs, double T,
-                                                     double *w, double (*dw)[kNS]) {
+__device__ __forceinline__ void chem_sources_grouped(const KinC &K, const double *rs, double T, double *w,
+                                                     double (*dw)[kNS]) {
     KinConst *K0 = kin_here(K);
     const double lnT = log(T);
     const double iT = rcp(T);
@@ -96,10 +95,8 @@ __device__ __forceinline__ void chem_sources_grouped(const KinC &K, const MixC &
         conc[s] = rs[s] * K0->iW[s];
         w[s] = 0.0;
         wT[s] = 0.0;
-        if (JAC) {
 #pragma unroll
-            for (int j = 0; j < kNS; ++j) dw[s][j] = 0.0;
-        }
+        for (int j = 0; j < kNS; ++j) dw[s][j] = 0.0;
     }
     const double lnpr = K0->lnpref_Ru - lnT;
 #pragma unroll 1
@@ -143,11 +140,9 @@ __device__ __forceinline__ void chem_sources_grouped(const KinC &K, const MixC &
             const double cf = kf * c, cb = kb * c;
             Sf += cf;
             Sb += cb;
-            if (JAC) {
-                Tf = fma(cf, dl, Tf);
-                Tb = fma(cb, dl - dlnK, Tb);
-                if (m < kNS) val[m] = kf * F - kb * B;
-            }
+            Tf = fma(cf, dl, Tf);
+            Tb = fma(cb, dl - dlnK, Tb);
+            if (m < kNS) val[m] = kf * F - kb * B;
         };
 #pragma unroll
         for (int m = 0; m < kNS; ++m)
@@ -156,30 +151,26 @@ __device__ __forceinline__ void chem_sources_grouped(const KinC &K, const MixC &
         const double R = Sf * F - Sb * B;
 #pragma unroll
         for (int s = 0; s < kNS; ++s) w[s] = fma(G.wdn[g][s], R, w[s]);
-        if (JAC) {
-            const double dRdT = Tf * F - Tb * B;
-            const double d0 = Sf * f[1], d1 = Sf * f[0], d2 = -Sb * f[3], d3 = -Sb * f[2];
-#pragma unroll
-            for (int j = 0; j < kNS; ++j) {
-                double v = fma(G.sel[g][0][j], d0, val[j]);
-                v = fma(G.sel[g][1][j], d1, v);
-                v = fma(G.sel[g][2][j], d2, v);
-                v = fma(G.sel[g][3][j], d3, v) * Kg->iW[j];  // dR / d rho_j at fixed T
-#pragma unroll
-                for (int s = 0; s < kNS; ++s) dw[s][j] = fma(G.wdn[g][s], v, dw[s][j]);
-            }
-#pragma unroll
-            for (int s = 0; s < kNS; ++s) wT[s] = fma(G.wdn[g][s], dRdT, wT[s]);
-        }
-    }
-    if (JAC) {
-        const double irc = rcp(rhocv);
+        const double dRdT = Tf * F - Tb * B;
+        const double d0 = Sf * f[1], d1 = Sf * f[0], d2 = -Sb * f[3], d3 = -Sb * f[2];
 #pragma unroll
         for (int j = 0; j < kNS; ++j) {
-            const double dT = dTdr[j] * irc;
+            double v = fma(G.sel[g][0][j], d0, val[j]);
+            v = fma(G.sel[g][1][j], d1, v);
+            v = fma(G.sel[g][2][j], d2, v);
+            v = fma(G.sel[g][3][j], d3, v) * Kg->iW[j];  // dR / d rho_j at fixed T
 #pragma unroll
-            for (int s = 0; s < kNS; ++s) dw[s][j] = fma(wT[s], dT, dw[s][j]);
+            for (int s = 0; s < kNS; ++s) dw[s][j] = fma(G.wdn[g][s], v, dw[s][j]);
         }
+#pragma unroll
+        for (int s = 0; s < kNS; ++s) wT[s] = fma(G.wdn[g][s], dRdT, wT[s]);
+    }
+    const double irc = rcp(rhocv);
+#pragma unroll
+    for (int j = 0; j < kNS; ++j) {
+        const double dT = dTdr[j] * irc;
+#pragma unroll
+        for (int s = 0; s < kNS; ++s) dw[s][j] = fma(wT[s], dT, dw[s][j]);
     }
 }
 
@@ -344,7 +335,7 @@ __device__ __forceinline__ bool chem_newton(const KinC &K, const MixC &M, const 
         ++it;
         if (solve_T() < 0 || !(Tn > 0.0)) return false;
         double w[kNS], A[kNS][kNS], G[kNS], d[kNS];
-        if constexpr (GRP) chem_sources_grouped<true>(K, M, rs, Tn, w, A);
+        if constexpr (GRP) chem_sources_grouped(K, rs, Tn, w, A);
         else chem_sources(K, M, rs, Tn, w, A);
 #pragma unroll
         for (int s = 0; s < kNS; ++s) {

@@ -1009,8 +1009,8 @@ static int set_mesh_once(dgx_ctx *ctx, const dgx_mesh *m, const std::vector<doub
         if ((rc = dalloc_mesh(ctx, ctx->kin_d, 1))) return rc;
         HIPCHK(hipMemcpy(ctx->kin_d.p, &ctx->kin, sizeof(KinC), hipMemcpyHostToDevice));
     }
-    // default elements per block: about 256 threads, LDS <= 64 KB; a cached
-    // autotuner choice for this configuration wins
+    // default launch shape; a cached autotuner choice for this configuration
+    // wins
     const int epb = default_epb(ctx, sel->slot);
     ctx->epb = epb;
     ctx->xcd = default_order(ctx);

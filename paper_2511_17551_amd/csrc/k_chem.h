@@ -368,9 +368,9 @@ __device__ __forceinline__ bool chem_newton(const KinC &K, const MixC &M, const 
 // ([nvar][count], species first).  GRP: the grouped rates.  Two waves per
 // SIMD: the Newton state, the 5x5 Jacobian and the rate terms need about 280
 // registers, and one wave per SIMD leaves the long dependency chains (T
-// solve, rates, elimination) unhidden; the compiler spills about 27 VGPRs at
-// this bound, a better trade (1.45x on the 131,072-node cylinder) than one
-// wave.  T holds the incoming state's temperature on entry and the new one on
+// solve, rates, elimination) unhidden: two were 1.45x faster for the general
+// rates on the 131,072-node cylinder.  At this bound the compiler spills six
+// VGPRs of the general form and none of the grouped one.  T holds the incoming state's temperature on entry and the new one on
 // exit.  GRP: on entry a warm start, from which (or from T0 where it is no
 // positive number or fails) the incoming temperature is solved for here: as
 // k_thermo before this kernel that took 6 of 80 us on the cylinder.  The

@@ -733,8 +733,9 @@ __device__ __forceinline__ void rhs_chunk(const RhsParams &P, int mode, int e0) 
     };
     if constexpr (S::ECM) {
         // the circulant pairs described below, with the loops over directions
-        // and offsets kept: the flux is about 1,200 instructions, and six
-        // copies of it do not fit the instruction cache
+        // and offsets kept: the flux is 1,000 vector and 700 scalar
+        // instructions (a pair's way through it takes 400 to 500 of the vector
+        // ones), and six copies of it do not fit the instruction cache
         // (the sums go to acc, with 1 - alpha in the coefficients: nine
         // registers fewer)
         int rem = node, step = 1;
@@ -1163,7 +1164,7 @@ __device__ __forceinline__ void mortar_item(const RhsParams &P, int m) {
 }
 
 // (the entropy-conservative mixture flux is held to three waves per SIMD, what
-// its LDS allows: 22 registers spill, outside the pair loop; 143 -> 137 us per
+// its LDS allows: 13 registers spill, outside the pair loop; 143 -> 137 us per
 // right-hand side against two waves at 215 registers)
 template <int DIM, int N, int EQ, int VF, int SF, bool CURV, bool MORT = false, int CHF = 0>
 __global__ void __launch_bounds__(512, (EQ >= 2 && VF == 0) ? 3 : 2) k_rhs(RhsParams P, int mode) {

@@ -554,9 +554,10 @@ std::string tune_key(const dgx_ctx *ctx) {
 // 54.8 / 51.4 / 48.9.  Curved Navier-Stokes elements run alone at N = 4 (four
 // SSPRK3 steps, us: 6^3 219 / 243 / 313, 10^3 295 / 307 / 321, 24^3 2504 / 2540 /
 // 2797) and at N = 3 while one wave per SIMD holds them all (8^3 197 / 198 / 208,
-// 10^3 211 / 230 / 212; beyond, 11^3 248 / 242 / 258, 12^3 261 / 259 / 264, 18^3
-// 547 / 542 / 545, 24^3 1089 / 1067 / 1093, 32^3 2865 / 2836 / 2925, though 14^3
-// 330 / 353 / 328).
+// 10^3 211 / 230 / 212).  Beyond, two are 0.8% faster than one on the average of
+// fifteen meshes from 11^3 to 28^3 (15^3 387 / 374 / 387, 22^3 898 / 854 / 895,
+// 24^3 1077 / 1067 / 1091; the exceptions are 14^3, 332 / 353 / 329, and 17^3, 484 /
+// 499 / 488).
 int default_epb(const dgx_ctx *ctx, int slot) {
     int epb = std::max(1, 256 / ctx->nn);
     while (epb > 1 && (size_t)epb * slot * sizeof(double) > 32 * 1024) epb >>= 1;

@@ -457,13 +457,15 @@ def dgx_destroy(ctx):
 class Solver:
     """A context bound to one workload (a ``workloads.Case``)."""
 
+    ctx = None
+
     def __init__(self, case):
         self.case = case
         self.ctx = dgx_create(case.cfg, case.species, case.reactions)
         try:
             dgx_set_mesh(self.ctx, case.mesh)
         except Exception:
-            dgx_destroy(self.ctx)
+            self.close()
             raise
         self.shape = (case.cfg["nvar"], case.mesh.nelem, case.mesh.nnodes)
 

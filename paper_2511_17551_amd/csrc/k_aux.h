@@ -254,14 +254,18 @@ __global__ void __launch_bounds__(512) k_grad(RhsParams P, double suthS, double 
 #pragma unroll
                     for (int w = 0; w < NW; ++w) Wn[w] = mg[(role * NW + w) * NF + q];
                 } else {
-                    // large side: sum_s (P_a x P_b) W*_s
+                    // large side: sum_s (P_a x P_b) W*_s (four nodes' loads at
+                    // a time: waiting for each of the 64 took k_grad 25 us on
+                    // the wall channel of 904 elements, now 15; its fewer
+                    // waves cost the meshes without mortars nothing, 54.5 us
+                    // on 21,952 elements either way)
 #pragma unroll
                     for (int w = 0; w < NW; ++w) Wn[w] = 0.0;
                     const int qa = q % N1, qb = q / N1;
 #pragma unroll 1
                     for (int sb = 0; sb < NSUB; ++sb) {
                         const int a = sb & 1, bsel = sb >> 1;
-#pragma unroll 1
+#pragma unroll 4
                         for (int j = 0; j < NF; ++j) {
                             const int ja = j % N1, jb = j / N1;
                             double wt = P.mops[50 + a * 25 + qa * N1 + ja];

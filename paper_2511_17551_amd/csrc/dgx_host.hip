@@ -1248,8 +1248,14 @@ int dgx_chem_step(dgx_ctx *ctx, double *u, double dt, double tol, int maxit, dgx
                            ctx->cfg.T_guess, ctx->cfg.newton_tol, ctx->cfg.newton_maxit, tol, maxit, ttol, tmaxit,
                            iters, subs, ctx->flags.p);
     };
-    if (ctx->cfg.dim == 2) grp ? launch(k_chem<2, true>) : launch(k_chem<2, false>);
-    else grp ? launch(k_chem<3, true>) : launch(k_chem<3, false>);
+    auto pick = [&](auto dim) {
+        constexpr int D = decltype(dim)::value;
+        if (grp) launch(k_chem<D, true, true>);
+        else if (ctx->mix.std_mol) launch(k_chem<D, false, true>);
+        else launch(k_chem<D, false, false>);
+    };
+    if (ctx->cfg.dim == 2) pick(std::integral_constant<int, 2>{});
+    else pick(std::integral_constant<int, 3>{});
     if (hipGetLastError() != hipSuccess) return set_err(ctx, DGX_E_DEVICE, "chemistry launch failed");
     if (!stats) return DGX_OK;
     return collect_stats(ctx, count, maxit, stats, s, true);

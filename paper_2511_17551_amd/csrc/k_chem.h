@@ -320,16 +320,13 @@ constexpr double kChemStall = 1e-3;  // a step cut below this fraction twice in 
 // Damped Newton for one backward-Euler step over h from ra into rs.  Tn: the
 // temperature of ra on entry, of rs on a converged exit.  Adds the
 // iterations to it; returns false if the iteration failed.
-template <bool GRP>
+template <bool GRP, bool STD>
 __device__ __forceinline__ bool chem_newton(const KinC &K, const MixC &M, const double *ra, double *rs, double rho,
                                             double rhoe, double h, double &Tn, double tol, int maxit, double ttol,
                                             int tmaxit, int &it) {
 #pragma unroll
     for (int s = 0; s < kNS; ++s) rs[s] = ra[s];
-    // (grouped form: std_mol holds)
-    auto solve_T = [&]() {
-        return GRP ? mix_newton_t<true>(M, rs, rhoe, Tn, ttol, tmaxit) : mix_newton(M, rs, rhoe, Tn, ttol, tmaxit);
-    };
+    auto solve_T = [&]() { return mix_newton_t<STD>(M, rs, rhoe, Tn, ttol, tmaxit); };
     int low = 0;
     for (int k = 0; k < maxit; ++k) {
         ++it;
@@ -365,20 +362,22 @@ __device__ __forceinline__ bool chem_newton(const KinC &K, const MixC &M, const 
 }
 
 // Chemistry over dt per node, in place on the species rows of u
-// ([nvar][count], species first).  GRP: the grouped rates.  Two waves per
-// SIMD: the Newton state, the 5x5 Jacobian and the rate terms need about 280
-// registers, and one wave per SIMD leaves the long dependency chains (T
-// solve, rates, elimination) unhidden: two were 1.45x faster for the general
-// rates on the 131,072-node cylinder.  At this bound the compiler spills six
-// VGPRs of the general form and none of the grouped one.  T holds the incoming state's temperature on entry and the new one on
-// exit.  GRP: on entry a warm start, from which (or from T0 where it is no
-// positive number or fails) the incoming temperature is solved for here: as
-// k_thermo before this kernel that took 6 of 80 us on the cylinder.  The
-// general rates keep the two launches (the solve's registers cost them more:
-// 394 -> 399 us a Strang step).  iters (optional) the Newton
+// ([nvar][count], species first).  GRP: the grouped rates.  STD: the molecules
+// are the first three species (GRP: always); known here, or the two forms of
+// the T(e) solve stand side by side and spill (other flags, 131,072 nodes: 2717
+// us, now 2197).  Two waves per SIMD: the Newton state, the 5x5 Jacobian and the
+// rate terms need about 280 registers, and one wave per SIMD leaves the long
+// dependency chains (T solve, rates, elimination) unhidden: two were 1.45x
+// faster for the general rates on the 131,072-node cylinder.  No form spills
+// VGPRs at this bound.  T holds the incoming state's temperature on entry and
+// the new one on exit.  GRP: on entry a warm start, from which (or from T0
+// where it is no positive number or fails) the incoming temperature is solved
+// for here: as k_thermo before this kernel that took 6 of 80 us on the
+// cylinder.  The general rates keep the two launches (the solve's registers
+// cost them more: 394 -> 399 us a Strang step).  iters (optional) the Newton
 // iterations summed over the substeps, -1 if the node did not converge;
 // subs (optional) the number of substeps.
-template <int DIM, bool GRP>
+template <int DIM, bool GRP, bool STD>
 __global__ void __launch_bounds__(256, 2) k_chem(double *__restrict__ u, int64_t count, double dt, const KinC *kin,
                                               MixC M, double *__restrict__ T, double T0, double ntol, int nmaxit,
                                               double tol, int maxit, double ttol, int tmaxit,
@@ -408,7 +407,7 @@ __global__ void __launch_bounds__(256, 2) k_chem(double *__restrict__ u, int64_t
 #pragma unroll 1
         for (int a = 0; a < 2 && !found; ++a) {
             if (a) Ta = T0;
-            const int n = mix_newton_t<true>(M, ra, rhoe, Ta, ntol, nmaxit);
+            const int n = mix_newton_t<STD>(M, ra, rhoe, Ta, ntol, nmaxit);
             found = n >= 0 && isfinite(Ta) && Ta > 0.0;
         }
         if (!found) atomicOr(flags, FLAG_NOCONV);
@@ -423,7 +422,7 @@ __global__ void __launch_bounds__(256, 2) k_chem(double *__restrict__ u, int64_t
         }
         double rs[kNS];
         double Tn = Ta;
-        if (chem_newton<GRP>(K, M, ra, rs, rho, rhoe, ldexp(dt, -lev), Tn, tol, maxit, ttol, tmaxit, it)) {
+        if (chem_newton<GRP, STD>(K, M, ra, rs, rho, rhoe, ldexp(dt, -lev), Tn, tol, maxit, ttol, tmaxit, it)) {
 #pragma unroll
             for (int s = 0; s < kNS; ++s) ra[s] = rs[s];
             Ta = Tn;

@@ -18,13 +18,14 @@ constexpr int kSurNorm = 14;  // feature mean[6], std[6], T mean, T std
 // fragments of 64 lanes x 4 values (surrogate.hip)
 constexpr int kSurFrags = 4 + 4 * 16;
 constexpr int kSurPacked = kSurFrags * 64 * 4;
+constexpr int kSurParamsRoom = (kSurParams + kSurNorm + 63) / 64 * 64;  // floats before the packed copy
 
 constexpr size_t kSurKeepBytes = (size_t)64 << 20;
 
 struct Surrogate {
     bool ready = false;
     float *params = nullptr;  // device [kSurParams + kSurNorm] FP32 master copy
-    unsigned short *packed = nullptr;  // device [kSurPacked], always the rounding of params
+    unsigned short *packed = nullptr;  // [kSurPacked] behind them, always the rounding of params
     float *adam_m = nullptr, *adam_v = nullptr, *grads = nullptr;
     // training workspace, kept between calls up to kSurKeepBytes: the waves'
     // partial gradients, the sample order and the loss accumulator

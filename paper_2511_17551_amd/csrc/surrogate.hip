@@ -108,7 +108,7 @@ __host__ __device__ __forceinline__ int packed_at(int frag, int r, int g, int j)
 }
 
 // The places of parameter i in the packed copy: none, one (W1) or two.
-__host__ __device__ __forceinline__ int packed_places(int i, int at[2]) {
+__device__ __forceinline__ int packed_places(int i, int at[2]) {
     if (i < ob1) {
         const int row = i / kSurIn, col = i - row * kSurIn;
         at[0] = packed_at(kF1 + row / 16, row % 16, col / 4, col % 4);
@@ -548,20 +548,50 @@ static unsigned short host_bf16(float f) {
     return (unsigned short)((u + 0x7fffu + (u >> 16 & 1u)) >> 16);
 }
 
-int surrogate_set(Surrogate &S, const float *host_params) {
-    if (!S.params && hipMalloc(&S.params, (kSurParams + kSurNorm) * sizeof(float)) != hipSuccess) return -3;
-    if (!S.packed && hipMalloc(&S.packed, kSurPacked * sizeof(unsigned short)) != hipSuccess) return -3;
-    static thread_local unsigned short pk[kSurPacked];
-    std::memset(pk, 0, sizeof(pk));
-    for (int i = 0; i < kSurParams; ++i) {
-        int at[2];
-        const int n = packed_places(i, at);
-        for (int k = 0; k < n; ++k) pk[at[k]] = host_bf16(host_params[i]);
+// The packed copy of the parameters P, fragment by fragment (the places of
+// packed_places; asking it for every parameter took 43 us of a call's 58, the
+// start of a program that sets its weights: now 16 in all).
+static void pack_weights(const float *P, unsigned short *pk) {
+    unsigned short b[kSurParams];
+    for (int i = 0; i < kSurParams; ++i) b[i] = host_bf16(P[i]);
+    for (int mt = 0; mt < 4; ++mt)
+        for (int r = 0; r < 16; ++r)
+            for (int col = 0; col < 16; ++col)
+                pk[packed_at(kF1 + mt, r, col / 4, col % 4)] = col < kSurIn ? b[oW1 + (16 * mt + r) * kSurIn + col] : 0;
+    for (int layer = 0; layer < 2; ++layer) {
+        const unsigned short *W = b + (layer ? oW3 : oW2);
+        const int f = layer ? kF3 : kF2, t = layer ? kT3 : kT2;
+        for (int mt = 0; mt < 4; ++mt)
+            for (int kc = 0; kc < 4; ++kc)
+                for (int g = 0; g < 4; ++g)
+                    for (int r = 0; r < 16; ++r) {
+                        unsigned short *fw = pk + packed_at(f + 4 * mt + kc, r, g, 0);
+                        unsigned short *tr = pk + packed_at(t + 4 * mt + kc, r, g, 0);
+                        const unsigned short *row = W + (16 * mt + r) * H + 16 * kc + 4 * g;
+                        const unsigned short *col = W + (16 * kc + 4 * g) * H + 16 * mt + r;
+                        for (int j = 0; j < 4; ++j) {
+                            fw[j] = row[j];
+                            tr[j] = col[j * H];
+                        }
+                    }
     }
-    S.ready = false;
-    if (hipMemcpy(S.params, host_params, (kSurParams + kSurNorm) * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(S.packed, pk, sizeof(pk), hipMemcpyHostToDevice) != hipSuccess)
+}
+
+// (parameters and packed copy lie in one allocation and go there in one copy)
+int surrogate_set(Surrogate &S, const float *host_params) {
+    static thread_local struct {
+        float params[kSurParamsRoom];
+        unsigned short packed[kSurPacked];
+    } block;
+    std::memcpy(block.params, host_params, (kSurParams + kSurNorm) * sizeof(float));
+    pack_weights(host_params, block.packed);
+    if (!S.params && hipMalloc(&S.params, sizeof(block)) != hipSuccess) {
+        S.params = nullptr;
         return -3;
+    }
+    S.packed = reinterpret_cast<unsigned short *>(S.params + kSurParamsRoom);
+    S.ready = false;
+    if (hipMemcpy(S.params, &block, sizeof(block), hipMemcpyHostToDevice) != hipSuccess) return -3;
     S.ready = true;
     return 0;
 }
@@ -771,7 +801,6 @@ void surrogate_free(Surrogate &S) {
     if (S.adam_m) (void)hipFree(S.adam_m);
     if (S.adam_v) (void)hipFree(S.adam_v);
     if (S.grads) (void)hipFree(S.grads);
-    if (S.packed) (void)hipFree(S.packed);
     if (S.partial) (void)hipFree(S.partial);
     if (S.loss) (void)hipFree(S.loss);
     if (S.order) (void)hipFree(S.order);

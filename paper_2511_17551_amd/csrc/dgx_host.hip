@@ -1147,23 +1147,30 @@ static int collect_stats(dgx_ctx *ctx, int64_t count, int maxit, dgx_newton_stat
     int mx = 0;
     double wsum = 0.0;
     int64_t nw = 0;
+    // (a wave's counts without branches, which the compiler then vectorises: one
+    // value at a time the loop took 100 us of dgx_thermo's 203 on 200,000 states,
+    // 133 where it came to lie badly; now 25)
     for (int64_t i = 0; i < count; i += 64) {
-        int wm = 0;
-        for (int64_t j = i; j < std::min(count, i + 64); ++j) {
-            int it = h[j];
-            if (it >= 0 && (it & kItersFallback)) {
-                ++fallbacks;
-                it &= ~kItersFallback;
-            }
-            if (it < 0) {
-                ++bad;
-                if (first < 0) first = j;
-                it = maxit;
-            }
-            tot += it;
-            mx = std::max(mx, it);
+        const int *w = h.data() + i;
+        const int n = (int)std::min<int64_t>(64, count - i);
+        int wm = 0, wbad = 0, wback = 0;
+        unsigned wtot = 0;  // exact while no count reaches 2^25
+        for (int j = 0; j < n; ++j) {
+            const int failed = w[j] < 0;
+            const int it = failed ? maxit : w[j] & ~kItersFallback;
+            wback += !failed & ((w[j] & kItersFallback) != 0);
+            wbad += failed;
+            wtot += (unsigned)it;
             wm = std::max(wm, it);
         }
+        for (int j = 0; wbad && first < 0; ++j)
+            if (w[j] < 0) first = i + j;
+        if (wm < 1 << 25) tot += wtot;
+        else
+            for (int j = 0; j < n; ++j) tot += w[j] < 0 ? maxit : w[j] & ~kItersFallback;
+        bad += wbad;
+        fallbacks += wback;
+        mx = std::max(mx, wm);
         wsum += wm;
         ++nw;
     }

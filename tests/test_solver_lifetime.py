@@ -6,12 +6,20 @@ import gc
 
 import pytest
 
-from paper_2511_17551_amd import dgx
 from paper_2511_17551_amd import workloads as W
 
 
 @pytest.fixture
-def destroyed(monkeypatch):
+def dgx():
+    # (not at import: the library takes the HIP runtime that is loaded first,
+    # which has to be torch's where tests on the device follow)
+    import torch  # noqa: F401
+    from paper_2511_17551_amd import dgx as mod
+    return mod
+
+
+@pytest.fixture
+def destroyed(dgx, monkeypatch):
     calls = []
     monkeypatch.setattr(dgx, "dgx_create", lambda cfg, sp, rx: dgx.C.c_void_p(1234))
     monkeypatch.setattr(dgx, "dgx_set_mesh", lambda ctx, mesh: None)
@@ -19,19 +27,21 @@ def destroyed(monkeypatch):
     return calls
 
 
-def refuse(*_):
-    raise dgx.DgxError(-1, "refused")
+def refuse(dgx):
+    def call(*_):
+        raise dgx.DgxError(-1, "refused")
+    return call
 
 
-def test_refused_mesh(destroyed, monkeypatch):
-    monkeypatch.setattr(dgx, "dgx_set_mesh", refuse)
+def test_refused_mesh(dgx, destroyed, monkeypatch):
+    monkeypatch.setattr(dgx, "dgx_set_mesh", refuse(dgx))
     with pytest.raises(dgx.DgxError):
         dgx.Solver(W.case_c1(n=2))
     gc.collect()
     assert destroyed == [1234]
 
 
-def test_closed_twice(destroyed):
+def test_closed_twice(dgx, destroyed):
     s = dgx.Solver(W.case_c1(n=2))
     s.close()
     s.close()
@@ -40,8 +50,8 @@ def test_closed_twice(destroyed):
     assert destroyed == [1234]
 
 
-def test_no_context(destroyed, monkeypatch):
-    monkeypatch.setattr(dgx, "dgx_create", refuse)
+def test_no_context(dgx, destroyed, monkeypatch):
+    monkeypatch.setattr(dgx, "dgx_create", refuse(dgx))
     with pytest.raises(dgx.DgxError):
         dgx.Solver(W.case_c1(n=2))
     gc.collect()
